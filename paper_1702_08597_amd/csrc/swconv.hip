@@ -20,6 +20,7 @@
 #include "swconv_dense_mfma.hpp"
 #include "swconv_fused_kernels.hpp"
 #include "swconv_kernels.hpp"
+#include "swconv_pack_kernels.hpp"
 #include "swconv_prune_kernels.hpp"
 
 using namespace swconv;
@@ -93,6 +94,17 @@ int upload(T** dptr, const std::vector<T>& h, size_t* cap = nullptr) {
   return SWCONV_OK;
 }
 
+// A device buffer of at least `bytes`, its contents undefined; kept while it is large enough.
+int reserve(void** dptr, size_t* cap, size_t bytes) {
+  if (*dptr && *cap >= bytes) return SWCONV_OK;
+  if (*dptr) (void)hipFree(*dptr);
+  *dptr = nullptr;
+  *cap = 0;
+  HIP_TRY(hipMalloc(dptr, std::max<size_t>(bytes, 256)));
+  *cap = bytes;
+  return SWCONV_OK;
+}
+
 }  // namespace
 
 // One position-wise sparse operand of the sparse product kernel in its packed form: P matrices of
@@ -107,6 +119,11 @@ struct PackedMatrix {
   int cus = 256;                      // compute units of the device
   int n_wgs_used = 0;                 // workgroups the current schedule uses
   bool packed = false, on_device = false;
+  size_t n_pairs = 0;                 // (row offset, weight) pairs of the stream, spare ones included
+  int n_slices = 0;
+  // The host copies below: what pack_matrix made, or nothing yet after a packing on the device
+  // (fetch_packed_host brings them over when something reads them).
+  bool host_current = false;
   int64_t nnz = 0, padded_nnz = 0, max_item = 0;
   std::vector<uint32_t> stream;       // 512-byte batches of (row offset, weight) pairs
   std::vector<Slice> slices;          // P * rows_padded / kSliceRows
@@ -120,7 +137,13 @@ struct PackedMatrix {
   Slice* d_slices = nullptr;
   WorkItem* d_items = nullptr;
   RangeHeader* d_ranges = nullptr;
-  size_t cap_stream = 0, cap_slices = 0, cap_items = 0, cap_ranges = 0;  // bytes of the four allocations
+  int32_t* d_index = nullptr;         // entry_index on the device; current when index_current is set
+  bool index_current = false;
+  size_t cap_stream = 0, cap_slices = 0, cap_items = 0, cap_ranges = 0, cap_index = 0;  // bytes of the allocations
+  // tables between the two launches of a packing on the device
+  PackTables tables{};
+  int32_t* d_tables = nullptr;
+  size_t cap_tables = 0;
 };
 
 // W_F packed for the fused product + output transform kernel (m = 2, few input channels): rows in
@@ -133,6 +156,7 @@ struct FusedProduct {
   bool ready = false;     // the current weights fit its format and are on the device
   int KC = 0;             // row chunks of kFusedRows
   int B = 0;              // batches per slice and position (the longest row decides)
+  size_t n_dwords = 0;    // of wpk
   std::vector<uint32_t> wpk;
   std::vector<int32_t> value_index;  // per pair of wpk: index into the caller's value array, -1 = padding
   std::vector<uint8_t> lens;
@@ -172,14 +196,14 @@ struct swconv_plan {
   GradTile* d_gtiles = nullptr;
   float* d_partial = nullptr; // backward pass: [tile blocks][stream entries of W_F] partial dot products
   size_t partial_floats = 0;
-  int32_t* d_entry_index = nullptr;
-  size_t cap_entry_index = 0;
-  bool index_current = false;
   // swconv_update_values: the device streams hold newer values than the host copies
   bool host_values_stale = false;
-  std::vector<int32_t> bt_value_index;  // per pair of the packed W_F^T: index into the caller's value array
-  int32_t* d_bt_value_index = nullptr;
-  size_t cap_bt_value_index = 0;
+  bool host_pattern = true;  // the weights came through swconv_set_weights
+  // packing on the device: what launch 1 reports (pinned host memory), and the transpose's bit matrix
+  PackReport* h_report = nullptr;
+  int32_t* h_bad_cols = nullptr;
+  uint32_t* d_bits = nullptr;
+  size_t cap_bits = 0;
   bool ran_backward = false;
   float* d_wdense = nullptr;  // [P][C][Kq]
 };
@@ -310,9 +334,9 @@ int launch_spmm_t(const swconv_plan* pl, const PackedMatrix& pm, const LaunchTar
     attr_set = true;
   }
   return launch_kernel(kern, dim3(pm.n_wgs_used), dim3(NW * 64), lds, to, X, Y, pm.d_stream,
-                       (uint32_t)(pm.stream.size() * sizeof(uint32_t)), pm.d_slices, (int)pm.slices.size(),
+                       (uint32_t)(pm.n_pairs * 2 * sizeof(uint32_t)), pm.d_slices, pm.n_slices,
                        pm.d_items, pm.d_ranges, pm.n_wgs_used, pm.cols, pm.rows, pl->g.Tp, y_bytes, x_bytes, partial,
-                       (uint32_t)(pm.stream.size() / 2));
+                       (uint32_t)pm.n_pairs);
 }
 
 template <bool SAMPLED>
@@ -341,7 +365,7 @@ int launch_product_output_t(const swconv_plan* pl, const LaunchTarget& to, const
   }
   const int n_wgs = pl->n_tau_blocks * fz.KC;
   return launch_kernel(kern, dim3(n_wgs), dim3(kFusedWaves * 64), lds, to, V, out,
-                       (const uint32_t*)fz.d_wpk, (uint32_t)(fz.wpk.size() * sizeof(uint32_t)),
+                       (const uint32_t*)fz.d_wpk, (uint32_t)(fz.n_dwords * sizeof(uint32_t)),
                        (const uint8_t*)fz.d_lens, (const OutTile*)fz.d_otiles, g.C, g.K, g.Tp, fz.KC, fz.B, n_wgs,
                        g.v_bytes, (uint32_t)(g.Ho * g.Wo), g.Wo, (uint32_t)g.out_image_stride,
                        (uint32_t)((int64_t)g.N * g.out_image_stride * (int64_t)sizeof(float)));
@@ -359,7 +383,7 @@ int launch_product_output4_t(const swconv_plan* pl, const LaunchTarget& to, cons
   const FusedProduct& fz = pl->fz;
   const int n_wgs = pl->n_tau_blocks * fz.KC;
   return launch_kernel(product_output4_kernel<3, G>, dim3(n_wgs), dim3(kFusedWaves * 64), 0, to, V, out,
-                       (const uint32_t*)fz.d_wpk, (uint32_t)(fz.wpk.size() * sizeof(uint32_t)),
+                       (const uint32_t*)fz.d_wpk, (uint32_t)(fz.n_dwords * sizeof(uint32_t)),
                        (const uint8_t*)fz.d_lens, (const TileInfo*)pl->d_tiles, (const BlockImage*)pl->d_blocks, fz.KC,
                        fz.B, n_wgs, pl->g);
 }
@@ -458,24 +482,35 @@ void build_transform_tables(swconv_plan* pl) {
   }
 }
 
+// Sizes of W_F's package format for the fused kernel; false (and the three-kernel path runs) when the layer is
+// not eligible or a row is longer than the kernel's batches hold.
+bool size_fused(swconv_plan* pl, int longest_row) {
+  FusedProduct& fz = pl->fz;
+  if (!fz.eligible) return false;
+  const bool units = fz.out_tile == 4;  // F(4x4,3x3): whole units of two batches
+  fz.KC = (pl->g.K + kFusedRows - 1) / kFusedRows;
+  fz.B = std::max(1, (longest_row + kBatchSteps - 1) / kBatchSteps);
+  if (units) fz.B = (fz.B + 1) / 2 * 2;
+  if (fz.B > (units ? kFused4MaxBatches : kFusedMaxBatches)) return false;
+  fz.n_dwords = (size_t)pl->P * fz.KC * fz.B * kFusedWaves * 128;
+  // The F(4x4,3x3) kernel runs only where asked for (SWCONV_FUSE_OUTPUT=2): with 64 + 16 accumulators per
+  // lane it holds 16 waves per CU, its vector ALU stays at about two thirds busy between the barriers of
+  // the 36 positions, and on the 56 x 56 layer it measured 217 us against 188 us for the two kernels.
+  fz.wanted = fz.out_tile == 2 || fz.mode == 2;
+  return fz.n_dwords * 4 < ((size_t)1 << 32) - 4096;
+}
+
 // Packs W_F for the fused kernel: rows in natural order; slice s of position p = rows 4s .. 4s+3,
-// workgroup chunk kc = slices 16 kc .. 16 kc + 15.  Not ready (and the three-kernel path runs) when
-// a row is longer than the kernel's batches hold.
+// workgroup chunk kc = slices 16 kc .. 16 kc + 15.
 void pack_fused(swconv_plan* pl, const int32_t* rowptr, const int32_t* colidx, const float* vals) {
   FusedProduct& fz = pl->fz;
   fz.ready = false;
-  if (!fz.eligible) return;
   const int P = pl->P, K = pl->g.K;
-  const bool units = fz.out_tile == 4;  // F(4x4,3x3): whole units of two batches
   int32_t longest = 0;
   for (int64_t i = 0; i < (int64_t)P * K; ++i) longest = std::max(longest, rowptr[i + 1] - rowptr[i]);
-  fz.KC = (K + kFusedRows - 1) / kFusedRows;
-  fz.B = std::max(1, (longest + kBatchSteps - 1) / kBatchSteps);
-  if (units) fz.B = (fz.B + 1) / 2 * 2;
-  if (fz.B > (units ? kFused4MaxBatches : kFusedMaxBatches)) return;
+  if (!size_fused(pl, longest)) return;
   const int spp = fz.KC * kFusedWaves;
-  const size_t dwords = (size_t)P * fz.KC * fz.B * kFusedWaves * 128;
-  if (dwords * 4 >= ((size_t)1 << 32) - 4096) return;
+  const size_t dwords = fz.n_dwords;
   fz.wpk.assign(dwords, 0u);
   fz.value_index.assign(dwords / 2, -1);
   fz.lens.assign((size_t)P * spp, 0);
@@ -542,29 +577,55 @@ int validate_csr(const swconv_plan* pl, const int32_t* rowptr, const int32_t* co
   return bad.load() ? SWCONV_EINVAL : SWCONV_OK;
 }
 
+// The heaviest workgroup's padded entries.
+void count_max_item(PackedMatrix* pm) {
+  pm->max_item = 0;
+  for (int b = 0; b < pm->n_wgs_used; ++b) {
+    int64_t steps = 0;
+    for (int i = pm->wg_begin[b]; i < pm->wg_begin[b + 1]; ++i)
+      for (int sidx = pm->items[i].slice_begin; sidx < pm->items[i].slice_end; ++sidx) steps += pm->slices[sidx].len;
+    pm->max_item = std::max(pm->max_item, steps * kSliceRows);
+  }
+}
+
+// What the cut of the schedule needs to know besides the slices.  Costs in units of the time a workgroup
+// spends on one step of a slice (four 16-byte LDS reads per wave quarter-row, 16 FMAs per lane).  Fitted on
+// MI355X over uniform and skewed patterns: a slice costs about 32 steps on top of its own (draw, descriptor,
+// first batches, row store), staging a panel about 20 steps per KiB.
+ScheduleShape schedule_shape(const PackedMatrix& pm, int P, int ntb) {
+  ScheduleShape s;
+  s.P = P;
+  s.ntb = ntb;
+  s.spp = pm.rows_padded / kSliceRows;
+  s.item_cap = pm.item_cap;
+  s.n_launch = (int)std::min<int64_t>(std::max(1, pm.n_wgs), (int64_t)P * ntb * s.spp);
+  s.cus = pm.cus;
+  s.second_share = std::min(100, std::max(10, env_int("SWCONV_SPMM_SECOND_SHARE", 70)));
+  s.slice_ovh = env_int("SWCONV_SPMM_SLICE_COST", 32);
+  const int panel_kib = (int)(((int64_t)pm.cols * kTileBlock * (int64_t)sizeof(float) + 1023) / 1024);
+  s.panel_cost = env_int("SWCONV_SPMM_PANEL_COST_PER_KIB", 20) * panel_kib;
+  return s;
+}
+
 // Static schedule of the sparse product.  The units (position, tile block, slice), in that order,
 // form one sequence; it is cut into one contiguous range per persistent workgroup such that every
 // range costs about the same: a slice costs its stream length plus a fixed overhead, and entering
 // a new panel costs one panel load.  The smallest feasible cost per
 // range is found by bisection.  A range touches at most a few panels, consecutive ranges share
 // panels and weights (and, through xcd_contiguous_id, an XCD's L2), and the split adapts by
-// itself to positions of very different density.
+// itself to positions of very different density.  (The cut that the device makes for patterns that live
+// there, cut_schedule, has a closed form instead of the search: up to 5 % less even, and 300 us faster.)
 void build_schedule(PackedMatrix* pm, int P, int ntb) {
   const int spp = pm->rows_padded / kSliceRows;
-  // Costs in units of the time a workgroup spends on one step of a slice (four 16-byte LDS reads
-  // per wave quarter-row, 16 FMAs per lane).  Fitted on MI355X over uniform and skewed patterns: a
-  // slice costs about 32 steps on top of its own (draw, descriptor, first batches, row store),
-  // staging a panel about 20 steps per KiB.
-  const int64_t slice_ovh = env_int("SWCONV_SPMM_SLICE_COST", 32);
-  const int64_t panel_kib = ((int64_t)pm->cols * kTileBlock * (int64_t)sizeof(float) + 1023) / 1024;
-  const int64_t panel_cost = (int64_t)env_int("SWCONV_SPMM_PANEL_COST_PER_KIB", 20) * panel_kib;
+  const ScheduleShape shape = schedule_shape(*pm, P, ntb);
+  const int64_t slice_ovh = shape.slice_ovh, panel_cost = shape.panel_cost;
   const int wgs_max = std::max(1, pm->n_wgs);
 
   // Workgroups are dispatched in id order, one per CU first: where a CU holds two, the one that
   // arrived second gets the issue slots the first one leaves (the oldest wave wins) and then runs on
   // alone with half the waves.  It therefore gets a smaller range: `second_share` percent of the
   // first one's budget.  A range's workgroup follows from xcd_contiguous_id for `n_launch` workgroups.
-  const int64_t second_share = std::min(100, std::max(10, env_int("SWCONV_SPMM_SECOND_SHARE", 70)));
+  const int64_t second_share = shape.second_share;
   const int64_t floor_budget = panel_cost + [&] {
     int64_t b = 0;
     for (const Slice& sl : pm->slices) b = std::max<int64_t>(b, sl.len + slice_ovh);
@@ -572,14 +633,9 @@ void build_schedule(PackedMatrix* pm, int P, int ntb) {
   }();
   int n_launch = wgs_max;
   auto range_budget = [&](int64_t budget, int r) -> int64_t {
-    if (second_share == 100) return budget;
-    const int per = n_launch / kXcds, rem = n_launch % kXcds;
-    // ranges of XCD x start at x * per + min(x, rem)
-    int xcd = per > 0 ? std::min(kXcds - 1, r / std::max(1, per)) : 0;
-    while (xcd > 0 && r < xcd * per + std::min(xcd, rem)) --xcd;
-    const int local = r - (xcd * per + std::min(xcd, rem));
-    const bool second = local * kXcds + xcd >= pm->cus;
-    return second ? std::max(floor_budget, budget * second_share / 100) : budget;
+    ScheduleShape s = shape;
+    s.n_launch = n_launch;
+    return second_on_cu(r, s) ? std::max(floor_budget, budget * second_share / 100) : budget;
   };
 
   std::vector<int64_t> cost_before(pm->slices.size() + 1, 0);
@@ -649,13 +705,7 @@ void build_schedule(PackedMatrix* pm, int P, int ntb) {
     h.item_end = pm->wg_begin[b + 1];
     h.first = pm->items[h.item_begin];
   }
-  pm->max_item = 0;
-  for (int b = 0; b < pm->n_wgs_used; ++b) {
-    int64_t steps = 0;
-    for (int i = pm->wg_begin[b]; i < pm->wg_begin[b + 1]; ++i)
-      for (int sidx = pm->items[i].slice_begin; sidx < pm->items[i].slice_end; ++sidx) steps += pm->slices[sidx].len;
-    pm->max_item = std::max(pm->max_item, steps * kSliceRows);
-  }
+  count_max_item(pm);
 }
 
 // Dword index of the (offset, weight) pair of row q, step e of a slice whose first 512-byte batch
@@ -784,6 +834,10 @@ void pack_matrix(PackedMatrix* pm, int P, int ntb, const int32_t* rowptr, const 
     }
   });
   build_schedule(pm, P, ntb);
+  pm->n_pairs = pm->stream.size() / 2;
+  pm->n_slices = (int)pm->slices.size();
+  pm->host_current = true;
+  pm->index_current = false;
   pm->packed = true;
 }
 
@@ -825,15 +879,10 @@ int upload_packed(PackedMatrix* pm) {
 }
 
 void free_packed(PackedMatrix* pm) {
-  void* bufs[] = {pm->d_stream, pm->d_slices, pm->d_items, pm->d_ranges};
+  void* bufs[] = {pm->d_stream, pm->d_slices, pm->d_items, pm->d_ranges, pm->d_index, pm->d_tables};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
-  pm->d_stream = nullptr;
-  pm->d_slices = nullptr;
-  pm->d_items = nullptr;
-  pm->d_ranges = nullptr;
-  pm->cap_stream = pm->cap_slices = pm->cap_items = pm->cap_ranges = 0;
-  pm->on_device = false;
+  *pm = PackedMatrix{};
 }
 
 // True when the schedule of `pm` is a partition of its (position, tile block, slice) units.
@@ -867,66 +916,188 @@ int copy_padded_to_host(const float* dsrc, float* hdst, size_t rows, int T, int 
   return SWCONV_OK;
 }
 
+// Host copies of an operand that was packed on the device: stream, index, slices and schedule come over, the
+// sorted-row tables and the statistics follow from them.
+int fetch_packed_host(PackedMatrix* pm, int P) {
+  if (pm->host_current) return SWCONV_OK;
+  HIP_TRY(hipDeviceSynchronize());
+  try {
+    pm->stream.resize(pm->n_pairs * 2);
+    pm->entry_index.resize(pm->n_pairs);
+    pm->slices.resize((size_t)pm->n_slices);
+    pm->ranges.resize((size_t)pm->n_wgs_used);
+    HIP_TRY(hipMemcpy(pm->stream.data(), pm->d_stream, pm->stream.size() * sizeof(uint32_t), hipMemcpyDeviceToHost));
+    HIP_TRY(hipMemcpy(pm->entry_index.data(), pm->d_index, pm->entry_index.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
+    HIP_TRY(hipMemcpy(pm->slices.data(), pm->d_slices, pm->slices.size() * sizeof(Slice), hipMemcpyDeviceToHost));
+    HIP_TRY(hipMemcpy(pm->ranges.data(), pm->d_ranges, pm->ranges.size() * sizeof(RangeHeader), hipMemcpyDeviceToHost));
+    pm->wg_begin.assign(1, 0);
+    for (const RangeHeader& h : pm->ranges) pm->wg_begin.push_back(h.item_end);
+    pm->items.resize((size_t)pm->wg_begin.back());
+    HIP_TRY(hipMemcpy(pm->items.data(), pm->d_items, pm->items.size() * sizeof(WorkItem), hipMemcpyDeviceToHost));
+    pm->sorted_rows.assign((size_t)P * pm->rows_padded, -1);
+    pm->sorted_len.assign((size_t)P * pm->rows_padded, 0);
+    pm->padded_nnz = 0;
+    for (const Slice& sl : pm->slices) {
+      pm->padded_nnz += (int64_t)sl.len * kSliceRows;
+      for (int r = 0; r < kSliceRows; ++r) {
+        int32_t len = 0;
+        while (len < sl.len && pm->entry_index[stream_entry(sl.batch0, r, len) / 2] >= 0) ++len;
+        pm->sorted_rows[(size_t)sl.row0 + r] = sl.k[r];
+        pm->sorted_len[(size_t)sl.row0 + r] = len;
+      }
+    }
+    count_max_item(pm);
+  } catch (const std::bad_alloc&) {
+    return SWCONV_ENOMEM;
+  }
+  pm->host_current = true;
+  return SWCONV_OK;
+}
+
 // After swconv_update_values the device stream of W_F holds the current values: fetch it before
-// the host copy is read (transposition for the backward pass, export).
+// the host copy is read (export).
 int refresh_host_values(swconv_plan* pl) {
-  if (!pl->host_values_stale) return SWCONV_OK;
+  int rc = fetch_packed_host(&pl->fw, pl->P);
+  if (rc || !pl->host_values_stale) return rc;
   HIP_TRY(hipDeviceSynchronize());
   HIP_TRY(hipMemcpy(pl->fw.stream.data(), pl->fw.d_stream, pl->fw.stream.size() * sizeof(uint32_t), hipMemcpyDeviceToHost));
   pl->host_values_stale = false;
   return SWCONV_OK;
 }
 
-// Packs W_F^T (per position: C rows of (k, weight) entries, k ascending) from the packed W_F and
-// allocates the dL/dI_F workspace.  Host work; done by the first backward pass after set_weights.
-int prepare_backward(swconv_plan* pl) {
+// The index map of W_F's stream on the device, where the host made it.
+int ensure_index(PackedMatrix* pm) {
+  if (pm->index_current) return SWCONV_OK;
+  HIP_TRY(hipDeviceSynchronize());  // an earlier pass may still read the index
+  int rc = upload(&pm->d_index, pm->entry_index, &pm->cap_index);
+  if (rc) return rc;
+  HIP_TRY(hipDeviceSynchronize());
+  pm->index_current = true;
+  return SWCONV_OK;
+}
+
+// ---- packing on the device (swconv_pack_kernels.hpp) ----
+
+// Tables of the two launches, one allocation per operand.
+int reserve_tables(PackedMatrix* pm, int P) {
+  const size_t rows = (size_t)P * pm->rows_padded, pre = (size_t)P * (pm->rows_padded / kSliceRows + 1);
+  const size_t ints = 2 * rows + 2 * pre + (size_t)P * sizeof(PositionStats) / sizeof(int32_t) + rows /* rank_of */;
+  int rc = reserve((void**)&pm->d_tables, &pm->cap_tables, ints * sizeof(int32_t));
+  if (rc) return rc;
+  int32_t* at = pm->d_tables;
+  pm->tables.stats = reinterpret_cast<PositionStats*>(at);
+  at += (size_t)P * sizeof(PositionStats) / sizeof(int32_t);
+  pm->tables.order = at;
+  pm->tables.len = at + rows;
+  pm->tables.batch_pre = at + 2 * rows;
+  pm->tables.cost_pre = at + 2 * rows + pre;
+  return SWCONV_OK;
+}
+int32_t* rank_table(const PackedMatrix& pm, int P) {
+  return pm.tables.cost_pre + (size_t)P * (pm.rows_padded / kSliceRows + 1);
+}
+
+// Buffers of a stream of `batches` 512-byte batches and of its schedule; fills in the operand's counts.
+int reserve_packed(PackedMatrix* pm, int P, int ntb, uint64_t batches, PackedOut* out, ScheduleShape* shape) {
+  if (batches * 512 >= ((uint64_t)1 << 32) - 4096) return SWCONV_ENOMEM;
+  *shape = schedule_shape(*pm, P, ntb);
+  const int spp = shape->spp;
+  pm->n_pairs = (size_t)batches * 64;
+  pm->n_slices = P * spp;
+  pm->n_wgs_used = shape->n_launch;
+  const size_t items = (size_t)P * ntb * ((spp + pm->item_cap - 1) / pm->item_cap + 1) + (size_t)shape->n_launch * 2;
+  int rc;
+  if ((rc = reserve((void**)&pm->d_stream, &pm->cap_stream, pm->n_pairs * 2 * sizeof(uint32_t)))) return rc;
+  if ((rc = reserve((void**)&pm->d_index, &pm->cap_index, pm->n_pairs * sizeof(int32_t)))) return rc;
+  if ((rc = reserve((void**)&pm->d_slices, &pm->cap_slices, (size_t)pm->n_slices * sizeof(Slice)))) return rc;
+  if ((rc = reserve((void**)&pm->d_items, &pm->cap_items, items * sizeof(WorkItem)))) return rc;
+  if ((rc = reserve((void**)&pm->d_ranges, &pm->cap_ranges, (size_t)shape->n_launch * sizeof(RangeHeader)))) return rc;
+  *out = PackedOut{pm->d_stream, pm->d_index, pm->d_slices, pm->d_items, pm->d_ranges, (uint32_t)pm->n_pairs};
+  return SWCONV_OK;
+}
+
+bool packs_on_device(const PackedMatrix& pm) { return pm.rows <= kPackMaxRows && pm.n_wgs <= kPackMaxWgs; }
+
+// The host's cut of the schedule for an operand whose rows launch 1 has sorted.
+int schedule_on_host(PackedMatrix* pm, int P, int ntb) {
+  try {
+    std::vector<int32_t> len((size_t)P * pm->rows_padded);
+    HIP_TRY(hipMemcpy(len.data(), pm->tables.len, len.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
+    pm->slices.assign((size_t)pm->n_slices, Slice{});
+    for (size_t i = 0; i < pm->slices.size(); ++i)
+      pm->slices[i].len = (len[i * kSliceRows] + kStepGroup - 1) / kStepGroup * kStepGroup;
+    build_schedule(pm, P, ntb);
+    int rc;
+    if ((rc = upload(&pm->d_items, pm->items, &pm->cap_items)) || (rc = upload(&pm->d_ranges, pm->ranges, &pm->cap_ranges)))
+      return rc;
+    HIP_TRY(hipDeviceSynchronize());
+  } catch (const std::bad_alloc&) {
+    return SWCONV_ENOMEM;
+  }
+  return SWCONV_OK;
+}
+
+// Packs W_F^T (per position: C rows of (k, weight) entries, k ascending) from the packed W_F, on `st`, and
+// allocates the dL/dI_F workspace.  Done by the first backward pass after the weights were set.
+int prepare_backward(swconv_plan* pl, hipStream_t st) {
   if (!pl->bt_supported) return SWCONV_EUNSUPPORTED;
   if (pl->bt_current && pl->bt.on_device && pl->dD) return SWCONV_OK;
   const int P = pl->P, K = pl->g.K, C = pl->g.C;
-  try {
-    const int64_t nnz = pl->fw.nnz;
-    std::vector<int32_t> rp((size_t)P * K + 1), ci((size_t)nnz), trp((size_t)P * C + 1, 0), tci((size_t)nnz);
-    std::vector<float> va((size_t)nnz), tva((size_t)nnz);
-    std::vector<int32_t> t_to_orig((size_t)nnz);  // entry of the transposed CSR -> entry of the caller's CSR
-    int rc0 = refresh_host_values(pl);
-    if (rc0) return rc0;
-    unpack_matrix(pl->fw, P, rp.data(), ci.data(), va.data());
-    for (int p = 0; p < P; ++p)
-      for (int32_t q = rp[(size_t)p * K]; q < rp[(size_t)(p + 1) * K]; ++q) ++trp[(size_t)p * C + ci[q] + 1];
-    for (size_t i = 0; i < (size_t)P * C; ++i) trp[i + 1] += trp[i];
-    std::vector<int32_t> fill(trp.begin(), trp.end() - 1);
-    for (int p = 0; p < P; ++p)
-      for (int k = 0; k < K; ++k)  // k ascending, so every transposed row gets its columns in ascending order
-        for (int32_t q = rp[(size_t)p * K + k]; q < rp[(size_t)p * K + k + 1]; ++q) {
-          const int32_t dst = fill[(size_t)p * C + ci[q]]++;
-          tci[dst] = k;
-          tva[dst] = va[q];
-          t_to_orig[dst] = q;
-        }
-    size_grid(&pl->bt, (int64_t)P * pl->n_tau_blocks * (pl->bt.rows_padded / kSliceRows));
-    pack_matrix(&pl->bt, P, pl->n_tau_blocks, trp.data(), tci.data(), tva.data());
-    pl->bt_value_index.assign(pl->bt.entry_index.size(), -1);
-    for (size_t e = 0; e < pl->bt.entry_index.size(); ++e)
-      if (pl->bt.entry_index[e] >= 0) pl->bt_value_index[e] = t_to_orig[(size_t)pl->bt.entry_index[e]];
-  } catch (const std::bad_alloc&) {
-    pl->bt.packed = false;
-    return SWCONV_ENOMEM;
-  }
-  int rc = upload_packed(&pl->bt);
-  if (rc) return rc;
-  if ((rc = upload(&pl->d_bt_value_index, pl->bt_value_index, &pl->cap_bt_value_index))) return rc;
+  PackedMatrix& bt = pl->bt;
+  int rc;
+  if ((rc = ensure_index(&pl->fw))) return rc;
+  bt.on_device = false;
+  size_grid(&bt, (int64_t)P * pl->n_tau_blocks * (bt.rows_padded / kSliceRows));
+  bt.n_wgs = std::min(bt.n_wgs, kPackMaxWgs);
+  // The transpose's batches without asking the device: its rows are sorted, so the slices' lengths sum to at
+  // most one longest row plus a quarter of the entries per position, and rounding adds less than a batch each.
+  const int spp = bt.rows_padded / kSliceRows;
+  const uint64_t batches = ((uint64_t)P * K + (uint64_t)pl->fw.nnz / kSliceRows) / kBatchSteps + (uint64_t)P * (spp + 1) + 2;
+  PackedOut out;
+  ScheduleShape shape;
+  if ((rc = reserve_tables(&bt, P)) || (rc = reserve_packed(&bt, P, pl->n_tau_blocks, batches, &out, &shape))) return rc;
+  const int words = (K + 31) / 32 | 1;  // odd: the rows of the bit matrix start on different LDS banks
+  if ((rc = reserve((void**)&pl->d_bits, &pl->cap_bits, (size_t)P * C * words * sizeof(uint2)))) return rc;
   if (!pl->dD) {
     HIP_TRY(hipMalloc((void**)&pl->dD, pl->g.v_bytes));
     HIP_TRY(hipMemset(pl->dD, 0, pl->g.v_bytes));
+    HIP_TRY(hipDeviceSynchronize());
   }
   if (pl->grad_images_per_group > 0 && !pl->d_gtiles && (rc = upload(&pl->d_gtiles, pl->gtiles))) return rc;
+  const LaunchTarget to{st, nullptr, nullptr};
+  const int fw_spp = pl->fw.rows_padded / kSliceRows;
+  const size_t lds = ((size_t)(C * words + 3) / 4 * 4 + 2 * (size_t)bt.rows_padded) * sizeof(uint32_t);
+  static bool attr_set = false;
+  if (!attr_set) {
+    // up to 638 x 21 words and two row tables, besides a few static words
+    HIP_TRY(hipFuncSetAttribute((const void*)transpose_sort_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024));
+    attr_set = true;
+  }
+  if ((rc = launch_kernel(transpose_sort_kernel, dim3(P), dim3(kPackThreads), lds, to, pl->fw.d_stream, pl->fw.d_index,
+                          pl->fw.d_slices, fw_spp, K, C, bt.rows_padded, words, bt.tables, shape.slice_ovh,
+                          (uint2*)pl->d_bits, rank_table(bt, P))))
+    return rc;
+  if (pl->host_pattern) {
+    // a pattern set from the host stays for many passes: its transpose gets the more even cut of the host as well
+    HIP_TRY(hipStreamSynchronize(st));
+    if ((rc = schedule_on_host(&bt, P, pl->n_tau_blocks))) return rc;
+    shape.n_launch = 0;  // nothing left to cut for launch 2
+  }
+  const int chunks = (std::max(spp, fw_spp) + 15) / 16;
+  if ((rc = launch_kernel(transpose_fill_kernel, dim3(1 + kPackSpareWgs + P * chunks), dim3(kPackThreads), 0, to,
+                          pl->fw.d_stream, pl->fw.d_index, pl->fw.d_slices, fw_spp, C, bt.rows_padded, words, chunks,
+                          (const uint2*)pl->d_bits, rank_table(bt, P), bt.tables, out, shape)))
+    return rc;
+  bt.nnz = pl->fw.nnz;
+  bt.host_current = false;
+  bt.index_current = bt.packed = bt.on_device = true;
   pl->bt_current = true;
   return SWCONV_OK;
 }
 
 // Device copies the weight gradient needs: the stream-entry -> CSR index map and the partial-sum buffer.
 int prepare_weight_grad(swconv_plan* pl) {
-  const size_t need = (size_t)pl->n_tau_blocks * (pl->fw.stream.size() / 2);
+  const size_t need = (size_t)pl->n_tau_blocks * pl->fw.n_pairs;
   if (need * sizeof(float) >= ((size_t)1 << 40)) return SWCONV_EUNSUPPORTED;
   if (pl->partial_floats < need) {
     if (pl->d_partial) (void)hipFree(pl->d_partial);
@@ -935,14 +1106,7 @@ int prepare_weight_grad(swconv_plan* pl) {
     HIP_TRY(hipMalloc((void**)&pl->d_partial, std::max<size_t>(need, 1) * sizeof(float)));
     pl->partial_floats = need;
   }
-  if (!pl->index_current) {
-    HIP_TRY(hipDeviceSynchronize());  // an earlier backward pass may still read the index
-    int rc = upload(&pl->d_entry_index, pl->fw.entry_index, &pl->cap_entry_index);
-    if (rc) return rc;
-    HIP_TRY(hipDeviceSynchronize());
-    pl->index_current = true;
-  }
-  return SWCONV_OK;
+  return ensure_index(&pl->fw);
 }
 
 template <int M, int R>
@@ -998,12 +1162,12 @@ bool backward_stage_runs(const swconv_plan* pl, int stage, const float* in, cons
   return true;
 }
 
-int backward_ready(swconv_plan* pl, const float* in_dev, const float* dout_dev, const float* dvals_dev) {
+int backward_ready(swconv_plan* pl, hipStream_t st, const float* in_dev, const float* dout_dev, const float* dvals_dev) {
   if (!pl || !dout_dev) return SWCONV_EINVAL;
   if (!pl->fw.on_device) return SWCONV_ESTATE;
   if (!in_dev && dvals_dev && !pl->ran_forward) return SWCONV_ESTATE;  // no I_F to reuse
   if ((int64_t)pl->g.N * pl->g.C * (pl->g.H + pl->m) * (pl->g.W + pl->m) >= ((int64_t)1 << 31)) return SWCONV_EUNSUPPORTED;  // 32-bit cell index of the gather
-  int rc = prepare_backward(pl);
+  int rc = prepare_backward(pl, st);
   if (rc) return rc;
   return dvals_dev ? prepare_weight_grad(pl) : SWCONV_OK;
 }
@@ -1020,16 +1184,54 @@ int launch_backward_stage(swconv_plan* pl, const LaunchTarget& to, int stage, co
     case 2:
       return launch_spmm_mode<true>(pl, pl->fw, to, pl->dV, pl->g.v_bytes, pl->dM, pl->g.m_bytes, pl->d_partial);
     case 3: {
-      const uint32_t n_entries = (uint32_t)(pl->fw.stream.size() / 2);
+      const uint32_t n_entries = (uint32_t)pl->fw.n_pairs;
       return launch_kernel(weight_grad_reduce_kernel, dim3((n_entries + 255) / 256), dim3(256), 0, to,
                            (const float*)pl->d_partial, pl->n_tau_blocks, n_entries,
-                           (const int32_t*)pl->d_entry_index, n_entries, dvals_dev);
+                           (const int32_t*)pl->fw.d_index, n_entries, dvals_dev);
     }
     case 4: return launch_spmm(pl, pl->bt, to, pl->dM, pl->g.m_bytes, pl->dD, pl->g.v_bytes);
     default:
       return dispatch_mr(pl, [&](auto M, auto R) {
         return launch_backward_transforms<M(), R()>(pl, to, stage - 4, nullptr, din_dev);
       });
+  }
+}
+
+// The weights change: what the workspaces hold belongs to the old ones (the products are stale, and a backward
+// pass must not pair I_F of an earlier pass with the new pattern without a forward pass in between), and so do
+// the other packed copies.
+void weights_replaced(swconv_plan* pl) {
+  pl->bt_current = false;
+  pl->host_values_stale = false;
+  pl->fz.ready = false;
+  pl->m_current = false;
+  pl->ran_forward = false;
+}
+
+// swconv_set_weights_device for sizes beyond the packing kernels: through host copies of the arrays.
+int set_weights_through_host(swconv_plan* pl, void* hip_stream, const int32_t* rowptr_dev, const int32_t* colidx_dev,
+                             const float* vals_dev) {
+  const size_t rows = (size_t)pl->P * pl->g.K;
+  try {
+    std::vector<int32_t> rp(rows + 1);
+    if (hipStreamSynchronize((hipStream_t)hip_stream) != hipSuccess ||
+        hipMemcpy(rp.data(), rowptr_dev, rp.size() * sizeof(int32_t), hipMemcpyDeviceToHost) != hipSuccess) {
+      (void)hipGetLastError();
+      return SWCONV_EHIP;
+    }
+    const int64_t nnz = rp[rows];
+    if (rp[0] != 0 || nnz < 0 || nnz > (int64_t)rows * pl->g.C) return SWCONV_EINVAL;
+    if (nnz > 0 && (!colidx_dev || !vals_dev)) return SWCONV_EINVAL;
+    std::vector<int32_t> ci((size_t)nnz);
+    std::vector<float> va((size_t)nnz);
+    if (nnz > 0 && (hipMemcpy(ci.data(), colidx_dev, ci.size() * sizeof(int32_t), hipMemcpyDeviceToHost) != hipSuccess ||
+                    hipMemcpy(va.data(), vals_dev, va.size() * sizeof(float), hipMemcpyDeviceToHost) != hipSuccess)) {
+      (void)hipGetLastError();
+      return SWCONV_EHIP;
+    }
+    return swconv_set_weights(pl, rp.data(), ci.data(), va.data());
+  } catch (const std::bad_alloc&) {
+    return SWCONV_ENOMEM;
   }
 }
 
@@ -1171,14 +1373,15 @@ int swconv_plan_set_image_strides(swconv_plan* pl, int64_t in_stride, int64_t ou
 
 void swconv_plan_destroy(swconv_plan* pl) {
   if (!pl) return;
-  void* bufs[] = {pl->dV, pl->dM, pl->dD, pl->d_partial, pl->d_entry_index, pl->d_wdense, pl->d_tiles, pl->d_blocks};
+  void* bufs[] = {pl->dV, pl->dM, pl->dD, pl->d_partial, pl->d_bits, pl->d_wdense, pl->d_tiles, pl->d_blocks};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
   free_packed(&pl->fw);
   free_packed(&pl->bt);
-  void* fused[] = {pl->fz.d_wpk, pl->fz.d_lens, pl->fz.d_otiles, pl->d_gtiles, pl->fz.d_value_index, pl->d_bt_value_index};
+  void* fused[] = {pl->fz.d_wpk, pl->fz.d_lens, pl->fz.d_otiles, pl->d_gtiles, pl->fz.d_value_index};
   for (void* b : fused)
     if (b) (void)hipFree(b);
+  if (pl->h_report) (void)hipHostFree(pl->h_report);
   delete pl;
 }
 
@@ -1187,21 +1390,11 @@ int swconv_set_weights(swconv_plan* pl, const int32_t* rowptr, const int32_t* co
   int rc = validate_csr(pl, rowptr, colidx, vals);
   if (rc) return rc;
   size_grid(&pl->fw, (int64_t)pl->P * pl->n_tau_blocks * (pl->fw.rows_padded / kSliceRows));
-  pl->bt_current = false;
-  pl->index_current = false;
-  pl->host_values_stale = false;
-  pl->fz.ready = false;
-  // what the workspaces hold belongs to the old weights: the products are stale, and a backward pass
-  // must not pair I_F of an earlier pass with the new pattern without a forward pass in between
-  pl->m_current = false;
-  pl->ran_forward = false;
+  weights_replaced(pl);
+  pl->host_pattern = true;
   try {
     pack_matrix(&pl->fw, pl->P, pl->n_tau_blocks, rowptr, colidx, vals);
     pack_fused(pl, rowptr, colidx, vals);
-    // The F(4x4,3x3) kernel runs only where asked for (SWCONV_FUSE_OUTPUT=2): with 64 + 16 accumulators per
-    // lane it holds 16 waves per CU, its vector ALU stays at about two thirds busy between the barriers of
-    // the 36 positions, and on the 56 x 56 layer it measured 217 us against 188 us for the two kernels.
-    pl->fz.wanted = pl->fz.out_tile == 2 || pl->fz.mode == 2;
   } catch (const std::bad_alloc&) {
     pl->fw.packed = false;
     pl->fw.on_device = false;
@@ -1293,7 +1486,7 @@ int swconv_profile_forward(swconv_plan* pl, void* hip_stream, const float* in_de
 
 int swconv_backward(swconv_plan* pl, void* hip_stream, const float* in_dev, const float* dout_dev, float* din_dev,
                     float* dvals_dev) {
-  int rc = backward_ready(pl, in_dev, dout_dev, dvals_dev);
+  int rc = backward_ready(pl, (hipStream_t)hip_stream, in_dev, dout_dev, dvals_dev);
   if (rc) return rc;
   for (int stage = 0; stage < kBackwardStages; ++stage)
     if ((rc = launch_backward_stage(pl, LaunchTarget{(hipStream_t)hip_stream, nullptr, nullptr}, stage, in_dev,
@@ -1307,7 +1500,7 @@ int swconv_backward(swconv_plan* pl, void* hip_stream, const float* in_dev, cons
 int swconv_profile_backward(swconv_plan* pl, void* hip_stream, const float* in_dev, const float* dout_dev,
                             float* din_dev, float* dvals_dev, int iters, float* stage_ms) {
   if (!stage_ms || iters < 1) return SWCONV_EINVAL;
-  int rc = backward_ready(pl, in_dev, dout_dev, dvals_dev);
+  int rc = backward_ready(pl, (hipStream_t)hip_stream, in_dev, dout_dev, dvals_dev);
   if (rc) return rc;
   hipStream_t st = (hipStream_t)hip_stream;
   // one (start, stop) pair per kernel launch; the events take the kernel's own time stamps
@@ -1374,28 +1567,63 @@ int swconv_prune_step(int64_t rows, const int32_t* rowptr_dev, const int32_t* co
 int swconv_set_weights_device(swconv_plan* pl, void* hip_stream, const int32_t* rowptr_dev, const int32_t* colidx_dev,
                               const float* vals_dev) {
   if (!pl || !rowptr_dev) return SWCONV_EINVAL;
-  const size_t rows = (size_t)pl->P * pl->g.K;
-  try {
-    std::vector<int32_t> rp(rows + 1);
-    if (hipStreamSynchronize((hipStream_t)hip_stream) != hipSuccess ||
-        hipMemcpy(rp.data(), rowptr_dev, rp.size() * sizeof(int32_t), hipMemcpyDeviceToHost) != hipSuccess) {
-      (void)hipGetLastError();
-      return SWCONV_EHIP;
-    }
-    const int64_t nnz = rp[rows];
-    if (rp[0] != 0 || nnz < 0 || nnz > (int64_t)rows * pl->g.C) return SWCONV_EINVAL;
-    if (nnz > 0 && (!colidx_dev || !vals_dev)) return SWCONV_EINVAL;
-    std::vector<int32_t> ci((size_t)nnz);
-    std::vector<float> va((size_t)nnz);
-    if (nnz > 0 && (hipMemcpy(ci.data(), colidx_dev, ci.size() * sizeof(int32_t), hipMemcpyDeviceToHost) != hipSuccess ||
-                    hipMemcpy(va.data(), vals_dev, va.size() * sizeof(float), hipMemcpyDeviceToHost) != hipSuccess)) {
-      (void)hipGetLastError();
-      return SWCONV_EHIP;
-    }
-    return swconv_set_weights(pl, rp.data(), ci.data(), va.data());
-  } catch (const std::bad_alloc&) {
-    return SWCONV_ENOMEM;
+  PackedMatrix& fw = pl->fw;
+  const int P = pl->P, K = pl->g.K, C = pl->g.C;
+  size_grid(&fw, (int64_t)P * pl->n_tau_blocks * (fw.rows_padded / kSliceRows));
+  if (!packs_on_device(fw)) return set_weights_through_host(pl, hip_stream, rowptr_dev, colidx_dev, vals_dev);
+  const hipStream_t st = (hipStream_t)hip_stream;
+  const LaunchTarget to{st, nullptr, nullptr};
+  int rc;
+  if ((rc = ensure_workspace(pl)) || (rc = reserve_tables(&fw, P))) return rc;
+  const int checks = (K + kPackCheckRows - 1) / kPackCheckRows;
+  if (!pl->h_report) {
+    const size_t bytes = sizeof(PackReport) + (size_t)P * checks * sizeof(int32_t);
+    HIP_TRY(hipHostMalloc((void**)&pl->h_report, bytes, hipHostMallocDefault));
+    pl->h_bad_cols = reinterpret_cast<int32_t*>(pl->h_report + 1);
   }
+  ScheduleShape shape = schedule_shape(fw, P, pl->n_tau_blocks);
+  if ((rc = launch_kernel(pack_sort_kernel, dim3(P, 1 + checks), dim3(kPackThreads),
+                          2 * (size_t)fw.rows_padded * sizeof(uint32_t), to, rowptr_dev, colidx_dev, P, K,
+                          fw.rows_padded, C, fw.tables, shape.slice_ovh, pl->h_report, pl->h_bad_cols)))
+    return rc;
+  HIP_TRY(hipStreamSynchronize(st));
+  const PackReport& rep = *pl->h_report;
+  bool bad = rep.bad || rep.nnz < 0 || (int64_t)rep.nnz > (int64_t)P * K * C;
+  for (int p = 0; p < P; ++p) bad |= rep.bad_rows[p] != 0;
+  for (int i = 0; i < P * checks; ++i) bad |= pl->h_bad_cols[i] != 0;
+  if (bad || (rep.nnz > 0 && (!colidx_dev || !vals_dev))) return SWCONV_EINVAL;
+
+  HIP_TRY(hipDeviceSynchronize());  // a pass still in flight may read the buffers that are overwritten below
+  weights_replaced(pl);
+  pl->host_pattern = false;
+  fw.on_device = fw.packed = fw.index_current = fw.host_current = false;
+  uint64_t batches = 2;  // the product fetches up to two batches past a slice's end
+  int longest = 0;
+  for (int p = 0; p < P; ++p) {
+    batches += (uint64_t)rep.stats[p].batches;
+    longest = std::max(longest, rep.stats[p].longest);
+  }
+  PackedOut out;
+  if ((rc = reserve_packed(&fw, P, pl->n_tau_blocks, batches, &out, &shape))) return rc;
+  fw.nnz = rep.nnz;
+  if ((rc = launch_kernel(pack_fill_kernel, dim3(1 + kPackSpareWgs + P * ((shape.spp + 15) / 16)), dim3(kPackThreads), 0,
+                          to, rowptr_dev, colidx_dev, vals_dev, K, fw.rows_padded, fw.tables, out, shape)))
+    return rc;
+  FusedProduct& fz = pl->fz;
+  const bool fused = size_fused(pl, longest);
+  if (fused) {
+    if ((rc = reserve((void**)&fz.d_wpk, &fz.cap_wpk, fz.n_dwords * sizeof(uint32_t)))) return rc;
+    if ((rc = reserve((void**)&fz.d_value_index, &fz.cap_value_index, fz.n_dwords / 2 * sizeof(int32_t)))) return rc;
+    if ((rc = reserve((void**)&fz.d_lens, &fz.cap_lens, (size_t)P * fz.KC * kFusedWaves))) return rc;
+    if (!fz.d_otiles && !fz.otiles.empty() && (rc = upload(&fz.d_otiles, fz.otiles))) return rc;
+    if ((rc = launch_kernel(pack_fused_kernel, dim3(P * fz.KC), dim3(kPackThreads), 0, to, rowptr_dev, colidx_dev,
+                            vals_dev, K, fz.KC, fz.B, fz.d_wpk, fz.d_value_index, fz.d_lens)))
+      return rc;
+  }
+  HIP_TRY(hipStreamSynchronize(st));  // the caller's arrays are his again, and a pass on any stream finds the weights
+  fw.packed = fw.on_device = fw.index_current = true;
+  fz.ready = fused;
+  return SWCONV_OK;
 }
 
 int swconv_update_values(swconv_plan* pl, void* hip_stream, const float* vals_dev) {
@@ -1404,20 +1632,16 @@ int swconv_update_values(swconv_plan* pl, void* hip_stream, const float* vals_de
   if (pl->fw.nnz == 0) return SWCONV_OK;
   if (!vals_dev) return SWCONV_EINVAL;
   int rc;
-  if (!pl->index_current) {  // the pair -> CSR index map of W_F (also used by the weight gradient)
-    HIP_TRY(hipDeviceSynchronize());
-    if ((rc = upload(&pl->d_entry_index, pl->fw.entry_index, &pl->cap_entry_index))) return rc;
-    pl->index_current = true;
-  }
+  if ((rc = ensure_index(&pl->fw))) return rc;  // the pair -> CSR index map of W_F
   const LaunchTarget to{(hipStream_t)hip_stream, nullptr, nullptr};
   auto refresh = [&](uint32_t* pairs, const int32_t* index, size_t n_pairs) {
     return launch_kernel(refresh_values_kernel, dim3((unsigned)((n_pairs + 255) / 256)), dim3(256), 0, to, pairs, index,
                          (uint32_t)n_pairs, vals_dev);
   };
-  if ((rc = refresh(pl->fw.d_stream, pl->d_entry_index, pl->fw.stream.size() / 2))) return rc;
-  if (pl->fz.ready && (rc = refresh(pl->fz.d_wpk, pl->fz.d_value_index, pl->fz.wpk.size() / 2))) return rc;
+  if ((rc = refresh(pl->fw.d_stream, pl->fw.d_index, pl->fw.n_pairs))) return rc;
+  if (pl->fz.ready && (rc = refresh(pl->fz.d_wpk, pl->fz.d_value_index, pl->fz.n_dwords / 2))) return rc;
   if (pl->bt_current && pl->bt.on_device &&
-      (rc = refresh(pl->bt.d_stream, pl->d_bt_value_index, pl->bt.stream.size() / 2)))
+      (rc = refresh(pl->bt.d_stream, pl->bt.d_index, pl->bt.n_pairs)))
     return rc;
   pl->host_values_stale = true;
   return SWCONV_OK;
@@ -1454,6 +1678,8 @@ int swconv_debug_export_weights(swconv_plan* pl, int32_t* rowptr, int32_t* colid
 int swconv_debug_check_schedule(const swconv_plan* pl) {
   if (!pl) return SWCONV_EINVAL;
   if (!pl->fw.packed) return SWCONV_ESTATE;
+  const int rc = fetch_packed_host(const_cast<PackedMatrix*>(&pl->fw), pl->P);  // a cache of what the device holds
+  if (rc) return rc;
   return schedule_is_partition(pl->fw, pl->P, pl->n_tau_blocks) ? SWCONV_OK : SWCONV_EINVAL;
 }
 
@@ -1470,6 +1696,8 @@ int swconv_plan_weight_stats(const swconv_plan* pl, int64_t* nnz, int64_t* padde
                              int64_t* max_item) {
   if (!pl) return SWCONV_EINVAL;
   if (!pl->fw.packed) return SWCONV_ESTATE;
+  const int rc = fetch_packed_host(const_cast<PackedMatrix*>(&pl->fw), pl->P);  // a cache of what the device holds
+  if (rc) return rc;
   if (nnz) *nnz = pl->fw.nnz;
   if (padded_nnz) *padded_nnz = pl->fw.padded_nnz;
   if (work_items) *work_items = (int)pl->fw.items.size();

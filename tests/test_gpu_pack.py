@@ -1,0 +1,109 @@
+"""The packing on the device (swconv_set_weights_device, and the transpose of W_F for the backward pass) against the
+host's packing of the same arrays: exported weights, passes in both directions and the statistics have to be equal bit
+for bit, the schedule a partition.  Sizes at the edges of its workgroups: one row, rows that fill no slice, more than
+1024 and the most rows a workgroup sorts (4096), the first size beyond (which goes through the host), several column
+checks per position, one and 638 columns (rows of up to 638 entries, 20 words of the transpose's bit matrix), empty,
+full and skewed patterns."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from paper_1702_08597_amd import binding as sw
+from paper_1702_08597_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def set_device(plan, rp, ci, va):
+    dev = [torch.from_numpy(a).cuda() if len(a) else None for a in (rp, ci, va)]
+    st = torch.cuda.current_stream().cuda_stream
+    return sw.lib().swconv_set_weights_device(plan, ctypes.c_void_p(st),
+                                              *(ctypes.c_void_p(a.data_ptr()) if a is not None else None for a in dev))
+
+
+def passes(plan, x, g, K, nnz, backward):
+    N, C, H, W = x.shape
+    P, T, Ho, Wo = sw.swconv_plan_sizes(plan)
+    out = torch.full((N, K, Ho, Wo), float("nan"), device="cuda")
+    din = torch.full(x.shape, float("nan"), device="cuda")
+    dv = torch.full((max(1, nnz),), float("nan"), device="cuda")
+    sw.swconv_forward(plan, 0, x.data_ptr(), out.data_ptr())
+    if backward:
+        sw.swconv_backward(plan, 0, 0, g.data_ptr(), din.data_ptr(), dv.data_ptr())
+    torch.cuda.synchronize()
+    res = [out.cpu().numpy()] + ([din.cpu().numpy(), dv.cpu().numpy()[:nnz]] if backward else [])
+    assert not any(np.isnan(r).any() for r in res)
+    return res
+
+
+@pytest.mark.parametrize("N,C,K,m,r,H,W,density,skew", [
+    (1, 1, 1, 2, 3, 3, 3, 1.0, False),
+    (2, 5, 7, 4, 3, 9, 6, 0.5, False),
+    (3, 33, 127, 4, 3, 13, 13, 0.1, False),
+    (2, 64, 129, 2, 5, 11, 7, 0.1, False),    # the fused format as well, two column checks per position
+    (1, 24, 70, 4, 5, 9, 9, 0.0, False),
+    (2, 48, 128, 2, 5, 27, 27, 0.094, False),
+    (4, 96, 384, 4, 3, 13, 13, 0.1, True),
+    (1, 638, 9, 2, 3, 6, 6, 1.0, False),
+    (1, 20, 638, 2, 3, 6, 6, 0.3, False),
+    (1, 3, 1030, 2, 3, 6, 6, 0.7, False),     # more rows than threads; K beyond the backward pass
+    (1, 2, 4096, 2, 3, 6, 6, 0.6, False),
+    (1, 2, 4097, 2, 3, 6, 6, 0.6, False),     # through the host
+])
+def test_device_packing_equals_host_packing(N, C, K, m, r, H, W, density, skew):
+    P = (m + r - 1) ** 2
+    rp, ci, va = synth.skewed_weights(P, K, C, 5 + K) if skew else synth.bernoulli_weights(P, K, C, density, 5 + K)
+    x = torch.from_numpy(synth.activations(N, C, H, W, 6)).cuda()
+    plans = [sw.swconv_plan_create(N, C, H, W, K, m, r, r // 2) for _ in range(2)]
+    try:
+        sw.swconv_set_weights(plans[0], rp, ci, va)
+        # another pattern first, so that the call really replaces weights (and shrinks or grows every buffer)
+        rp0, ci0, va0 = synth.bernoulli_weights(P, K, C, 0.25, 7)
+        assert set_device(plans[1], rp0, ci0, va0) == sw.SWCONV_OK
+        assert set_device(plans[1], rp, ci, va) == sw.SWCONV_OK
+        rp2, ci2, va2 = sw.swconv_debug_export_weights(plans[1], K, len(va))
+        np.testing.assert_array_equal(rp2, rp)
+        np.testing.assert_array_equal(ci2, ci)
+        np.testing.assert_array_equal(va2.view(np.uint32), va.view(np.uint32))
+        sw.swconv_debug_check_schedule(plans[1])
+        a, b = (sw.swconv_plan_weight_stats(p) for p in plans)
+        assert (a["nnz"], a["padded_nnz"]) == (b["nnz"], b["padded_nnz"])
+        Ho, Wo = sw.swconv_plan_sizes(plans[0])[2:]
+        g = torch.randn((N, K, Ho, Wo), generator=torch.Generator(device="cuda").manual_seed(8), device="cuda")
+        for p, q in zip(*(passes(pl, x, g, K, len(va), K <= 638) for pl in plans)):
+            np.testing.assert_array_equal(p.view(np.uint32), q.view(np.uint32))
+    finally:
+        for pl in plans:
+            sw.swconv_plan_destroy(pl)
+
+
+def test_malformed_device_arrays_are_refused_and_the_weights_stay():
+    K, C = 130, 40
+    rp, ci, va = synth.bernoulli_weights(36, K, C, 0.3, 3)
+    plan = sw.swconv_plan_create(2, C, 13, 13, K, 4, 3, 1)
+    try:
+        assert set_device(plan, rp, ci, va) == sw.SWCONV_OK
+        last = int(rp[-2])  # first entry of the last row, which the second column check of its position reads
+        full = next(i for i in range(36 * K) if rp[i + 1] - rp[i] >= 2)
+
+        def bad(a, where, value):
+            b = a.copy()
+            b[where] = value
+            return b
+
+        for args in ((bad(rp, 0, 1), ci, va), (bad(rp, 5, rp[4] - 1), ci, va), (bad(rp, 7, rp[-1] + 1), ci, va),
+                     (bad(rp, 9, -3), ci, va), (bad(rp, -1, -1), ci, va), (rp, bad(ci, last, C), va),
+                     (rp, bad(ci, rp[full], -1), va), (rp, bad(ci, rp[full] + 1, ci[rp[full]]), va),
+                     (bad(rp, slice(1, 3), rp[3] + C), ci, va)):
+            assert set_device(plan, *args) == sw.SWCONV_EINVAL
+        assert sw.lib().swconv_set_weights_device(plan, None, None, None, None) == sw.SWCONV_EINVAL
+        d = torch.from_numpy(rp).cuda()
+        assert sw.lib().swconv_set_weights_device(plan, None, ctypes.c_void_p(d.data_ptr()), None, None) == sw.SWCONV_EINVAL
+        rp2, ci2, va2 = sw.swconv_debug_export_weights(plan, K, len(va))
+        np.testing.assert_array_equal(rp2, rp)
+        np.testing.assert_array_equal(ci2, ci)
+        np.testing.assert_array_equal(va2, va)
+    finally:
+        sw.swconv_plan_destroy(plan)
