@@ -1554,7 +1554,7 @@ int swconv_prune_step(int64_t rows, const int32_t* rowptr_dev, const int32_t* co
     return SWCONV_EINVAL;
   if (!(eta >= 0.0f) || !(lambda >= 0.0f) || !(eps >= 0.0f) || !(beta >= 0.0f)) return SWCONV_EINVAL;
   const LaunchTarget to{(hipStream_t)hip_stream, nullptr, nullptr};
-  const dim3 grid((unsigned)((rows + 255) / 256));
+  const dim3 grid((unsigned)((rows + kPruneRows - 1) / kPruneRows));
   int rc;
   if ((rc = launch_kernel(prune_update_kernel, grid, dim3(256), 0, to, rows, rowptr_dev, vals_dev, grad_dev, eta, lambda,
                           eps, beta, updated_dev, rowptr_out_dev)))
