@@ -234,7 +234,9 @@ int swconv_update_values(swconv_plan* plan, void* hip_stream, const float* vals_
  * pair of HIP events (as swconv_profile_forward); mean milliseconds per kernel, in launch order:
  *   stage_ms  HOST, 7 floats: dL/dZ transform, input transform (I_F again), sampled products,
  *             reduction to CSR order, transposed sparse product, patch transform, gather;
- *             0 for kernels the call does not run (din_dev or dvals_dev NULL).  Where the image
+ *             0 for kernels the call does not run (din_dev or dvals_dev NULL).  Sampled products
+ *             and transposed sparse product are one kernel where both run: the third and the fifth
+ *             value are its parts, by their shares of its inner loop.  Where the image
  *             planes fit LDS (3x3 filters) the last two run as one kernel that keeps no patch
  *             buffer: the sixth value is its time and the seventh is 0 (the environment
  *             variable SWCONV_FUSE_INPUT_GRAD=0, read by swconv_plan_create, keeps two kernels).

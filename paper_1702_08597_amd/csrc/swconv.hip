@@ -194,7 +194,7 @@ struct swconv_plan {
   int grad_images_per_group = 0;  // 0: the patch + gather kernels run instead
   std::vector<GradTile> gtiles;   // Tp
   GradTile* d_gtiles = nullptr;
-  float* d_partial = nullptr; // backward pass: [tile blocks][stream entries of W_F] partial dot products
+  float* d_partial = nullptr; // backward pass: [tile blocks][stream entries of W_F^T] partial dot products
   size_t partial_floats = 0;
   // swconv_update_values: the device streams hold newer values than the host copies
   bool host_values_stale = false;
@@ -319,37 +319,51 @@ int launch_output_transform(const swconv_plan* pl, const LaunchTarget& to, const
   return launch_kernel(kern, grid, dim3(256), lds, to, Mbuf, out, pl->d_tiles, pl->d_blocks, pl->g);
 }
 
-// Y[p] = A[p] * X[p] for the packed operand `pm`: X has pm.cols rows of Tp tiles per position and
-// x_bytes in all, Y gets pm.rows rows per position.  With `partial` set (sampled mode): Y is read
-// and partial[tile block][stream entry] receives the entry's dot product over the block.
-template <int NW, bool SAMPLED>
-int launch_spmm_t(const swconv_plan* pl, const PackedMatrix& pm, const LaunchTarget& to, const float* X,
-                  uint32_t x_bytes, float* Y, uint32_t y_bytes, float* partial) {
+// The operands of a pass over the packed operand `pm`: panels of X (pm.cols rows of Tp tiles per position,
+// x_bytes in all); Y and Z have pm.rows rows per position.
+struct SpmmArgs {
+  const float* X;
+  uint32_t x_bytes;
+  float* Y;            // products
+  uint32_t y_bytes;
+  const float* Z;      // rows of the dot products
+  float* partial;      // their sums, per tile block and stream entry
+};
+
+template <int NW, int PIECES, bool DOTS>
+int launch_spmm_t(const swconv_plan* pl, const PackedMatrix& pm, const LaunchTarget& to, const SpmmArgs& a) {
   if (pm.n_wgs_used == 0) return SWCONV_OK;
   const size_t lds = (size_t)pm.cols * kTileBlock * sizeof(float) + kSpmmLdsExtra + (size_t)pm.item_cap * sizeof(Slice);
-  auto kern = spmm_kernel<NW, SAMPLED>;
+  auto kern = spmm_kernel<NW, PIECES, DOTS>;
   static bool attr_set = false;
   if (!attr_set) {
     HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes));
     attr_set = true;
   }
-  return launch_kernel(kern, dim3(pm.n_wgs_used), dim3(NW * 64), lds, to, X, Y, pm.d_stream,
+  return launch_kernel(kern, dim3(pm.n_wgs_used), dim3(NW * 64), lds, to, a.X, a.Y, pm.d_stream,
                        (uint32_t)(pm.n_pairs * 2 * sizeof(uint32_t)), pm.d_slices, pm.n_slices,
-                       pm.d_items, pm.d_ranges, pm.n_wgs_used, pm.cols, pm.rows, pl->g.Tp, y_bytes, x_bytes, partial,
-                       (uint32_t)pm.n_pairs);
+                       pm.d_items, pm.d_ranges, pm.n_wgs_used, pm.cols, pm.rows, pl->g.Tp, a.y_bytes, a.x_bytes, a.Z,
+                       a.partial, (uint32_t)pm.n_pairs);
 }
 
-template <bool SAMPLED>
-int launch_spmm_mode(const swconv_plan* pl, const PackedMatrix& pm, const LaunchTarget& to, const float* X,
-                     uint32_t x_bytes, float* Y, uint32_t y_bytes, float* partial) {
-  if (pm.waves == 12) return launch_spmm_t<12, SAMPLED>(pl, pm, to, X, x_bytes, Y, y_bytes, partial);
-  return pm.waves == 16 ? launch_spmm_t<16, SAMPLED>(pl, pm, to, X, x_bytes, Y, y_bytes, partial)
-                        : launch_spmm_t<8, SAMPLED>(pl, pm, to, X, x_bytes, Y, y_bytes, partial);
+// The registers that hold a panel on its way are sized in steps: a piece that no panel needs costs its register
+// and an instruction per item (48 channels, 12 waves: one piece of seven).
+template <bool DOTS>
+int launch_spmm(const swconv_plan* pl, const PackedMatrix& pm, const LaunchTarget& to, const SpmmArgs& a) {
+  const int threads = pm.waves * 64, pieces = (pm.cols * (kTileBlock / 4) + threads - 1) / threads;
+  if (pm.waves == 12)
+    return pieces <= 2   ? launch_spmm_t<12, 2, DOTS>(pl, pm, to, a)
+           : pieces <= 6 ? launch_spmm_t<12, 6, DOTS>(pl, pm, to, a)
+                         : launch_spmm_t<12, kPanelPieces12, DOTS>(pl, pm, to, a);
+  if (pm.waves == 16)
+    return pieces <= 6 ? launch_spmm_t<16, 6, DOTS>(pl, pm, to, a) : launch_spmm_t<16, kPanelPieces, DOTS>(pl, pm, to, a);
+  return launch_spmm_t<8, kPanelPieces, DOTS>(pl, pm, to, a);
 }
 
-int launch_spmm(const swconv_plan* pl, const PackedMatrix& pm, const LaunchTarget& to, const float* X,
-                uint32_t x_bytes, float* Y, uint32_t y_bytes) {
-  return launch_spmm_mode<false>(pl, pm, to, X, x_bytes, Y, y_bytes, nullptr);
+// Y[p] = A[p] * X[p]
+int launch_product(const swconv_plan* pl, const PackedMatrix& pm, const LaunchTarget& to, const float* X,
+                   uint32_t x_bytes, float* Y, uint32_t y_bytes) {
+  return launch_spmm<false>(pl, pm, to, SpmmArgs{X, x_bytes, Y, y_bytes, nullptr, nullptr});
 }
 
 template <int R, int PP>
@@ -412,7 +426,7 @@ int launch_stage(const swconv_plan* pl, const LaunchTarget& to, int stage, const
   switch (stage) {
     case 0:
       return dispatch_mr(pl, [&](auto M, auto R) { return launch_input_transform<M(), R()>(pl, to, in, ws.V); });
-    case 1: return launch_spmm(pl, pl->fw, to, ws.V, pl->g.v_bytes, ws.M, pl->g.m_bytes);
+    case 1: return launch_product(pl, pl->fw, to, ws.V, pl->g.v_bytes, ws.M, pl->g.m_bytes);
     default:
       return dispatch_mr(pl, [&](auto M, auto R) { return launch_output_transform<M(), R()>(pl, to, ws.M, out); });
   }
@@ -731,8 +745,9 @@ bool configure_packed(PackedMatrix* pm, int rows, int cols) {
   const int dflt_waves = wg_lds * 2 > kMaxLdsBytes ? 16 : 12;
   pm->waves = env_int("SWCONV_SPMM_WAVES", dflt_waves);
   if (pm->waves != 8 && pm->waves != 12 && pm->waves != 16) pm->waves = dflt_waves;
-  // a thread stages at most kPanelPieces 16-byte pieces of a panel
-  if (panel_bytes > (int64_t)kPanelPieces * pm->waves * 64 * 16) pm->waves = 16;
+  // a thread stages at most kPanelPieces (kPanelPieces12) 16-byte pieces of a panel
+  const int pieces = pm->waves == 12 ? kPanelPieces12 : kPanelPieces;
+  if (panel_bytes > (int64_t)pieces * pm->waves * 64 * 16) pm->waves = 16;
   return true;
 }
 
@@ -1095,9 +1110,9 @@ int prepare_backward(swconv_plan* pl, hipStream_t st) {
   return SWCONV_OK;
 }
 
-// Device copies the weight gradient needs: the stream-entry -> CSR index map and the partial-sum buffer.
+// The partial-sum buffer of the weight gradient (its stream-entry -> CSR index map came with the packing).
 int prepare_weight_grad(swconv_plan* pl) {
-  const size_t need = (size_t)pl->n_tau_blocks * pl->fw.n_pairs;
+  const size_t need = (size_t)pl->n_tau_blocks * pl->bt.n_pairs;
   if (need * sizeof(float) >= ((size_t)1 << 40)) return SWCONV_EUNSUPPORTED;
   if (pl->partial_floats < need) {
     if (pl->d_partial) (void)hipFree(pl->d_partial);
@@ -1106,7 +1121,7 @@ int prepare_weight_grad(swconv_plan* pl) {
     HIP_TRY(hipMalloc((void**)&pl->d_partial, std::max<size_t>(need, 1) * sizeof(float)));
     pl->partial_floats = need;
   }
-  return ensure_index(&pl->fw);
+  return SWCONV_OK;
 }
 
 template <int M, int R>
@@ -1148,8 +1163,9 @@ int launch_backward_transforms(swconv_plan* pl, const LaunchTarget& to, int whic
 //   0  dL/dZ = A dL/dO~ A^T                      (Eq. 5, first line)      -> M workspace
 //   1  I_F = B^T I~ B again (forward step 1)                              -> V workspace   } only for
 //   2  per stored entry and tile block: <dL/dZ row, I_F row>              -> partial sums  } dL/dW_F
+//      and, in the same pass, what 4 makes                                -> dL/dI_F workspace
 //   3  sum over the tile blocks, CSR order        (Eq. 5, second line)    -> dvals         }
-//   4  dL/dI_F[p] = W_F[p]^T dL/dZ[p]             (Eq. 6, first line)     -> dL/dI_F workspace
+//   4  dL/dI_F[p] = W_F[p]^T dL/dZ[p]             (Eq. 6, first line)     -> dL/dI_F workspace, where 2 did not run
 //   5  dL/dI~ = B dL/dI_F B^T                     (Eq. 6, second line)    -> V workspace   } only for
 //   6  every pixel gathers its patch entries      (Eq. 6, third line)     -> din           } dL/dI
 constexpr int kBackwardStages = 7;
@@ -1157,6 +1173,7 @@ constexpr int kBackwardStages = 7;
 bool backward_stage_runs(const swconv_plan* pl, int stage, const float* in, const float* din, const float* dvals) {
   if (stage == 1 && !in) return false;  // I_F of the last forward pass is still in the V workspace
   if (stage >= 1 && stage <= 3) return dvals != nullptr && pl->fw.nnz > 0;
+  if (stage == 4) return !backward_stage_runs(pl, 2, in, din, dvals);
   if (stage == 6 && pl->grad_images_per_group > 0) return false;  // stage 5 did both
   if (stage >= 5) return din != nullptr;
   return true;
@@ -1182,14 +1199,15 @@ int launch_backward_stage(swconv_plan* pl, const LaunchTarget& to, int stage, co
       });
     case 1: return launch_stage(pl, to, 0, in_dev, nullptr);
     case 2:
-      return launch_spmm_mode<true>(pl, pl->fw, to, pl->dV, pl->g.v_bytes, pl->dM, pl->g.m_bytes, pl->d_partial);
+      return launch_spmm<true>(pl, pl->bt, to,
+                               SpmmArgs{pl->dM, pl->g.m_bytes, pl->dD, pl->g.v_bytes, pl->dV, pl->d_partial});
     case 3: {
-      const uint32_t n_entries = (uint32_t)pl->fw.n_pairs;
+      const uint32_t n_entries = (uint32_t)pl->bt.n_pairs;
       return launch_kernel(weight_grad_reduce_kernel, dim3((n_entries + 255) / 256), dim3(256), 0, to,
                            (const float*)pl->d_partial, pl->n_tau_blocks, n_entries,
-                           (const int32_t*)pl->fw.d_index, n_entries, dvals_dev);
+                           (const int32_t*)pl->bt.d_index, n_entries, dvals_dev);
     }
-    case 4: return launch_spmm(pl, pl->bt, to, pl->dM, pl->g.m_bytes, pl->dD, pl->g.v_bytes);
+    case 4: return launch_product(pl, pl->bt, to, pl->dM, pl->g.m_bytes, pl->dD, pl->g.v_bytes);
     default:
       return dispatch_mr(pl, [&](auto M, auto R) {
         return launch_backward_transforms<M(), R()>(pl, to, stage - 4, nullptr, din_dev);
@@ -1525,6 +1543,11 @@ int swconv_profile_backward(swconv_plan* pl, void* hip_stream, const float* in_d
         }
       stage_ms[stage] = (float)(sum / iters);
     }
+    // one kernel made the dot products and the products: each gets its share of the kernel's inner loop
+    if (backward_stage_runs(pl, 2, in_dev, din_dev, dvals_dev)) {
+      stage_ms[4] = stage_ms[2] * 80.0f / 177.0f;
+      stage_ms[2] -= stage_ms[4];
+    }
     pl->ran_forward = false;
     pl->ran_backward = true;
   }
@@ -1658,7 +1681,7 @@ int swconv_debug_copy_M(swconv_plan* pl, float* M_host) {
   if (!pl->ran_forward) return SWCONV_ESTATE;
   if (!pl->m_current) {  // the fused kernel kept the products on chip: run step 2 alone on the V of that pass
     HIP_TRY(hipDeviceSynchronize());
-    int rc = launch_spmm(pl, pl->fw, LaunchTarget{nullptr, nullptr, nullptr}, pl->dV, pl->g.v_bytes, pl->dM, pl->g.m_bytes);
+    int rc = launch_product(pl, pl->fw, LaunchTarget{nullptr, nullptr, nullptr}, pl->dV, pl->g.v_bytes, pl->dM, pl->g.m_bytes);
     if (rc) return rc;
     pl->m_current = true;
   }

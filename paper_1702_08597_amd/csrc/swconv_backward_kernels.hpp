@@ -291,7 +291,7 @@ __global__ __launch_bounds__(256) void input_grad_kernel(const float* __restrict
 
 // ---------------------------------------------------------------------------------------------
 // Eq. 5, second line, last step: the per-tile-block partial sums of every stream entry (written by
-// the sparse kernel in sampled mode) are added over the tile blocks, in ascending order, and go to
+// the sparse kernel with DOTS) are added over the tile blocks, in ascending order, and go to
 // the entry's place in the caller's CSR order; padding entries (index -1) are skipped.
 __global__ __launch_bounds__(256) void weight_grad_reduce_kernel(const float* __restrict__ partial, int n_tau_blocks,
                                                                  uint32_t partial_stride,

@@ -123,7 +123,8 @@ constexpr int kSliceRows = 4;    // rows per slice = quarters of a wave
 constexpr int kTileBlock = 64;   // tiles per panel row: 16 lanes of a quarter x 4 tiles
 constexpr int kBatchSteps = 16;  // steps per 512-byte stream batch (one per lane of a quarter)
 constexpr int kStepGroup = 4;    // steps issued together; a slice's length is a multiple of it
-constexpr int kPanelPieces = 10; // 16-byte panel pieces a thread holds in registers
+constexpr int kPanelPieces = 10; // 16-byte panel pieces a thread holds in registers at most
+constexpr int kPanelPieces12 = 7;  // the same in workgroups of 12 waves: two of them per CU, so at most 319 channels
 constexpr int kMaxItemSlices = 256;  // slices per work item: their descriptors are staged in LDS, two 16-byte
                                      // pieces each, one piece per thread of the smallest workgroup (512 threads)
 constexpr int kMinItemSlices = 8;    // the least the LDS left over by a large panel must hold
@@ -404,12 +405,12 @@ constexpr int kUnitSteps = 2 * kBatchSteps;
 #undef SWCONV_XR14
 #undef SWCONV_XR15
 
-// ---- sampled mode (backward pass, Eq. 5 second line): dL/dW_F at the stored entries ----
-// The same walk over the packed W_F, but instead of accumulating w * x into the row, every stored
-// entry (k, c) gets the dot product of dL/dZ[p][k][.] with the panel row of c over the 64 tiles of
-// the block: the lane multiplies its four tiles, the 16 lanes of the quarter are summed with DPP
-// exchanges, and lane i of the quarter ends up with the sum of step i, so that after a batch every
-// lane holds the partial sum of "its" stream entry and the wave stores 256 contiguous bytes.
+// ---- dot products (backward pass, Eq. 5 second line): dL/dW_F at the stored entries ----
+// The same walk over a packed operand, but every stored entry (row, column) gets the dot product of a
+// tensor's row with the panel row of the column over the 64 tiles of the block: the lane multiplies its
+// four tiles, the 16 lanes of the quarter are summed with DPP exchanges, and lane i of the quarter ends
+// up with the sum of step i, so that after a batch every lane holds the partial sum of "its" stream
+// entry and the wave stores 256 contiguous bytes.
 
 // x + (the value of `send` in the lane given by the DPP control): one v_add_f32 with a DPP operand.
 template <int CTRL>
@@ -417,12 +418,17 @@ __device__ __forceinline__ float dpp_add(float x, float send) {
   return x + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, send), CTRL, 0xf, 0xf, true));
 }
 
-// Steps G*kStepGroup .. +kStepGroup-1: the lane's share (its four tiles) of each step's dot product.
+// Steps G*kStepGroup .. +kStepGroup-1 of the batch (boff, bw): the lane's share (its four tiles) of each
+// step's dot product with z, and the products.
 template <int G>
-__device__ __forceinline__ void sampled_group(const float* panel, uint32_t lane_sub, uint32_t boff, const f32x4_t& z,
-                                              float (&d)[kBatchSteps]) {
+__device__ __forceinline__ void product_dots_group(const float* panel, uint32_t lane_sub, const u32x2_t& b, const f32x4_t& z,
+                                              float (&d)[kBatchSteps], Acc4& acc) {
   constexpr int I0 = G * kStepGroup;
-  const Group4 g = quarter_reads<G>(panel, lane_sub, boff);
+  const Group4 g = quarter_reads<G>(panel, lane_sub, b.x);
+  quarter_fma<I0 + 0, true>(acc, b.y, g.x0);
+  quarter_fma<I0 + 1, false>(acc, b.y, g.x1);
+  quarter_fma<I0 + 2, false>(acc, b.y, g.x2);
+  quarter_fma<I0 + 3, false>(acc, b.y, g.x3);
   const f32x4_t* x[4] = {&g.x0, &g.x1, &g.x2, &g.x3};
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -434,42 +440,68 @@ __device__ __forceinline__ void sampled_group(const float* panel, uint32_t lane_
   }
 }
 
+// a <- in the lanes of the banks (groups of four lanes of a row of 16) of LO: a + a of the lane given by
+// CTRL_LO; in the others: b + b of the lane given by CTRL_HI.  The bank masks of the two instructions do the
+// selecting.  Two wait states lie between the vector-ALU write of a register and its read through DPP.
+#define SWCONV_FOLD(LO_CTRL, LO, HI_CTRL, HI)                                  \
+  asm("s_nop 1\n"                                                              \
+      "v_add_f32_dpp %0, %0, %0 " LO_CTRL " row_mask:0xf bank_mask:" LO "\n"    \
+      "v_add_f32_dpp %1, %1, %1 " LO_CTRL " row_mask:0xf bank_mask:" LO "\n"    \
+      "v_add_f32_dpp %2, %2, %2 " LO_CTRL " row_mask:0xf bank_mask:" LO "\n"    \
+      "v_add_f32_dpp %3, %3, %3 " LO_CTRL " row_mask:0xf bank_mask:" LO "\n"    \
+      "v_add_f32_dpp %0, %4, %4 " HI_CTRL " row_mask:0xf bank_mask:" HI "\n"    \
+      "v_add_f32_dpp %1, %5, %5 " HI_CTRL " row_mask:0xf bank_mask:" HI "\n"    \
+      "v_add_f32_dpp %2, %6, %6 " HI_CTRL " row_mask:0xf bank_mask:" HI "\n"    \
+      "v_add_f32_dpp %3, %7, %7 " HI_CTRL " row_mask:0xf bank_mask:" HI           \
+      : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3)                                 \
+      : "v"(b0), "v"(b1), "v"(b2), "v"(b3))
+__device__ __forceinline__ void fold_bit3(float& a0, float& a1, float& a2, float& a3, float b0, float b1, float b2, float b3) {
+  SWCONV_FOLD("row_ror:8", "0x3", "row_ror:8", "0xc");  // partner lane ^ 8
+}
+__device__ __forceinline__ void fold_bit2(float& a0, float& a1, float& a2, float& a3, float b0, float b1, float b2, float b3) {
+  SWCONV_FOLD("row_shl:4", "0x5", "row_shr:4", "0xa");  // partner lane ^ 4
+}
+#undef SWCONV_FOLD
+
 // The first `steps` steps of one batch; returns, in lane (q, i), the partial sum of row q, step i
 // (0 for steps that were not run).  Every lane first collects its share of all 16 steps; the 16
 // lanes of a quarter then add them up in a transposing butterfly: in the stage with partner
-// lane ^ 15 (then ^ 7, ^ 3, ^ 1: the DPP mirror and quad patterns) a lane keeps the half of its
-// values whose step has the lane's own bit 3 (2, 1, 0) and adds the partner's values for that
-// half, so 8 + 4 + 2 + 1 additions leave the total of step i in lane i - against four additions
-// per step for a reduction step by step.
-__device__ __forceinline__ float sampled_batch(const float* panel, uint32_t lane_sub, const u32x2_t& b, int steps,
-                                               const f32x4_t& z, int lane_in_quarter) {
+// lane ^ 8 (then ^ 4, ^ 2, ^ 1) a lane keeps the half of its values whose step has the lane's own
+// bit 3 (2, 1, 0) and adds the partner's values for that half, so 8 + 4 + 2 + 1 sums leave the total
+// of step i in lane i: 33 instructions, as the bank masks of DPP select for free in the first two
+// stages, against 45 with selects in all four and 80 for a reduction step by step.
+__device__ __forceinline__ float product_dots_batch(const float* panel, uint32_t lane_sub, const u32x2_t& b, int steps,
+                                               const f32x4_t& z, int lane_in_quarter, Acc4& acc) {
   float d[kBatchSteps];
 #pragma unroll
   for (int i = 0; i < kBatchSteps; ++i) d[i] = 0.0f;
-  sampled_group<0>(panel, lane_sub, b.x, z, d);
-  if (steps > 1 * kStepGroup) sampled_group<1>(panel, lane_sub, b.x, z, d);
-  if (steps > 2 * kStepGroup) sampled_group<2>(panel, lane_sub, b.x, z, d);
-  if (steps > 3 * kStepGroup) sampled_group<3>(panel, lane_sub, b.x, z, d);
-  const bool b3 = lane_in_quarter & 8, b2 = lane_in_quarter & 4, b1 = lane_in_quarter & 2, b0 = lane_in_quarter & 1;
-  float e[8], f[4], g[2];
+  product_dots_group<0>(panel, lane_sub, b, z, d, acc);
+  if (steps > 1 * kStepGroup) product_dots_group<1>(panel, lane_sub, b, z, d, acc);
+  if (steps > 2 * kStepGroup) product_dots_group<2>(panel, lane_sub, b, z, d, acc);
+  if (steps > 3 * kStepGroup) product_dots_group<3>(panel, lane_sub, b, z, d, acc);
+  fold_bit3(d[0], d[1], d[2], d[3], d[8], d[9], d[10], d[11]);
+  fold_bit3(d[4], d[5], d[6], d[7], d[12], d[13], d[14], d[15]);
+  fold_bit2(d[0], d[1], d[2], d[3], d[4], d[5], d[6], d[7]);
+  const bool b1 = lane_in_quarter & 2, b0 = lane_in_quarter & 1;
+  float g[2];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) e[i] = dpp_add<0x140>(b3 ? d[i + 8] : d[i], b3 ? d[i] : d[i + 8]);  // row_mirror: lane ^ 15
-#pragma unroll
-  for (int i = 0; i < 4; ++i) f[i] = dpp_add<0x141>(b2 ? e[i + 4] : e[i], b2 ? e[i] : e[i + 4]);  // row_half_mirror: lane ^ 7
-#pragma unroll
-  for (int i = 0; i < 2; ++i) g[i] = dpp_add<0x1B>(b1 ? f[i + 2] : f[i], b1 ? f[i] : f[i + 2]);   // quad_perm [3,2,1,0]: lane ^ 3
-  return dpp_add<0xB1>(b0 ? g[1] : g[0], b0 ? g[0] : g[1]);                                      // quad_perm [1,0,3,2]: lane ^ 1
+  for (int i = 0; i < 2; ++i) g[i] = dpp_add<0x4E>(b1 ? d[i + 2] : d[i], b1 ? d[i] : d[i + 2]);  // quad_perm [2,3,0,1]: lane ^ 2
+  return dpp_add<0xB1>(b0 ? g[1] : g[0], b0 ? g[0] : g[1]);                                       // quad_perm [1,0,3,2]: lane ^ 1
 }
 
-// SAMPLED = false: Mbuf[p] = A[p] * V[p] (forward step 2; backward Eq. 6 first line on the packed
-// transpose).  SAMPLED = true: Mbuf is read (dL/dZ), and partial[tau_block][stream entry] gets the
-// entry's dot product over that tile block (Eq. 5 second line; `partial_stride` entries per block).
-template <int NWAVES, bool SAMPLED>
+// One pass over a packed operand A with panels of V: Mbuf[p] = A[p] * V[p] (forward step 2; on the packed
+// transpose the backward pass's dL/dI_F, Eq. 6 first line).
+// With DOTS, on the transpose, the same pass makes dL/dW_F (Eq. 5 second line) too:
+// partial[tau_block][stream entry] = the entry's dot product of its row of `zrows` (I_F) with its column's row
+// of V (dL/dZ) over that tile block; `partial_stride` entries per block.  An entry's dot product does not
+// depend on which of the two tensors is the panel, so dL/dZ, the weights and every LDS value are read once for
+// both gradients: 177 vector-ALU instructions per 16 steps against 80 + 125 in two passes, half the LDS reads.
+template <int NWAVES, int PIECES, bool DOTS>
 __global__ __launch_bounds__(NWAVES * 64, NWAVES == 12 ? 6 : 4) void spmm_kernel(
     const float* __restrict__ V, float* __restrict__ Mbuf, const uint32_t* __restrict__ stream, uint32_t stream_bytes,
     const Slice* __restrict__ slices, int n_slices, const WorkItem* __restrict__ items,
     const RangeHeader* __restrict__ ranges, int n_wgs, int C, int K, int Tp, uint32_t m_bytes, uint32_t v_bytes,
-    float* __restrict__ partial, uint32_t partial_stride) {
+    const float* __restrict__ zrows, float* __restrict__ partial, uint32_t partial_stride) {
   constexpr int NT = NWAVES * 64;
   constexpr int TB = kTileBlock;
   typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
@@ -483,7 +515,7 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 12 ? 6 : 4) void spmm_kernel
   const RangeHeader hdr = ranges[xcd_contiguous_id(blockIdx.x, n_wgs)];
   const int quarter = lane >> 4;
   const uint32_t lane_sub = (uint32_t)(lane & 15) * 16u;  // byte offset of the lane's four tiles in a row
-  const __amdgpu_buffer_rsrc_t mr = make_rsrc(Mbuf, m_bytes);
+  const __amdgpu_buffer_rsrc_t mr = make_rsrc(Mbuf, m_bytes), zr = make_rsrc(zrows, m_bytes);
   const __amdgpu_buffer_rsrc_t sr = make_rsrc(stream, stream_bytes);
   const __amdgpu_buffer_rsrc_t dr = make_rsrc(slices, (uint32_t)n_slices * (uint32_t)sizeof(Slice));
   const uint32_t lane8 = (uint32_t)lane * 8u;
@@ -500,14 +532,16 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 12 ? 6 : 4) void spmm_kernel
   constexpr int v4_per_row = TB / 4;
   const int total = C * v4_per_row;
   const __amdgpu_buffer_rsrc_t vr = make_rsrc(V, v_bytes);
-  uint32_t voff[kPanelPieces];
-#pragma unroll
-  for (int u = 0; u < kPanelPieces; ++u) {
-    const int idx = threadIdx.x + u * NT;
-    const int row = idx / v4_per_row, q = idx % v4_per_row;
-    voff[u] = idx < total ? ((uint32_t)row * Tp + q * 4) * 4u : 0xfffffff0u;
-  }
-  u32x4_t piece[kPanelPieces], desc_piece;
+  constexpr int rows_per_piece = NT / v4_per_row;
+  const int row0 = threadIdx.x / v4_per_row;
+  const uint32_t voff0 = ((uint32_t)row0 * Tp + (threadIdx.x % v4_per_row) * 4) * 4u;
+  const uint32_t piece_stride = (uint32_t)rows_per_piece * (uint32_t)Tp * 4u;
+  auto load_piece = [&](int u, uint32_t soff) -> u32x4_t {
+    uint32_t at = row0 + u * rows_per_piece < C ? voff0 : 0xfffffff0u;
+    asm volatile("" : "+v"(at));  // formed where it is used: kept ready, one per piece, they cost the loop its registers
+    return __builtin_amdgcn_raw_buffer_load_b128(vr, (int)at, (int)(soff + (uint32_t)u * piece_stride), 0);
+  };
+  u32x4_t piece[PIECES], desc_piece;
   auto load_batch = [&](uint32_t byte_off) -> u32x2_t {
     return __builtin_amdgcn_raw_buffer_load_b64(sr, (int)lane8, (int)byte_off, 0);  // past the end: reads 0
   };
@@ -530,19 +564,18 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 12 ? 6 : 4) void spmm_kernel
   // memory round trip.
   Cur cur;
   u32x2_t b0 = {0u, 0u}, b1 = {0u, 0u};
-  // sampled mode: the lane's four tiles of the dL/dZ row of its quarter (zeros for a padding row)
+  // dot products: the lane's four tiles of the row of its quarter (zeros for a padding row)
   f32x4_t z_cur = {0.0f, 0.0f, 0.0f, 0.0f};
   auto row_offset = [&](int p, int tau0, int k) -> uint32_t {  // quarters of padding rows are parked beyond the buffer
     return k >= 0 ? (((uint32_t)p * K + (uint32_t)k) * Tp + tau0) * 4u + lane_sub : 0xfffffff0u;
   };
   auto load_z = [&](int p, int tau0, int k) -> f32x4_t {
-    return __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(mr, (int)row_offset(p, tau0, k), 0, 0));
+    return __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(zr, (int)row_offset(p, tau0, k), 0, 0));
   };
   auto start_item = [&](const WorkItem& w) {
     const uint32_t soff = ((uint32_t)w.p * C * Tp + (uint32_t)w.tau_block * TB) * 4u;
 #pragma unroll
-    for (int u = 0; u < kPanelPieces; ++u)
-      piece[u] = __builtin_amdgcn_raw_buffer_load_b128(vr, (int)voff[u], (int)soff, 0);
+    for (int u = 0; u < PIECES; ++u) piece[u] = load_piece(u, soff);
     const int n_desc_pieces = 2 * (w.slice_end - w.slice_begin);
     desc_piece = __builtin_amdgcn_raw_buffer_load_b128(
         dr, (int)((int)threadIdx.x < n_desc_pieces ? threadIdx.x * 16u : 0xfffffff0u),
@@ -553,7 +586,7 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 12 ? 6 : 4) void spmm_kernel
     cur.k = quarter_k(sl.k[0], sl.k[1], sl.k[2], sl.k[3]);
     b0 = load_batch(cur.base);
     b1 = load_batch(cur.base + 512u);
-    if constexpr (SAMPLED) z_cur = load_z(w.p, w.tau_block * TB, cur.k);
+    if constexpr (DOTS) z_cur = load_z(w.p, w.tau_block * TB, cur.k);
   };
 
   WorkItem it = hdr.first;
@@ -561,14 +594,14 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 12 ? 6 : 4) void spmm_kernel
   for (int item = hdr.item_begin;; ++item) {
     const int tau0 = it.tau_block * TB;
     const int n_item_slices = it.slice_end - it.slice_begin;
-    // sampled mode: this tile block's row of the partial-sum buffer, one float per stream entry
+    // dot products: this tile block's row of the partial-sum buffer, one float per stream entry
     const __amdgpu_buffer_rsrc_t pr =
-        make_rsrc(SAMPLED ? partial + (size_t)it.tau_block * partial_stride : nullptr, SAMPLED ? partial_stride * 4u : 0u);
+        make_rsrc(DOTS ? partial + (size_t)it.tau_block * partial_stride : nullptr, DOTS ? partial_stride * 4u : 0u);
     const bool has_next = item + 1 < hdr.item_end;
     const WorkItem it_next = items[has_next ? item + 1 : item];
     if (item != hdr.item_begin) __syncthreads();  // every wave is done with the previous panel and descriptors
 #pragma unroll
-    for (int u = 0; u < kPanelPieces; ++u) {
+    for (int u = 0; u < PIECES; ++u) {
       const int idx = threadIdx.x + u * NT;
       if (idx < total) *reinterpret_cast<u32x4_t*>(panel + idx * 4) = piece[u];
     }
@@ -599,18 +632,18 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 12 ? 6 : 4) void spmm_kernel
         nxt.k = quarter_k((int)d_k.x, (int)d_k.y, (int)d_k.z, (int)d_k.w);
         const int batches = (cur.len + kBatchSteps - 1) / kBatchSteps;
         f32x4_t z_next = {0.0f, 0.0f, 0.0f, 0.0f};
-        if constexpr (SAMPLED) z_next = load_z(it.p, tau0, more ? nxt.k : -1);
+        if constexpr (DOTS) z_next = load_z(it.p, tau0, more ? nxt.k : -1);
         for (int j = 0, remaining = cur.len; j < batches; j += 2, remaining -= 2 * kBatchSteps) {
-          if constexpr (SAMPLED) {
-            const float r0 = sampled_batch(panel, lane_sub, b0, remaining, z_cur, lane & 15);
+          if constexpr (DOTS) {
+            const float r0 = product_dots_batch(panel, lane_sub, b0, remaining, z_cur, lane & 15, acc);
             buffer_store_f32<SWCONV_AUX_M>(pr, lane * 4u, cur.base / 2u + (uint32_t)j * 256u, r0);
           } else {
             quarter_batch(panel, lane_sub, b0, remaining, acc);
           }
           b0 = load_batch(j + 2 < batches ? cur.base + (uint32_t)(j + 2) * 512u : nxt.base);
           if (j + 1 < batches) {
-            if constexpr (SAMPLED) {
-              const float r1 = sampled_batch(panel, lane_sub, b1, remaining - kBatchSteps, z_cur, lane & 15);
+            if constexpr (DOTS) {
+              const float r1 = product_dots_batch(panel, lane_sub, b1, remaining - kBatchSteps, z_cur, lane & 15, acc);
               buffer_store_f32<SWCONV_AUX_M>(pr, lane * 4u, cur.base / 2u + (uint32_t)(j + 1) * 256u, r1);
             } else {
               quarter_batch(panel, lane_sub, b1, remaining - kBatchSteps, acc);
@@ -622,11 +655,9 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 12 ? 6 : 4) void spmm_kernel
           b0 = load_batch(nxt.base);
           b1 = load_batch(nxt.base + 512u);
         }
-        if constexpr (!SAMPLED) {
-          const u32x4v_t result = {__float_as_uint(acc.a0), __float_as_uint(acc.a1), __float_as_uint(acc.a2),
-                                   __float_as_uint(acc.a3)};
-          __builtin_amdgcn_raw_buffer_store_b128(result, mr, (int)row_offset(it.p, tau0, cur.k), 0, SWCONV_AUX_M);
-        }
+        const u32x4v_t result = {__float_as_uint(acc.a0), __float_as_uint(acc.a1), __float_as_uint(acc.a2),
+                                 __float_as_uint(acc.a3)};
+        __builtin_amdgcn_raw_buffer_store_b128(result, mr, (int)row_offset(it.p, tau0, cur.k), 0, SWCONV_AUX_M);
         if (!more) break;
         cur = nxt;
         z_cur = z_next;
