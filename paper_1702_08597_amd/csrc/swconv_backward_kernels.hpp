@@ -35,31 +35,17 @@ __global__ __launch_bounds__(256) void output_grad_transform_kernel(const float*
   float* my = stage + wave * g.out_area;
   const BlockImage* bi = blocks + (size_t)blockIdx.x * g.slots;
   const size_t plane = (size_t)g.Ho * g.Wo;
+  const TileInfo ti = tiles[tau0 + lane];  // asked for first: it arrives while the rows are staged
   if (k < g.K) {
-    for (int sidx = 0; sidx < g.slots; ++sidx) {
-      const BlockImage b = bi[sidx];
-      if (b.n < 0) continue;
-      // loads past the part's end return 0 (descriptor), so the padded tail of the run is zero
-      const __amdgpu_buffer_rsrc_t src = make_rsrc(dout + (size_t)b.n * g.out_image_stride + k * plane + b.out_elem0,
-                                                   (uint32_t)b.out_span * 4u);
-      float* dst = my + b.out_off + lane;
-      constexpr int EL = 4;  // loads per lane in flight
-      for (int e0 = 0; e0 < b.out_span; e0 += 64 * EL) {
-        float buf[EL];
-#pragma unroll
-        for (int u = 0; u < EL; ++u)
-          if (e0 + u * 64 < b.out_span) buf[u] = buffer_load_f32(src, (lane + u * 64) * 4u, e0 * 4u);
-#pragma unroll
-        for (int u = 0; u < EL; ++u)
-          if (e0 + u * 64 < b.out_span) dst[e0 + u * 64] = buf[u];
-      }
-    }
+    auto part = [&](const BlockImage& b) {
+      return StagedPart{dout + (size_t)max(b.n, 0) * g.out_image_stride + k * plane + b.out_elem0, b.out_span, b.out_off};
+    };
+    stage_parts<1>(bi, g.slots, g.out_area, my, lane, part);
   }
   __syncthreads();
   if (k >= g.K) return;
   float gr[M][M];
   {
-    const TileInfo ti = tiles[tau0 + lane];
     const int y0 = (int16_t)(ti.yx0 & 0xffff), x0 = ti.yx0 >> 16;
     // rows / columns of the tile inside the output (<= 0 for a padding tile, whose y0 is -32768)
     const int rows = y0 == -32768 ? 0 : g.Ho - (y0 + g.pad), cols = g.Wo - (x0 + g.pad);

@@ -138,11 +138,112 @@ __device__ __forceinline__ int xcd_contiguous_id(int bid, int nblocks) {
   return xcd * per + (xcd < rem ? xcd : rem) + local;
 }
 
+// One image's part of a block's rows: where they lie in the tensor, how many floats, where they go in the
+// wave's staging area (a run rounded up to a multiple of 64 floats).
+struct StagedPart {
+  const float* src;
+  int span, off;
+};
+
+// Copies the parts of a tile block into the wave's LDS area, with the loads of IG images x EL steps in flight before
+// the first LDS write.
+// stage_dwords: 64 floats a load.  The descriptor ends with the part: lanes past the end read zeros, and as a run is
+// padded to a multiple of 64 floats neither loads nor LDS writes need lane predicates.
+template <int IG, int EL, typename Part>
+__device__ __forceinline__ void stage_dwords(const BlockImage* bi, int slots, float* my, int lane, Part part) {
+  for (int s0 = 0; s0 < slots; s0 += IG) {
+    __amdgpu_buffer_rsrc_t src[IG];
+    float* dst[IG];
+    int span[IG], max_span = 0;
+#pragma unroll
+    for (int i = 0; i < IG; ++i) {
+      const BlockImage b = bi[min(s0 + i, slots - 1)];
+      const StagedPart pt = part(b);
+      span[i] = s0 + i < slots && b.n >= 0 ? pt.span : 0;
+      src[i] = make_rsrc(pt.src, (uint32_t)span[i] * 4u);
+      dst[i] = my + pt.off + lane;
+      max_span = max(max_span, span[i]);
+    }
+    for (int e0 = 0; e0 < max_span; e0 += 64 * EL) {
+      float buf[IG][EL];
+#pragma unroll
+      for (int i = 0; i < IG; ++i)
+#pragma unroll
+        for (int u = 0; u < EL; ++u)
+          if (e0 + u * 64 < span[i]) buf[i][u] = buffer_load_f32(src[i], (lane + u * 64) * 4u, e0 * 4u);
+#pragma unroll
+      for (int i = 0; i < IG; ++i)
+#pragma unroll
+        for (int u = 0; u < EL; ++u)
+          if (e0 + u * 64 < span[i]) dst[i][e0 + u * 64] = buf[i][u];
+    }
+  }
+}
+// stage_quads: 256 floats a load.  A row start is only known to be aligned to a float, which is all that a multi-dword
+// buffer load needs.  Every load lies wholly inside or wholly outside its descriptor: that covers the whole quads of
+// the span, and the one to three floats that remain come by a dword load.  Lanes past the quads write nothing: the
+// next part's run may begin there.
+template <int IG, int EL, typename Part>
+__device__ __forceinline__ void stage_quads(const BlockImage* bi, int slots, float* my, int lane, Part part) {
+  typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
+  for (int s0 = 0; s0 < slots; s0 += IG) {
+    __amdgpu_buffer_rsrc_t src[IG];
+    float* dst[IG];
+    int span[IG], max_span = 0;
+    float tail[IG];
+#pragma unroll
+    for (int i = 0; i < IG; ++i) {
+      const BlockImage b = bi[min(s0 + i, slots - 1)];
+      const StagedPart pt = part(b);
+      span[i] = s0 + i < slots && b.n >= 0 ? pt.span : 0;
+      src[i] = make_rsrc(pt.src, (uint32_t)(span[i] & ~3) * 4u);
+      dst[i] = my + pt.off;
+      max_span = max(max_span, span[i]);
+      if (span[i] & 3)  // lanes past the span read 0 into the run's padding
+        tail[i] = buffer_load_f32(make_rsrc(pt.src, (uint32_t)span[i] * 4u), lane * 4u, (uint32_t)(span[i] & ~3) * 4u);
+    }
+    for (int e0 = 0; e0 < max_span; e0 += 256 * EL) {
+      u32x4_t buf[IG][EL];
+#pragma unroll
+      for (int i = 0; i < IG; ++i)
+#pragma unroll
+        for (int u = 0; u < EL; ++u)
+          if (e0 + u * 256 < span[i])
+            buf[i][u] = __builtin_amdgcn_raw_buffer_load_b128(src[i], lane * 16, (e0 + u * 256) * 4, 0);
+#pragma unroll
+      for (int i = 0; i < IG; ++i)
+#pragma unroll
+        for (int u = 0; u < EL; ++u)
+          if (e0 + u * 256 < span[i] && e0 + u * 256 + lane * 4 < (span[i] & ~3))
+            *reinterpret_cast<u32x4_t*>(dst[i] + e0 + u * 256 + lane * 4) = buf[i][u];
+    }
+#pragma unroll
+    for (int i = 0; i < IG; ++i)
+      if (lane < (span[i] & 3)) dst[i][(span[i] & ~3) + lane] = tail[i];
+  }
+}
+// Which of them: quads where the parts are longer than 192 floats on average of the largest block.  Up to there dword
+// loads need one round trip to memory too, and every lane of them carries something (64 images of 13 x 13, 384
+// channels: input transform 12.2 us against 12.6, output gradient transform 14.5 against 15.8).  Beyond it they go
+// to memory in rounds, six in a row for the 26 rows of 56 pixels that a block touches: 32 images of 56 x 56,
+// 256 channels: 75 -> 63 us and 69 -> 60 us with quads (5.3 and 5.5 TB/s); 11 of 29 x 23, 131 channels: 10.3 -> 9.8 us.
+// <2, 4> for blocks of at most two images, <4, 2> for the others: 32 registers either way.
+// DWORD_IMAGES: images in flight on the dword path; the output gradient's 13 x 13 planes go faster one by one.
+template <int DWORD_IMAGES, typename Part>
+__device__ __forceinline__ void stage_parts(const BlockImage* bi, int slots, int area, float* my, int lane, Part part) {
+  if (area <= 192 * slots)
+    stage_dwords<DWORD_IMAGES, 4>(bi, slots, my, lane, part);
+  else if (slots <= 2)
+    stage_quads<2, 4>(bi, slots, my, lane, part);
+  else
+    stage_quads<4, 2>(bi, slots, my, lane, part);
+}
+
 // ---------------------------------------------------------------------------------------------
 // Step 1: gather phi + V = B^T d B.  A wave owns one channel and 64 consecutive tiles: it copies
 // the input rows those tiles touch into its private LDS area with lane-contiguous (coalesced)
-// loads - each pixel is read from memory once although up to (t/m)^2 tiles use it; the loads of
-// up to four images are all in flight before the first LDS write - then every lane gathers its
+// loads (stage_parts) - each pixel is read from memory once although up to (t/m)^2 tiles use it -
+// then every lane gathers its
 // t x t tile from LDS (clamped addresses, all reads issued back to back, then selects zero what
 // lies outside the image), transforms it in registers and stores one value per position:
 // 64 lanes -> 256 contiguous bytes of V[p][c][.], addressed as wave-uniform row + lane.
@@ -163,38 +264,10 @@ __global__ __launch_bounds__(256) void input_transform_kernel(const float* __res
   const size_t plane = (size_t)g.H * g.W;
   const TileInfo ti = tiles[tau0 + lane];  // asked for first: it arrives while the rows are staged
   if (c < g.C) {
-    // Each image part is read through its own buffer descriptor (base = first staged element,
-    // size = the part's bytes): lanes past the end read zeros, so loads and LDS writes need no
-    // lane predicates; every part's run is padded to a multiple of 64 floats to take the zero tail.
-    constexpr int IG = 4, EL = 4;  // images x loads per lane in flight
-    for (int s0 = 0; s0 < g.slots; s0 += IG) {
-      __amdgpu_buffer_rsrc_t src[IG];
-      float* dst[IG];
-      int span[IG], max_span = 0;
-#pragma unroll
-      for (int i = 0; i < IG; ++i) {
-        const int sidx = min(s0 + i, g.slots - 1);
-        const BlockImage b = bi[sidx];
-        const bool used = s0 + i < g.slots && b.n >= 0;
-        span[i] = used ? b.in_span : 0;
-        src[i] = make_rsrc(in + (size_t)max(b.n, 0) * g.in_image_stride + c * plane + b.in_elem0, (uint32_t)span[i] * 4u);
-        dst[i] = my + b.in_off + lane;
-        max_span = max(max_span, span[i]);
-      }
-      for (int e0 = 0; e0 < max_span; e0 += 64 * EL) {
-        float buf[IG][EL];
-#pragma unroll
-        for (int i = 0; i < IG; ++i)
-#pragma unroll
-          for (int u = 0; u < EL; ++u)
-            if (e0 + u * 64 < span[i]) buf[i][u] = buffer_load_f32(src[i], (lane + u * 64) * 4u, e0 * 4u);
-#pragma unroll
-        for (int i = 0; i < IG; ++i)
-#pragma unroll
-          for (int u = 0; u < EL; ++u)
-            if (e0 + u * 64 < span[i]) dst[i][e0 + u * 64] = buf[i][u];
-      }
-    }
+    auto part = [&](const BlockImage& b) {
+      return StagedPart{in + (size_t)max(b.n, 0) * g.in_image_stride + c * plane + b.in_elem0, b.in_span, b.in_off};
+    };
+    stage_parts<4>(bi, g.slots, g.in_area, my, lane, part);
   }
   __syncthreads();
   if (c >= g.C) return;
