@@ -1138,17 +1138,20 @@ int launch_backward_transforms(swconv_plan* pl, const LaunchTarget& to, int whic
     return launch_kernel(kern, dim3(g.Tp / 64, (g.K + 3) / 4), dim3(256), (size_t)4 * g.out_area * sizeof(float), to,
                          dout, pl->dM, pl->d_tiles, pl->d_blocks, g);
   }
-  if (which == 1 && pl->grad_images_per_group > 0) {  // both remaining steps at once, planes in LDS
-    const int G = pl->grad_images_per_group;
-    const size_t lds = (size_t)4 * (((size_t)G * g.H * g.W + 63) / 64 * 64 + 64) * sizeof(float);
-    auto kern = input_grad_kernel<M, R>;
-    static bool attr_set = false;
-    if (!attr_set) {
-      HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes));
-      attr_set = true;
+  if constexpr ((M + R - 2) / M == 1) {  // the other plans have no grad_images_per_group
+    if (which == 1 && pl->grad_images_per_group > 0) {  // both remaining steps at once, planes in LDS
+      const int G = pl->grad_images_per_group;
+      const size_t lds = (size_t)4 * (((size_t)G * g.H * g.W + 63) / 64 * 64 + 64) * sizeof(float);
+      auto kern = G * g.tpi > 64 ? input_grad_kernel<M, R, true> : input_grad_kernel<M, R, false>;
+      static bool attr_set = false;
+      if (!attr_set) {
+        for (const void* k : {(const void*)input_grad_kernel<M, R, true>, (const void*)input_grad_kernel<M, R, false>})
+          HIP_TRY(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes));
+        attr_set = true;
+      }
+      return launch_kernel(kern, dim3((g.N + G - 1) / G, (g.C + 3) / 4), dim3(256), lds, to, (const float*)pl->dD, din,
+                           (const GradTile*)pl->d_gtiles, G, g);
     }
-    return launch_kernel(kern, dim3((g.N + G - 1) / G, (g.C + 3) / 4), dim3(256), lds, to, (const float*)pl->dD, din,
-                         (const GradTile*)pl->d_gtiles, G, g);
   }
   if (which == 1)  // dL/dI~ = B dL/dI_F B^T, from the dL/dI_F workspace into the V workspace
     return launch_kernel(input_grad_patch_kernel<M, R>, dim3(g.Tp / 64, (g.C + 3) / 4), dim3(256), 0, to, pl->dD, pl->dV,
@@ -1343,9 +1346,8 @@ int swconv_plan_create(swconv_plan** out, int N, int C, int H, int W, int K, int
   {
     const int G = (int)std::min<int64_t>(N, std::max<int64_t>(1, 64 / g.tpi));
     const int64_t wave_floats = ((int64_t)G * H * W + 63) / 64 * 64 + 64;
-    // (with patches reaching two tiles back, F(2x2,5x5), its nine phases measured slower than the two kernels;
-    // with 8 x 8 patches, F(4x4,5x5), patch, transform and LDS indices together overflow the 256 vector registers)
-    if (4 * wave_floats * (int64_t)sizeof(float) <= kMaxLdsBytes && (t - 1) / m == 1 && t <= 6 &&
+    // (the kernel sums over direct neighbours: F(2x2,5x5), whose patches reach two tiles back, takes the two kernels)
+    if (4 * wave_floats * (int64_t)sizeof(float) <= kMaxLdsBytes && (t - 1) / m == 1 &&
         env_int("SWCONV_FUSE_INPUT_GRAD", 1) != 0) {
       try {
         GradTile none;

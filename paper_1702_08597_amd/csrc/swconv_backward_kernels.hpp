@@ -175,24 +175,34 @@ __global__ __launch_bounds__(256) void input_grad_gather_kernel(const float* __r
 // ---------------------------------------------------------------------------------------------
 // Eq. 6, second and third line in one kernel, for images whose planes fit LDS: no patch buffer.
 // A wave owns one input channel and a group of G whole images (G = 64 / tiles per image, at least
-// 1), whose planes it keeps in LDS.  In passes of 64 consecutive tiles every lane reads the t*t
-// values dL/dI_F(c, tau, :, :), applies B . B^T in registers and adds its t x t patch into the
-// plane.  Patches of tiles closer than t pixels overlap, so the additions run in (back+1)^2
-// phases, phase (ty mod (back+1), tx mod (back+1)): the tiles of one phase are disjoint, LDS
-// executes a wave's operations in order, and every pixel therefore receives its terms in a fixed
-// order.  Then the wave writes its planes with lane-contiguous stores.  Block = 4 waves = 4
-// channels of the same image group.
+// 1), whose planes it builds up in LDS.  In passes of 64 consecutive tiles every lane reads the t*t
+// values dL/dI_F(c, tau, :, :) and applies B . B^T in registers.  Patches of neighbouring tiles overlap by
+// R - 1 pixels (at most m: no patch reaches past its neighbour), and the overlaps are summed where that is cheapest:
+//   - columns in registers: a lane takes the last R - 1 columns of the tile to its left from the lane before it
+//     (DPP shift by one lane; the pass before hands lane 63's over in scalar registers);
+//   - rows through LDS: every tile stores its last R - 1 rows into the plane, then reads what the tile above
+//     has stored where its own first R - 1 rows go, adds and stores.
+// LDS executes a wave's operations in order, so the sums have a fixed order, and every pixel is stored at least
+// once: the planes need no zeroing.  Then the wave writes its planes with lane-contiguous stores.
+// LDS was the bound: adding whole patches in four phases of disjoint tiles takes 8 t^2 = 288 LDS instructions a pass
+// for F(4x4,3x3), this 32 and the right edge's.  32 images of 56 x 56, 256 channels: 104 -> 78 us (4.3 TB/s; three
+// workgroups fit a CU's LDS); 64 of 13 x 13, 384 channels: 21.1 -> 16.2 us; F(4x4,5x5), 32 of 27 x 27, 48 channels, whose
+// indices of whole patches overflowed the registers: 10.4 us against 16.5 for the patch and gather kernels.
+// PREFETCH: groups of more than one pass ask for the next pass's values before they work on the present one's, at
+// t^2 registers that groups of one pass spend on more waves per SIMD.
+// Block = 4 waves = 4 channels of the same image group.
 struct GradTile {
   int32_t org;  // float offset of pixel (0, 0) of the tile's image inside the wave's LDS area
   int32_t yx0;  // as TileInfo::yx0; y0 = x0 = -32768 for tiles past the last image
 };
 
-template <int M, int R>
+template <int M, int R, bool PREFETCH>
 __global__ __launch_bounds__(256) void input_grad_kernel(const float* __restrict__ dV, float* __restrict__ din,
                                                          const GradTile* __restrict__ gtiles, int images_per_group,
                                                          const Geometry g) {
   constexpr int t = Wino<M, R>::t;
-  constexpr int back = (t - 1) / M, PH = back + 1;
+  constexpr int ov = t - M;  // columns (rows) that a patch shares with the next one
+  static_assert(ov <= M, "a patch reaches no further than its neighbour");
   extern __shared__ float stage[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -204,16 +214,14 @@ __global__ __launch_bounds__(256) void input_grad_kernel(const float* __restrict
   const int area = images_per_group * plane;
   const int area_padded = (area + 63) / 64 * 64;  // the wave's planes, then one spare float per lane
   float* my = stage + (size_t)wave * (area_padded + 64);
-  for (int e = lane; e < area; e += 64) my[e] = 0.0f;
+  const int spare = area_padded + lane;  // entries outside the image go here
   const __amdgpu_buffer_rsrc_t src = make_rsrc(dV, g.v_bytes);
   const uint32_t pstride = (uint32_t)g.C * (uint32_t)g.Tp * 4u;
   const int tau0 = n0 * g.tpi, tau_end = tau0 + n_img * g.tpi;
-  for (int base = tau0; base < tau_end; base += 64) {
+  auto load = [&](int base, float (&f)[t][t], GradTile& gt) {
     const int tau = base + lane;
-    const bool live = tau < tau_end;
     // lanes past the group's last tile are parked past the end of the buffer: they read zeros
-    const uint32_t voff = live ? ((uint32_t)c * g.Tp + (uint32_t)tau) * 4u : 0xfffffff0u;
-    float f[t][t], d[t][t];
+    const uint32_t voff = tau < tau_end ? ((uint32_t)c * g.Tp + (uint32_t)tau) * 4u : 0xfffffff0u;
     uint32_t soff = 0;
 #pragma unroll
     for (int i = 0; i < t; ++i)
@@ -223,55 +231,90 @@ __global__ __launch_bounds__(256) void input_grad_kernel(const float* __restrict
         soff += pstride;
         asm volatile("" : "+s"(soff));
       }
-    const GradTile gt = gtiles[live ? tau : tau0];
+    gt = gtiles[tau < tau_end ? tau : tau0];
+  };
+  float carry[t][ov];  // the last columns of the tile before this pass's first one
+#pragma unroll
+  for (int a = 0; a < t; ++a)
+#pragma unroll
+    for (int b = 0; b < ov; ++b) carry[a][b] = 0.0f;
+  float f[t][t];
+  GradTile gt;
+  load(tau0, f, gt);
+  for (int base = tau0; base < tau_end; base += 64) {
+    float d[t][t];
+    const GradTile at = gt;
     input_grad_transform<M, R>(f, d);
-    const int y0 = (int16_t)(gt.yx0 & 0xffff), x0 = gt.yx0 >> 16;
-    const int ty = (y0 + g.pad) >> g.m_shift, tx = (x0 + g.pad) >> g.m_shift;
-    const int phase = live ? (ty % PH) * PH + tx % PH : -1;
-    // LDS index of every patch entry; entries outside the image go to a spare float of the lane
-    const int spare = area_padded + lane;
-    const int org = gt.org + y0 * g.W + x0;
-    int at[t][t];
+    if constexpr (PREFETCH)
+      if (base + 64 < tau_end) load(base + 64, f, gt);
+    const bool live = base + lane < tau_end;
+    const int y0 = (int16_t)(at.yx0 & 0xffff), x0 = at.yx0 >> 16;
+    const bool left = x0 > -g.pad, above = y0 > -g.pad;  // the tile has a neighbour there
 #pragma unroll
-    for (int a = 0; a < t; ++a) {
-      const bool yok = y0 + a >= 0 && y0 + a < g.H;
+    for (int a = 0; a < t; ++a)
 #pragma unroll
-      for (int b = 0; b < t; ++b) at[a][b] = (yok && x0 + b >= 0 && x0 + b < g.W) ? org + a * g.W + b : spare;
-    }
-#pragma unroll
-    for (int ph = 0; ph < PH * PH; ++ph) {
-      if (ph == 0 && base == tau0) {
-        // first phase of the first pass: the planes still hold zeros, so the patch is stored as it is
-        if (phase == 0) {
-#pragma unroll
-          for (int a = 0; a < t; ++a)
-#pragma unroll
-            for (int b = 0; b < t; ++b) my[at[a][b]] = d[a][b];
-        }
-      } else if (phase == ph) {
-        // plain read-add-write (an LDS float atomic costs about 38 clocks per instruction here):
-        // the lanes of a phase touch disjoint pixels, and a lane's own entries are distinct
-        float cur[t][t];
-#pragma unroll
-        for (int a = 0; a < t; ++a)
-#pragma unroll
-          for (int b = 0; b < t; ++b) cur[a][b] = my[at[a][b]];
-#pragma unroll
-        for (int a = 0; a < t; ++a)
-#pragma unroll
-          for (int b = 0; b < t; ++b) my[at[a][b]] = cur[a][b] + d[a][b];
+      for (int b = 0; b < ov; ++b) {
+        const int mine = __builtin_bit_cast(int, d[a][M + b]);
+        const float from_left = __builtin_bit_cast(
+            float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, carry[a][b]), mine, 0x138, 0xf, 0xf, false));  // wave_shr:1
+        d[a][b] += left ? from_left : 0.0f;
+        carry[a][b] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(mine, 63));
       }
-      // the next phase adds to what this one wrote: keep the compiler from moving LDS accesses across
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    // LDS index of an entry; columns M .. t-1 are the next tile's, except behind the last tile of a row
+    const bool last_column = x0 + g.pad == (g.tw - 1) * M;
+    const int org = at.org + y0 * g.W + x0;
+    auto index = [&](int a, int b) -> int {
+      const int y = y0 + a, x = x0 + b;
+      return live && y >= 0 && y < g.H && x >= 0 && x < g.W ? org + a * g.W + b : spare;
+    };
+    // whether a column behind the last tile is inside the image (uniform)
+    auto edge = [&](int b) { return (g.tw - 1) * M - g.pad + b < g.W; };
+    auto store = [&](int a) {
+#pragma unroll
+      for (int b = 0; b < M; ++b) my[index(a, b)] = d[a][b];
+#pragma unroll
+      for (int b = M; b < t; ++b)
+        if (edge(b)) my[last_column ? index(a, b) : spare] = d[a][b];
+    };
+#pragma unroll
+    for (int a = ov; a < t; ++a) store(a);  // rows of this tile alone, and the first rows of the tile below
+    // the reads below see what other lanes stored above: keep the compiler from moving LDS accesses across
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    float up[ov][t];
+#pragma unroll
+    for (int a = 0; a < ov; ++a) {
+#pragma unroll
+      for (int b = 0; b < M; ++b) up[a][b] = my[index(a, b)];
+#pragma unroll
+      for (int b = M; b < t; ++b) up[a][b] = edge(b) ? my[last_column ? index(a, b) : spare] : 0.0f;
     }
+#pragma unroll
+    for (int a = 0; a < ov; ++a) {
+#pragma unroll
+      for (int b = 0; b < t; ++b) d[a][b] += above ? up[a][b] : 0.0f;
+      store(a);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if constexpr (!PREFETCH)
+      if (base + 64 < tau_end) load(base + 64, f, gt);
   }
+  typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
   for (int i = 0; i < n_img; ++i) {
     const float* from = my + (size_t)i * plane;
     const __amdgpu_buffer_rsrc_t dst =
         make_rsrc(din + (size_t)(n0 + i) * g.in_image_stride + (size_t)c * plane, (uint32_t)plane * 4u);
-    for (int e0 = 0; e0 < plane; e0 += 64)  // lanes past the plane's end read their wave's padding and store nothing
-      buffer_store_f32<SWCONV_AUX_OUT>(dst, lane * 4u, e0 * 4u, from[min(e0 + lane, plane - 1)]);
+    // lanes past the plane's end read the plane's last floats and store nothing; whole quads start on 16 bytes of LDS
+    if (plane % 4 == 0) {
+      for (int e0 = 0; e0 < plane; e0 += 256) {
+        const u32x4_t v = *reinterpret_cast<const u32x4_t*>(from + min(e0 + lane * 4, plane - 4));
+        __builtin_amdgcn_raw_buffer_store_b128(v, dst, lane * 16, e0 * 4, SWCONV_AUX_OUT);
+      }
+    } else {
+      for (int e0 = 0; e0 < plane; e0 += 64)
+        buffer_store_f32<SWCONV_AUX_OUT>(dst, lane * 4u, e0 * 4u, from[min(e0 + lane, plane - 1)]);
+    }
   }
 }
 
