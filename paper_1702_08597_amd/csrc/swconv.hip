@@ -150,9 +150,7 @@ struct PackedMatrix {
 // their natural order, 64 per workgroup, one package of 16-step batches per position.
 struct FusedProduct {
   int out_tile = 0;       // m of the kernel that would run: 2 (product_output_kernel) or 4 (product_output4_kernel)
-  int mode = 1;           // SWCONV_FUSE_OUTPUT: 0 never, 1 where it pays (m = 2), 2 wherever a kernel can run
-  bool wanted = true;     // m = 2: always; m = 4: only when asked for through SWCONV_FUSE_OUTPUT=2
-  bool eligible = false;  // the layer shape allows the kernel
+  bool eligible = false;  // the layer shape allows the kernel, and it pays or was asked for
   bool ready = false;     // the current weights fit its format and are on the device
   int KC = 0;             // row chunks of kFusedRows
   int B = 0;              // batches per slice and position (the longest row decides)
@@ -414,7 +412,7 @@ int launch_product_output4(const swconv_plan* pl, const LaunchTarget& to, const 
 // The forward pass is three kernels, or two where steps 2 and 3 run fused.
 bool fused_runs(const swconv_plan* pl) {
   // its output stores use 32-bit byte offsets from the output pointer
-  return pl->fz.ready && pl->fz.wanted &&
+  return pl->fz.ready &&
          (int64_t)pl->g.N * pl->g.out_image_stride * (int64_t)sizeof(float) < ((int64_t)1 << 32) - 256;
 }
 bool forward_stage_runs(const swconv_plan* pl, int stage) { return stage < 2 || !fused_runs(pl); }
@@ -507,10 +505,6 @@ bool size_fused(swconv_plan* pl, int longest_row) {
   if (units) fz.B = (fz.B + 1) / 2 * 2;
   if (fz.B > (units ? kFused4MaxBatches : kFusedMaxBatches)) return false;
   fz.n_dwords = (size_t)pl->P * fz.KC * fz.B * kFusedWaves * 128;
-  // The F(4x4,3x3) kernel runs only where asked for (SWCONV_FUSE_OUTPUT=2): with 64 + 16 accumulators per
-  // lane it holds 16 waves per CU, its vector ALU stays at about two thirds busy between the barriers of
-  // the 36 positions, and on the 56 x 56 layer it measured 217 us against 188 us for the two kernels.
-  fz.wanted = fz.out_tile == 2 || fz.mode == 2;
   return fz.n_dwords * 4 < ((size_t)1 << 32) - 4096;
 }
 
@@ -1325,14 +1319,18 @@ int swconv_plan_create(swconv_plan** out, int N, int C, int H, int W, int K, int
   g.out_image_stride = (int64_t)K * Ho * Wo;
   // steps 2 and 3 in one kernel: m = 2 (16 output accumulators per lane) and a panel of at most
   // kFusedMaxPieces 16-byte pieces per thread
-  // or F(4x4,3x3) with two C x 64 panels in LDS and whole groups of four panel rows
+  // or F(4x4,3x3) with two C x 64 panels in LDS and whole groups of four panel rows.
+  // SWCONV_FUSE_OUTPUT: 0 never, 1 where it pays (m = 2), 2 wherever a kernel can run.  The F(4x4,3x3) kernel runs only
+  // where asked for: with 64 + 16 accumulators per lane it holds 16 waves per CU, its vector ALU stays at about two
+  // thirds busy between the barriers of the 36 positions, and on the 56 x 56 layer it measured 217 us against 188 us for
+  // the two kernels.  Nor are its packages made otherwise: keeping them up to date took 5 us of every new set of
+  // values and of every new pattern on layers of 256 channels.
   const int fuse_mode = env_int("SWCONV_FUSE_OUTPUT", 1);
   pl->fz.out_tile = m;
-  pl->fz.mode = fuse_mode;
   if (m == 2)
     pl->fz.eligible = C * (kTileBlock / 4) <= kFusedMaxPieces * kFusedWaves * 64 && fuse_mode != 0;
   else
-    pl->fz.eligible = r == 3 && C % 4 == 0 && C <= kFused4MaxC && fuse_mode != 0;  // and its staging area, see below
+    pl->fz.eligible = r == 3 && C % 4 == 0 && C <= kFused4MaxC && fuse_mode == 2;  // and its staging area, see below
   try {
     if (pl->fz.eligible && m == 2) pl->fz.otiles.assign((size_t)g.Tp, OutTile{0, 0u, 0u, 0u});
     build_transform_tables(pl);
