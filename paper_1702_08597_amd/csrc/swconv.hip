@@ -640,17 +640,10 @@ void build_schedule(PackedMatrix* pm, int P, int ntb) {
     return b;
   }();
   int n_launch = wgs_max;
-  std::vector<uint8_t> second;  // second_on_cu of the ranges, asked for some 30 times each by the bisection
-  auto set_launch = [&](int n) {
-    n_launch = n;
-    ScheduleShape s = shape;
-    s.n_launch = n;
-    second.resize((size_t)std::max(n, wgs_max) + 1);
-    for (size_t r = 0; r < second.size(); ++r) second[r] = second_on_cu((int)r, s);
-  };
-  set_launch(wgs_max);
   auto range_budget = [&](int64_t budget, int r) -> int64_t {
-    return second[(size_t)r] ? std::max(floor_budget, budget * second_share / 100) : budget;
+    ScheduleShape s = shape;
+    s.n_launch = n_launch;
+    return second_on_cu(r, s) ? std::max(floor_budget, budget * second_share / 100) : budget;
   };
 
   std::vector<int64_t> cost_before(pm->slices.size() + 1, 0);
@@ -668,14 +661,13 @@ void build_schedule(PackedMatrix* pm, int P, int ntb) {
       if (begin) begin->push_back((int32_t)items->size());
       open_wg = false;
       acc = 0;
-      if (wgs <= wgs_max) budget = range_budget(base_budget, wgs);
+      budget = range_budget(base_budget, wgs);
     };
     for (int p = 0; p < P; ++p)
       for (int tb = 0; tb < ntb; ++tb) {
         int s = p * spp;
         const int s_end = s + spp;
         while (s < s_end) {
-          if (wgs > wgs_max) return wgs;  // the budget is too small
           // a new item in the current workgroup: pay the panel, then take slices while they fit
           if (open_wg && acc + panel_cost + pm->slices[s].len + slice_ovh > budget) close_wg();
           open_wg = true;
@@ -712,7 +704,7 @@ void build_schedule(PackedMatrix* pm, int P, int ntb) {
     }
     pm->n_wgs_used = cut(l, &pm->items, &pm->wg_begin);
     if (second_share == 100 || pm->n_wgs_used == n_launch) break;
-    set_launch(pm->n_wgs_used);  // the id -> range map depends on the number launched: once more with that
+    n_launch = pm->n_wgs_used;  // the id -> range map depends on the number launched: once more with that
   }
   pm->ranges.assign((size_t)pm->n_wgs_used, RangeHeader{});
   for (int b = 0; b < pm->n_wgs_used; ++b) {
