@@ -13,6 +13,7 @@
 // counts, never from atomics, and equal the ranks of the host's stable sort.
 #pragma once
 #include "swconv_kernels.hpp"
+#include "swconv_rows.hpp"
 
 namespace swconv {
 
@@ -239,10 +240,13 @@ __global__ __launch_bounds__(kPackThreads) void pack_sort_kernel(const int32_t* 
   for (int k = ((int)blockIdx.y - 1) * kPackCheckRows + (int)(threadIdx.x >> 4); k < k_end; k += kPackThreads / 16) {
     const int32_t a = rp[k], b = rp[k + 1];
     if (colidx == nullptr || !row_ok(a, b)) continue;  // the host rejects a missing array by nnz alone
-    for (int32_t q = a + (int32_t)(threadIdx.x & 15); q < b; q += 16) {
-      const int32_t c = colidx[q], before = q > a ? colidx[q - 1] : -1;
+    for_row_chunks<16>(a, b, [&](uint32_t i, uint32_t n) {
+      const uint32_t e = i + (threadIdx.x & 15);
+      if (e >= n) return;
+      const size_t q = (size_t)a + e;
+      const int32_t c = colidx[q], before = e > 0 ? colidx[q - 1] : -1;
       bad |= c <= before || c >= C;
-    }
+    });
   }
   bad = __syncthreads_or(bad);
   if (threadIdx.x == 0) bad_cols[p * ((int)gridDim.y - 1) + (int)blockIdx.y - 1] = bad;

@@ -6,6 +6,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include "swconv_rows.hpp"
 
 namespace swconv {
 
@@ -43,14 +44,15 @@ __global__ __launch_bounds__(256) void prune_update_kernel(int64_t rows, const i
   if (row == 0 && lane == 0) rowptr_out[0] = 0;
   const int32_t q0 = row < rows ? rowptr[row] : 0, q1 = row < rows ? rowptr[row + 1] : 0;
   int kept = 0;
-  for (int32_t q = q0; q < q1; q += kPruneRowLanes) {  // whole 16-lane rows stay in the loop together
+  for_row_chunks<kPruneRowLanes>(q0, q1, [&](uint32_t i, uint32_t n) {  // the 16 lanes of a row stay together
     bool drop = true;
-    if (q + lane < q1) {
-      const float wn = pruned_value(vals[q + lane], grad[q + lane], eta, lambda, eps, beta, &drop);
-      updated[q + lane] = drop ? 0.0f : wn;
+    if (i + lane < n) {
+      const size_t q = (size_t)q0 + i + lane;
+      const float wn = pruned_value(vals[q], grad[q], eta, lambda, eps, beta, &drop);
+      updated[q] = drop ? 0.0f : wn;
     }
     kept += __popc(kept_in_row(!drop));
-  }
+  });
   if (row < rows && lane == 0) rowptr_out[row + 1] = kept;
 }
 
@@ -121,13 +123,14 @@ __global__ __launch_bounds__(256) void prune_compact_kernel(int64_t rows, const 
   const int lane = threadIdx.x % kPruneRowLanes;
   const int32_t q0 = row < rows ? rowptr[row] : 0, q1 = row < rows ? rowptr[row + 1] : 0;
   int32_t dst = row < rows ? rowptr_out[row] : 0;
-  for (int32_t q = q0; q < q1; q += kPruneRowLanes) {
+  for_row_chunks<kPruneRowLanes>(q0, q1, [&](uint32_t i, uint32_t n) {
     bool drop = true;
     float wn = 0.0f;
     int32_t c = 0;
-    if (q + lane < q1) {
-      c = colidx[q + lane];
-      wn = pruned_value(vals[q + lane], grad[q + lane], eta, lambda, eps, beta, &drop);
+    if (i + lane < n) {
+      const size_t q = (size_t)q0 + i + lane;
+      c = colidx[q];
+      wn = pruned_value(vals[q], grad[q], eta, lambda, eps, beta, &drop);
     }
     const unsigned kept = kept_in_row(!drop);
     if (!drop) {
@@ -136,7 +139,7 @@ __global__ __launch_bounds__(256) void prune_compact_kernel(int64_t rows, const 
       vals_out[at] = wn;
     }
     dst += __popc(kept);
-  }
+  });
 }
 
 // Fine-tuning with the sparsity pattern fixed (Section 4.3): only the values of W_F change.  Every

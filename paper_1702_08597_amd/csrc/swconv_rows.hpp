@@ -1,0 +1,20 @@
+// How a group of lanes walks a CSR row.  Plain C++, so that the arithmetic can be run on the host over the whole
+// range of int32 row pointers.
+#pragma once
+#include <cstdint>
+
+namespace swconv {
+
+// Stored entries of row [q0, q1); a row that runs backwards has none.
+constexpr uint32_t row_entries(int32_t q0, int32_t q1) { return q1 > q0 ? (uint32_t)q1 - (uint32_t)q0 : 0u; }
+
+// f(i, n) for every chunk of kLanes entries of a row of n: lane l of the group works on entry i + l of the row while
+// i + l < n, every lane of the group comes through every chunk.  Entries count from the row's start and unsigned: the
+// position in the arrays, q0 + i + l, passes the int32 range in the last chunk of a row that ends near 2^31.
+template <uint32_t kLanes, typename F>
+constexpr void for_row_chunks(int32_t q0, int32_t q1, F&& f) {
+  const uint32_t n = row_entries(q0, q1);
+  for (uint32_t i = 0; i < n; i += kLanes) f(i, n);
+}
+
+}  // namespace swconv
