@@ -1577,13 +1577,13 @@ int swconv_prune_step(int64_t rows, const int32_t* rowptr_dev, const int32_t* co
     return SWCONV_EINVAL;
   if (!(eta >= 0.0f) || !(lambda >= 0.0f) || !(eps >= 0.0f) || !(beta >= 0.0f)) return SWCONV_EINVAL;
   const LaunchTarget to{(hipStream_t)hip_stream, nullptr, nullptr};
-  const dim3 grid((unsigned)((rows + kPruneRows - 1) / kPruneRows));
+  const dim3 grid(prune_groups(rows));
   int rc;
-  if ((rc = launch_kernel(prune_update_kernel, grid, dim3(256), 0, to, rows, rowptr_dev, vals_dev, grad_dev, eta, lambda,
+  if ((rc = launch_kernel(prune_update_kernel, grid, dim3(kPruneThreads), 0, to, rows, rowptr_dev, vals_dev, grad_dev, eta, lambda,
                           eps, beta, updated_dev, rowptr_out_dev)))
     return rc;
   if ((rc = launch_kernel(prune_scan_kernel, dim3(1), dim3(1024), 0, to, rows, rowptr_out_dev))) return rc;
-  return launch_kernel(prune_compact_kernel, grid, dim3(256), 0, to, rows, rowptr_dev, colidx_dev, vals_dev, grad_dev,
+  return launch_kernel(prune_compact_kernel, grid, dim3(kPruneThreads), 0, to, rows, rowptr_dev, colidx_dev, vals_dev, grad_dev,
                        eta, lambda, eps, beta, (const int32_t*)rowptr_out_dev, colidx_out_dev, vals_out_dev);
 }
 

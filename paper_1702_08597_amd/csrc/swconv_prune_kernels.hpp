@@ -24,8 +24,6 @@ __device__ __forceinline__ float pruned_value(float w, float g, float eta, float
 // With one thread per row every load of a wave touched 64 lines and a row was a chain of 25 loads; with the
 // serial scan below, the step took 77 us on the 13 824 rows and 354 k entries of the 256 -> 384, F(4x4,3x3) layer,
 // and takes 15 us now - three launches, of which none moves more than 7 MB.
-constexpr int kPruneRowLanes = 16;
-constexpr int kPruneRows = 256 / kPruneRowLanes;  // rows per workgroup
 
 // The lanes of the calling lane's row that say `keep`, as a 16-bit mask.
 __device__ __forceinline__ unsigned kept_in_row(bool keep) {
@@ -39,21 +37,23 @@ __global__ __launch_bounds__(256) void prune_update_kernel(int64_t rows, const i
                                                            const float* __restrict__ grad, float eta, float lambda,
                                                            float eps, float beta, float* __restrict__ updated,
                                                            int32_t* __restrict__ rowptr_out) {
-  const int64_t row = (int64_t)blockIdx.x * kPruneRows + threadIdx.x / kPruneRowLanes;
   const int lane = threadIdx.x % kPruneRowLanes;
-  if (row == 0 && lane == 0) rowptr_out[0] = 0;
-  const int32_t q0 = row < rows ? rowptr[row] : 0, q1 = row < rows ? rowptr[row + 1] : 0;
-  int kept = 0;
-  for_row_chunks<kPruneRowLanes>(q0, q1, [&](uint32_t i, uint32_t n) {  // the 16 lanes of a row stay together
-    bool drop = true;
-    if (i + lane < n) {
-      const size_t q = (size_t)q0 + i + lane;
-      const float wn = pruned_value(vals[q], grad[q], eta, lambda, eps, beta, &drop);
-      updated[q] = drop ? 0.0f : wn;
-    }
-    kept += __popc(kept_in_row(!drop));
-  });
-  if (row < rows && lane == 0) rowptr_out[row + 1] = kept;
+  if (blockIdx.x == 0 && threadIdx.x == 0) rowptr_out[0] = 0;
+  for (int64_t row0 = (int64_t)blockIdx.x * kPruneRows; row0 < rows; row0 += (int64_t)gridDim.x * kPruneRows) {
+    const int64_t row = row0 + threadIdx.x / kPruneRowLanes;
+    const int32_t q0 = row < rows ? rowptr[row] : 0, q1 = row < rows ? rowptr[row + 1] : 0;
+    int kept = 0;
+    for_row_chunks<kPruneRowLanes>(q0, q1, [&](uint32_t i, uint32_t n) {  // the 16 lanes of a row stay together
+      bool drop = true;
+      if (i + lane < n) {
+        const size_t q = (size_t)q0 + i + lane;
+        const float wn = pruned_value(vals[q], grad[q], eta, lambda, eps, beta, &drop);
+        updated[q] = drop ? 0.0f : wn;
+      }
+      kept += __popc(kept_in_row(!drop));
+    });
+    if (row < rows && lane == 0) rowptr_out[row + 1] = kept;
+  }
 }
 
 // Inclusive scan of rowptr_out[1 .. rows] in place: one workgroup of 1024 threads takes 16 x 1024 values at a
@@ -119,27 +119,29 @@ __global__ __launch_bounds__(256) void prune_compact_kernel(int64_t rows, const 
                                                             const int32_t* __restrict__ rowptr_out,
                                                             int32_t* __restrict__ colidx_out,
                                                             float* __restrict__ vals_out) {
-  const int64_t row = (int64_t)blockIdx.x * kPruneRows + threadIdx.x / kPruneRowLanes;
   const int lane = threadIdx.x % kPruneRowLanes;
-  const int32_t q0 = row < rows ? rowptr[row] : 0, q1 = row < rows ? rowptr[row + 1] : 0;
-  int32_t dst = row < rows ? rowptr_out[row] : 0;
-  for_row_chunks<kPruneRowLanes>(q0, q1, [&](uint32_t i, uint32_t n) {
-    bool drop = true;
-    float wn = 0.0f;
-    int32_t c = 0;
-    if (i + lane < n) {
-      const size_t q = (size_t)q0 + i + lane;
-      c = colidx[q];
-      wn = pruned_value(vals[q], grad[q], eta, lambda, eps, beta, &drop);
-    }
-    const unsigned kept = kept_in_row(!drop);
-    if (!drop) {
-      const int32_t at = dst + __popc(kept & ((1u << lane) - 1u));
-      colidx_out[at] = c;
-      vals_out[at] = wn;
-    }
-    dst += __popc(kept);
-  });
+  for (int64_t row0 = (int64_t)blockIdx.x * kPruneRows; row0 < rows; row0 += (int64_t)gridDim.x * kPruneRows) {
+    const int64_t row = row0 + threadIdx.x / kPruneRowLanes;
+    const int32_t q0 = row < rows ? rowptr[row] : 0, q1 = row < rows ? rowptr[row + 1] : 0;
+    int32_t dst = row < rows ? rowptr_out[row] : 0;
+    for_row_chunks<kPruneRowLanes>(q0, q1, [&](uint32_t i, uint32_t n) {
+      bool drop = true;
+      float wn = 0.0f;
+      int32_t c = 0;
+      if (i + lane < n) {
+        const size_t q = (size_t)q0 + i + lane;
+        c = colidx[q];
+        wn = pruned_value(vals[q], grad[q], eta, lambda, eps, beta, &drop);
+      }
+      const unsigned kept = kept_in_row(!drop);
+      if (!drop) {
+        const int32_t at = dst + __popc(kept & ((1u << lane) - 1u));
+        colidx_out[at] = c;
+        vals_out[at] = wn;
+      }
+      dst += __popc(kept);
+    });
+  }
 }
 
 // Fine-tuning with the sparsity pattern fixed (Section 4.3): only the values of W_F change.  Every

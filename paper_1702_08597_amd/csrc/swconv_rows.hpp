@@ -17,4 +17,16 @@ constexpr void for_row_chunks(int32_t q0, int32_t q1, F&& f) {
   for (uint32_t i = 0; i < n; i += kLanes) f(i, n);
 }
 
+// The two entry-wise kernels of the pruning step: 16 lanes to a row, kPruneRows rows per workgroup.
+constexpr int kPruneRowLanes = 16;
+constexpr int kPruneThreads = 256;
+constexpr int kPruneRows = kPruneThreads / kPruneRowLanes;
+
+// Their workgroups: one per kPruneRows rows up to 2^23 (a launch holds less than 2^32 threads); beyond 2^27 rows a
+// workgroup takes more than one turn.  Any row count that int32 row pointers can number.
+constexpr unsigned prune_groups(int64_t rows) {
+  const int64_t groups = (rows + kPruneRows - 1) / kPruneRows, most = (int64_t)1 << 23;
+  return (unsigned)(groups < most ? groups : most);
+}
+
 }  // namespace swconv

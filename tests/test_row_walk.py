@@ -1,5 +1,6 @@
 """The walk of a group of lanes over a CSR row (csrc/swconv_rows.hpp), run on the host over the range of int32 row
-pointers: every entry once, none beyond the row, and an end, also where the row ends at the last index of 31 bits."""
+pointers: every entry once, none beyond the row, and an end, also where the row ends at the last index of 31 bits.
+And the pruning step's grid: a launch the device takes (less than 2^32 threads) for every row count that is accepted."""
 import os
 import subprocess
 
@@ -11,6 +12,13 @@ PROGRAM = r"""
 #include <cstdio>
 #include <cstdlib>
 #include "swconv_rows.hpp"
+
+static_assert(swconv::prune_groups(1) == 1 && swconv::prune_groups(16) == 1 && swconv::prune_groups(17) == 2, "");
+constexpr bool grid_fits(int64_t rows) {
+  return (uint64_t)swconv::prune_groups(rows) * swconv::kPruneThreads < ((uint64_t)1 << 32) &&
+         (swconv::prune_groups(rows) == 1 << 23 || (int64_t)swconv::prune_groups(rows) * swconv::kPruneRows >= rows);
+}
+static_assert(grid_fits((1 << 27) + 1) && grid_fits(1 << 28) && grid_fits(((int64_t)1 << 31) - 257), "");
 
 int main(int, char** argv) {
   const int32_t q0 = (int32_t)atoll(argv[1]), q1 = (int32_t)atoll(argv[2]);
