@@ -276,19 +276,25 @@ int swconv_debug_copy_M(swconv_plan* plan, float* M_host);
 
 /*
  * Round trip of the re-packed sparse weights: unpacks the host-side copy of the sliced layout
- * back to per-position CSR (padding dropped, rows back in their original order).
+ * back to per-position CSR (padding dropped, rows back in their original order).  After
+ * swconv_set_weights_device or swconv_update_values that copy first comes from the device, which
+ * waits for the device.
  *   rowptr HOST P*K + 1 entries; colidx, vals HOST nnz entries each (nnz as passed to
  *   swconv_set_weights).  The result equals that call's arrays bit for bit.
- * Errors: ESTATE when no sparse weights were set.
+ * Errors: ESTATE when no sparse weights were set; ENOMEM, EHIP for a copy that failed.
  */
 int swconv_debug_export_weights(swconv_plan* plan, int32_t* rowptr, int32_t* colidx, float* vals);
 
 /*
  * Verifies the static schedule of the sparse product on the host: every (position, tile block,
- * slice) unit is assigned to exactly one persistent workgroup, no launched workgroup is idle and
- * no work item has more slices than the kernel stages descriptors for.
+ * slice) unit is assigned to exactly one persistent workgroup, no launched workgroup is idle,
+ * no work item has more slices than the kernel stages descriptors for, and the statistics of
+ * swconv_plan_weight_stats are the schedule's.  Once a backward pass has packed the transposed
+ * weights, their schedule is verified too.  The plan is only read.  After swconv_set_weights alone
+ * it needs no GPU; what was packed on the device (swconv_set_weights_device, the transposed
+ * weights) is copied from there, which waits for the device.
  * Returns SWCONV_OK, or SWCONV_EINVAL when the schedule is not a partition; ESTATE when no sparse
- * weights were set.  Needs no GPU.
+ * weights were set; ENOMEM, EHIP for a copy that failed.
  */
 int swconv_debug_check_schedule(const swconv_plan* plan);
 
@@ -310,7 +316,9 @@ int swconv_plan_set_image_strides(swconv_plan* plan, int64_t in_stride, int64_t 
 int swconv_plan_sizes(const swconv_plan* plan, int* P, int64_t* T, int* Ho, int* Wo);
 
 /*
- * Statistics of the packed weights and the work list built by swconv_set_weights:
+ * Statistics of the packed weights and the work list built by swconv_set_weights or
+ * swconv_set_weights_device.  Reads what the call kept on the host: the plan does not change, the
+ * device is not touched.
  *   nnz          stored entries as passed in
  *   padded_nnz   entries after padding to the sliced layout (what the kernel multiplies)
  *   work_items   entries of the statically scheduled work list

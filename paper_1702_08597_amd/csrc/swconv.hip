@@ -124,7 +124,8 @@ struct PackedMatrix {
   // The host copies below: what pack_matrix made, or nothing yet after a packing on the device
   // (fetch_packed_host brings them over when something reads them).
   bool host_current = false;
-  int64_t nnz = 0, padded_nnz = 0, max_item = 0;
+  int64_t nnz = 0, padded_nnz = 0, max_item = 0;  // statistics; of the forward operand, kept with every packing
+  int n_items = 0;
   std::vector<uint32_t> stream;       // 512-byte batches of (row offset, weight) pairs
   std::vector<Slice> slices;          // P * rows_padded / kSliceRows
   std::vector<int32_t> sorted_rows;   // P * rows_padded: original row of each sorted row, -1 = padding
@@ -586,14 +587,16 @@ int validate_csr(const swconv_plan* pl, const int32_t* rowptr, const int32_t* co
 }
 
 // The heaviest workgroup's padded entries.
-void count_max_item(PackedMatrix* pm) {
-  pm->max_item = 0;
-  for (int b = 0; b < pm->n_wgs_used; ++b) {
+int64_t heaviest_range(const std::vector<Slice>& slices, const std::vector<WorkItem>& items,
+                       const std::vector<int32_t>& wg_begin) {
+  int64_t most = 0;
+  for (size_t b = 0; b + 1 < wg_begin.size(); ++b) {
     int64_t steps = 0;
-    for (int i = pm->wg_begin[b]; i < pm->wg_begin[b + 1]; ++i)
-      for (int sidx = pm->items[i].slice_begin; sidx < pm->items[i].slice_end; ++sidx) steps += pm->slices[sidx].len;
-    pm->max_item = std::max(pm->max_item, steps * kSliceRows);
+    for (int i = wg_begin[b]; i < wg_begin[b + 1]; ++i)
+      for (int sidx = items[i].slice_begin; sidx < items[i].slice_end; ++sidx) steps += slices[sidx].len;
+    most = std::max(most, steps * kSliceRows);
   }
+  return most;
 }
 
 // What the cut of the schedule needs to know besides the slices.  Costs in units of the time a workgroup
@@ -713,7 +716,8 @@ void build_schedule(PackedMatrix* pm, int P, int ntb) {
     h.item_end = pm->wg_begin[b + 1];
     h.first = pm->items[h.item_begin];
   }
-  count_max_item(pm);
+  pm->n_items = (int)pm->items.size();
+  pm->max_item = heaviest_range(pm->slices, pm->items, pm->wg_begin);
 }
 
 // Dword index of the (offset, weight) pair of row q, step e of a slice whose first 512-byte batch
@@ -895,15 +899,16 @@ void free_packed(PackedMatrix* pm) {
 }
 
 // True when the schedule of `pm` is a partition of its (position, tile block, slice) units.
-bool schedule_is_partition(const PackedMatrix& pm, int P, int ntb) {
+bool is_partition(const PackedMatrix& pm, int P, int ntb, const std::vector<WorkItem>& items,
+                  const std::vector<int32_t>& wg_begin) {
   const int spp = pm.rows_padded / kSliceRows;
   std::vector<uint8_t> seen((size_t)P * ntb * spp, 0);
-  if ((int)pm.wg_begin.size() != pm.n_wgs_used + 1 || pm.wg_begin[0] != 0 ||
-      pm.wg_begin.back() != (int32_t)pm.items.size() || pm.n_wgs_used > std::max(1, pm.n_wgs))
+  if ((int)wg_begin.size() != pm.n_wgs_used + 1 || wg_begin[0] != 0 || wg_begin.back() != (int32_t)items.size() ||
+      pm.n_wgs_used > std::max(1, pm.n_wgs))
     return false;
   for (int b = 0; b < pm.n_wgs_used; ++b)
-    if (pm.wg_begin[b + 1] <= pm.wg_begin[b]) return false;  // no idle workgroup is launched
-  for (const WorkItem& w : pm.items) {
+    if (wg_begin[b + 1] <= wg_begin[b]) return false;  // no idle workgroup is launched
+  for (const WorkItem& w : items) {
     if (w.p < 0 || w.p >= P || w.tau_block < 0 || w.tau_block >= ntb) return false;
     if (w.slice_begin < w.p * spp || w.slice_end > (w.p + 1) * spp || w.slice_begin >= w.slice_end) return false;
     if (w.slice_end - w.slice_begin > pm.item_cap) return false;  // descriptors must fit their LDS area
@@ -925,8 +930,44 @@ int copy_padded_to_host(const float* dsrc, float* hdst, size_t rows, int T, int 
   return SWCONV_OK;
 }
 
-// Host copies of an operand that was packed on the device: stream, index, slices and schedule come over, the
-// sorted-row tables and the statistics follow from them.
+// The schedule of `pm` is a partition and its statistics say so; reads the operand's device copy where the host
+// has none, and changes nothing.
+int check_schedule(const PackedMatrix& pm, int P, int ntb, bool with_stats) {
+  try {
+    std::vector<Slice> slices(pm.slices);
+    std::vector<WorkItem> items(pm.items);
+    std::vector<int32_t> wg_begin(pm.wg_begin);
+    if (!pm.host_current) {
+      std::vector<RangeHeader> ranges((size_t)pm.n_wgs_used);
+      slices.resize((size_t)pm.n_slices);
+      HIP_TRY(hipDeviceSynchronize());
+      HIP_TRY(hipMemcpy(slices.data(), pm.d_slices, slices.size() * sizeof(Slice), hipMemcpyDeviceToHost));
+      HIP_TRY(hipMemcpy(ranges.data(), pm.d_ranges, ranges.size() * sizeof(RangeHeader), hipMemcpyDeviceToHost));
+      wg_begin.assign(1, 0);
+      for (const RangeHeader& h : ranges) {
+        if (h.item_begin != wg_begin.back() || h.item_end < h.item_begin) return SWCONV_EINVAL;
+        wg_begin.push_back(h.item_end);
+      }
+      if ((size_t)wg_begin.back() * sizeof(WorkItem) > pm.cap_items) return SWCONV_EINVAL;
+      items.resize((size_t)wg_begin.back());
+      HIP_TRY(hipMemcpy(items.data(), pm.d_items, items.size() * sizeof(WorkItem), hipMemcpyDeviceToHost));
+    }
+    if (!is_partition(pm, P, ntb, items, wg_begin)) return SWCONV_EINVAL;
+    if (with_stats) {
+      int64_t padded = 0;
+      for (const Slice& sl : slices) padded += (int64_t)sl.len * kSliceRows;
+      if (pm.padded_nnz != padded || pm.n_items != (int)items.size() ||
+          pm.max_item != heaviest_range(slices, items, wg_begin))
+        return SWCONV_EINVAL;
+    }
+  } catch (const std::bad_alloc&) {
+    return SWCONV_ENOMEM;
+  }
+  return SWCONV_OK;
+}
+
+// Host copies of an operand that was packed on the device: stream, index and slices come over, the sorted-row
+// tables follow from them.
 int fetch_packed_host(PackedMatrix* pm, int P) {
   if (pm->host_current) return SWCONV_OK;
   HIP_TRY(hipDeviceSynchronize());
@@ -945,9 +986,7 @@ int fetch_packed_host(PackedMatrix* pm, int P) {
     HIP_TRY(hipMemcpy(pm->items.data(), pm->d_items, pm->items.size() * sizeof(WorkItem), hipMemcpyDeviceToHost));
     pm->sorted_rows.assign((size_t)P * pm->rows_padded, -1);
     pm->sorted_len.assign((size_t)P * pm->rows_padded, 0);
-    pm->padded_nnz = 0;
     for (const Slice& sl : pm->slices) {
-      pm->padded_nnz += (int64_t)sl.len * kSliceRows;
       for (int r = 0; r < kSliceRows; ++r) {
         int32_t len = 0;
         while (len < sl.len && pm->entry_index[stream_entry(sl.batch0, r, len) / 2] >= 0) ++len;
@@ -955,7 +994,6 @@ int fetch_packed_host(PackedMatrix* pm, int P) {
         pm->sorted_len[(size_t)sl.row0 + r] = len;
       }
     }
-    count_max_item(pm);
   } catch (const std::bad_alloc&) {
     return SWCONV_ENOMEM;
   }
@@ -1622,15 +1660,17 @@ int swconv_set_weights_device(swconv_plan* pl, void* hip_stream, const int32_t* 
   fw.on_device = fw.packed = fw.index_current = fw.host_current = false;
   uint64_t batches = 2;  // the product fetches up to two batches past a slice's end
   int longest = 0;
+  fw.padded_nnz = 0;
   for (int p = 0; p < P; ++p) {
     batches += (uint64_t)rep.stats[p].batches;
+    fw.padded_nnz += ((int64_t)rep.stats[p].cost - (int64_t)shape.spp * shape.slice_ovh) * kSliceRows;
     longest = std::max(longest, rep.stats[p].longest);
   }
   PackedOut out;
   if ((rc = reserve_packed(&fw, P, pl->n_tau_blocks, batches, &out, &shape))) return rc;
   fw.nnz = rep.nnz;
   if ((rc = launch_kernel(pack_fill_kernel, dim3(1 + kPackSpareWgs + P * ((shape.spp + 15) / 16)), dim3(kPackThreads), 0,
-                          to, rowptr_dev, colidx_dev, vals_dev, K, fw.rows_padded, fw.tables, out, shape)))
+                          to, rowptr_dev, colidx_dev, vals_dev, K, fw.rows_padded, fw.tables, out, shape, pl->h_report)))
     return rc;
   FusedProduct& fz = pl->fz;
   const bool fused = size_fused(pl, longest);
@@ -1644,6 +1684,8 @@ int swconv_set_weights_device(swconv_plan* pl, void* hip_stream, const int32_t* 
       return rc;
   }
   HIP_TRY(hipStreamSynchronize(st));  // the caller's arrays are his again, and a pass on any stream finds the weights
+  fw.n_items = rep.items;
+  fw.max_item = (int64_t)rep.heaviest_steps * kSliceRows;
   fw.packed = fw.on_device = fw.index_current = true;
   fz.ready = fused;
   return SWCONV_OK;
@@ -1701,9 +1743,9 @@ int swconv_debug_export_weights(swconv_plan* pl, int32_t* rowptr, int32_t* colid
 int swconv_debug_check_schedule(const swconv_plan* pl) {
   if (!pl) return SWCONV_EINVAL;
   if (!pl->fw.packed) return SWCONV_ESTATE;
-  const int rc = fetch_packed_host(const_cast<PackedMatrix*>(&pl->fw), pl->P);  // a cache of what the device holds
-  if (rc) return rc;
-  return schedule_is_partition(pl->fw, pl->P, pl->n_tau_blocks) ? SWCONV_OK : SWCONV_EINVAL;
+  int rc = check_schedule(pl->fw, pl->P, pl->n_tau_blocks, true);
+  if (!rc && pl->bt_current) rc = check_schedule(pl->bt, pl->P, pl->n_tau_blocks, false);
+  return rc;
 }
 
 int swconv_plan_sizes(const swconv_plan* pl, int* P, int64_t* T, int* Ho, int* Wo) {
@@ -1719,11 +1761,9 @@ int swconv_plan_weight_stats(const swconv_plan* pl, int64_t* nnz, int64_t* padde
                              int64_t* max_item) {
   if (!pl) return SWCONV_EINVAL;
   if (!pl->fw.packed) return SWCONV_ESTATE;
-  const int rc = fetch_packed_host(const_cast<PackedMatrix*>(&pl->fw), pl->P);  // a cache of what the device holds
-  if (rc) return rc;
   if (nnz) *nnz = pl->fw.nnz;
   if (padded_nnz) *padded_nnz = pl->fw.padded_nnz;
-  if (work_items) *work_items = (int)pl->fw.items.size();
+  if (work_items) *work_items = pl->fw.n_items;
   if (max_item) *max_item = pl->fw.max_item;
   return SWCONV_OK;
 }

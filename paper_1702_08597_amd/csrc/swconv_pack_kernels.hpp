@@ -27,9 +27,8 @@ constexpr int kPackSpareWgs = 16;      // workgroups of launch 2 that clear the 
 // What launch 1 says about a position.
 struct PositionStats {
   int32_t batches;  // 512-byte stream batches of its slices
-  int32_t cost;     // schedule cost of its slices
+  int32_t cost;     // schedule cost of its slices: their lengths and slice_ovh for each
   int32_t longest;  // stored entries of its longest row
-  int32_t steps;    // sum of its slices' lengths
 };
 
 // Launch 1's tables of one operand, per position: rows in sorted order, and exclusive prefix sums over
@@ -172,10 +171,9 @@ __device__ inline void sort_position(int p, int rows, int rows_padded, const uin
   int steps = 0;
   if (s < spp) steps = (length(sorted[s * kSliceRows]) + kStepGroup - 1) / kStepGroup * kStepGroup;
   const int batches = (steps + kBatchSteps - 1) / kBatchSteps;
-  int all_batches, all_cost, all_steps;
+  int all_batches, all_cost;
   const int b0 = block_scan(batches, part, &all_batches);
   const int c0 = block_scan(s < spp ? steps + slice_ovh : 0, part, &all_cost);
-  (void)block_scan(steps, part, &all_steps);
   if (s < spp) {
     t.batch_pre[(size_t)p * (spp + 1) + s] = b0;
     t.cost_pre[(size_t)p * (spp + 1) + s] = c0;
@@ -183,16 +181,20 @@ __device__ inline void sort_position(int p, int rows, int rows_padded, const uin
   if (s == 0) {
     t.batch_pre[(size_t)p * (spp + 1) + spp] = all_batches;
     t.cost_pre[(size_t)p * (spp + 1) + spp] = all_cost;
-    t.stats[p] = PositionStats{all_batches, all_cost, length(sorted[0]), all_steps};
+    t.stats[p] = PositionStats{all_batches, all_cost, length(sorted[0])};
   }
 }
 
-// What the host reads between the two launches of a forward operand (pinned host memory, written by launch 1).
+// What the host reads of the packing of a forward operand (pinned host memory).
 struct PackReport {
+  // after launch 1
   int32_t nnz;
   int32_t bad;  // rowptr[0] != 0
   PositionStats stats[kMaxPositions];
   int32_t bad_rows[kMaxPositions];  // a row of the position leaves [0, nnz], is too long or runs backwards
+  // after launch 2, of the schedule
+  int32_t items;
+  unsigned long long heaviest_steps;  // slice steps of the workgroup with the most of them
 };
 
 // Launch 1 of a forward operand.  Grid (P, 1 + ceil(K / kPackCheckRows)): workgroup (p, 0) sorts position p,
@@ -262,20 +264,28 @@ __device__ __forceinline__ int position_batch0(const PositionStats* stats, int p
 
 // The schedule: one workgroup, one range per thread.  The net budgets, scaled to the whole work, say where the
 // ranges begin; the cuts are located in the prefix sums, made strictly ascending - no range is empty - and
-// written as work items.
-__device__ inline void cut_schedule(const ScheduleShape& s, const PackTables& t, WorkItem* items, RangeHeader* ranges) {
+// written as work items.  `report` (or null) gets the schedule's two statistics.
+__device__ inline void cut_schedule(const ScheduleShape& s, const PackTables& t, WorkItem* items, RangeHeader* ranges,
+                                    PackReport* report) {
   __shared__ double block_cost[kMaxPositions + 1];
+  __shared__ int64_t work_before[kMaxPositions + 1];  // the same without the panels
+  __shared__ unsigned long long heaviest;
   __shared__ int32_t cut[kPackMaxWgs + 1];
   __shared__ double dpart[17];
   __shared__ int32_t ipart[17];
   const int r = threadIdx.x;
   if (r == 0) {
     double sum = 0;
+    int64_t work = 0;
     for (int p = 0; p < s.P; ++p) {
       block_cost[p] = sum;
+      work_before[p] = work;
       sum += (double)s.ntb * ((double)s.panel_cost + t.stats[p].cost);
+      work += (int64_t)s.ntb * t.stats[p].cost;
     }
     block_cost[s.P] = sum;
+    work_before[s.P] = work;
+    heaviest = 0;
   }
   __syncthreads();
   const double total = block_cost[s.P];
@@ -321,6 +331,23 @@ __device__ inline void cut_schedule(const ScheduleShape& s, const PackTables& t,
       if (i == 0) h.first = w;
     });
     ranges[r] = h;
+  }
+  if (report == nullptr) return;
+  auto work_in_front = [&](int u) -> int64_t {  // slice costs of the units before u
+    const int pt = u / s.spp, p = pt / s.ntb;
+    if (p >= s.P) return work_before[s.P];
+    const int32_t* c = t.cost_pre + (size_t)p * (s.spp + 1);
+    return work_before[p] + (int64_t)(pt - p * s.ntb) * c[s.spp] + c[u - pt * s.spp];
+  };
+  if (r < n) {
+    const int64_t steps =
+        work_in_front(cut[r + 1]) - work_in_front(cut[r]) - (int64_t)s.slice_ovh * (cut[r + 1] - cut[r]);
+    atomicMax(&heaviest, (unsigned long long)steps);
+  }
+  __syncthreads();
+  if (r == 0) {
+    report->items = all;
+    report->heaviest_steps = heaviest;
   }
 }
 
@@ -380,9 +407,10 @@ __device__ __forceinline__ void fill_spare(const PackTables& t, int P, const Pac
 __global__ __launch_bounds__(kPackThreads) void pack_fill_kernel(const int32_t* __restrict__ rowptr,
                                                                  const int32_t* __restrict__ colidx,
                                                                  const float* __restrict__ vals, int K, int rows_padded,
-                                                                 PackTables t, PackedOut out, ScheduleShape shape) {
+                                                                 PackTables t, PackedOut out, ScheduleShape shape,
+                                                                 PackReport* __restrict__ report) {
   if (blockIdx.x == 0) {
-    if (shape.n_launch > 0) cut_schedule(shape, t, out.items, out.ranges);
+    if (shape.n_launch > 0) cut_schedule(shape, t, out.items, out.ranges, report);
     return;
   }
   if (blockIdx.x <= kPackSpareWgs) return fill_spare(t, shape.P, out, (int)blockIdx.x - 1);
@@ -453,7 +481,7 @@ __global__ __launch_bounds__(kPackThreads) void transpose_fill_kernel(const uint
                                                                       const int32_t* __restrict__ rank_of, PackTables t,
                                                                       PackedOut out, ScheduleShape shape) {
   if (blockIdx.x == 0) {
-    if (shape.n_launch > 0) cut_schedule(shape, t, out.items, out.ranges);
+    if (shape.n_launch > 0) cut_schedule(shape, t, out.items, out.ranges, nullptr);
     return;
   }
   if (blockIdx.x <= kPackSpareWgs) return fill_spare(t, shape.P, out, (int)blockIdx.x - 1);

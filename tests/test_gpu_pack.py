@@ -74,9 +74,36 @@ def test_device_packing_equals_host_packing(N, C, K, m, r, H, W, density, skew):
         g = torch.randn((N, K, Ho, Wo), generator=torch.Generator(device="cuda").manual_seed(8), device="cuda")
         for p, q in zip(*(passes(pl, x, g, K, len(va), K <= 638) for pl in plans)):
             np.testing.assert_array_equal(p.view(np.uint32), q.view(np.uint32))
+        for pl in plans:
+            sw.swconv_debug_check_schedule(pl)  # now the transpose's too
     finally:
         for pl in plans:
             sw.swconv_plan_destroy(pl)
+
+
+def test_queries_of_a_device_packed_plan_read_the_plan_and_nothing_else():
+    K, C = 96, 64
+    rp, ci, va = synth.bernoulli_weights(36, K, C, 0.1, 9)
+    plan = sw.swconv_plan_create(2, C, 13, 13, K, 4, 3, 1)
+    x, out = torch.randn((2, C, 13, 13), device="cuda"), torch.zeros((2, K, 13, 13), device="cuda")
+    try:
+        assert set_device(plan, rp, ci, va) == sw.SWCONV_OK
+        sw.swconv_forward(plan, torch.cuda.current_stream().cuda_stream, x.data_ptr(), out.data_ptr())
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):  # a call that waited for the device here would end the capture
+            sw.swconv_forward(plan, torch.cuda.current_stream().cuda_stream, x.data_ptr(), out.data_ptr())
+            during = sw.swconv_plan_weight_stats(plan)
+        sw.swconv_debug_check_schedule(plan)  # the statistics against the schedule that the device holds
+        assert during == sw.swconv_plan_weight_stats(plan)
+        assert during["nnz"] == len(va) and during["work_items"] > 0 and during["max_item"] > 0
+        want = out.clone()
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+    finally:
+        sw.swconv_plan_destroy(plan)
 
 
 def test_malformed_device_arrays_are_refused_and_the_weights_stay():
