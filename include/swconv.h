@@ -180,7 +180,8 @@ int swconv_forward_dense(swconv_plan* plan, void* hip_stream, const float* in_de
  *   dvals_dev  DEVICE, nnz floats or NULL: dL/dW_F at the stored entries, in the order of the CSR
  *              arrays given to swconv_set_weights
  * The first call after the weights were set also packs the transposed weights (on the device; it allocates, and
- * after swconv_set_weights it blocks for the schedule, which the host cuts).
+ * after swconv_set_weights it blocks for the schedule, which the host cuts): that call cannot be captured into a
+ * HIP graph (EHIP; the capture goes on without it).
  * Overwrites the plan's workspaces (swconv_debug_copy_V / _M then see backward data).
  * Errors: EINVAL, ESTATE (no weights), EUNSUPPORTED (K > 638: the panels of dL/dZ do not fit LDS; or
  * N*C*(H+m)*(W+m) >= 2^31), ENOMEM, EHIP.
@@ -213,7 +214,7 @@ int swconv_prune_step(int64_t rows, const int32_t* rowptr_dev, const int32_t* co
  * are validated and re-packed by kernels on `hip_stream`, nothing but the sizes crosses to the host (layers of
  * more than 4096 output channels go through host copies).  Blocks the host until the packed weights are on the
  * device; the caller's arrays are not used after that.  Errors as for swconv_set_weights (a malformed CSR leaves
- * the previous weights in place), EHIP for a failed copy or launch.
+ * the previous weights in place), EHIP for a failed copy or launch, and while `hip_stream` is being captured.
  */
 int swconv_set_weights_device(swconv_plan* plan, void* hip_stream, const int32_t* rowptr_dev,
                               const int32_t* colidx_dev, const float* vals_dev);

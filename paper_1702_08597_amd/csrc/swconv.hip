@@ -1025,6 +1025,15 @@ int ensure_index(PackedMatrix* pm) {
 
 // ---- packing on the device (swconv_pack_kernels.hpp) ----
 
+// Whether work enqueued on `st` now would be recorded into a graph instead of run (or another stream's capture
+// forbids it).  A packing notes on the host what the device holds when it returns, so it cannot be recorded.
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
 // Tables of the two launches, one allocation per operand.
 int reserve_tables(PackedMatrix* pm, int P) {
   const size_t rows = (size_t)P * pm->rows_padded, pre = (size_t)P * (pm->rows_padded / kSliceRows + 1);
@@ -1089,6 +1098,7 @@ int schedule_on_host(PackedMatrix* pm, int P, int ntb) {
 int prepare_backward(swconv_plan* pl, hipStream_t st) {
   if (!pl->bt_supported) return SWCONV_EUNSUPPORTED;
   if (pl->bt_current && pl->bt.on_device && pl->dD) return SWCONV_OK;
+  if (capturing(st)) return SWCONV_EHIP;
   const int P = pl->P, K = pl->g.K, C = pl->g.C;
   PackedMatrix& bt = pl->bt;
   int rc;
@@ -1631,8 +1641,9 @@ int swconv_set_weights_device(swconv_plan* pl, void* hip_stream, const int32_t* 
   PackedMatrix& fw = pl->fw;
   const int P = pl->P, K = pl->g.K, C = pl->g.C;
   size_grid(&fw, (int64_t)P * pl->n_tau_blocks * (fw.rows_padded / kSliceRows));
-  if (!packs_on_device(fw)) return set_weights_through_host(pl, hip_stream, rowptr_dev, colidx_dev, vals_dev);
   const hipStream_t st = (hipStream_t)hip_stream;
+  if (capturing(st)) return SWCONV_EHIP;
+  if (!packs_on_device(fw)) return set_weights_through_host(pl, hip_stream, rowptr_dev, colidx_dev, vals_dev);
   const LaunchTarget to{st, nullptr, nullptr};
   int rc;
   if ((rc = ensure_workspace(pl)) || (rc = reserve_tables(&fw, P))) return rc;

@@ -106,6 +106,37 @@ def test_queries_of_a_device_packed_plan_read_the_plan_and_nothing_else():
         sw.swconv_plan_destroy(plan)
 
 
+def test_packing_is_refused_under_capture():
+    """A packing that a capture only records has not happened, whatever the plan then notes: the first backward pass
+    on new weights and the new weights themselves are refused there, and the eager passes after it are right."""
+    N, K, C = 2, 96, 64
+    patterns = [synth.bernoulli_weights(36, K, C, d, 11) for d in (0.2, 0.1)]
+    x = torch.from_numpy(synth.activations(N, C, 13, 13, 12)).cuda()
+    g = torch.randn((N, K, 13, 13), generator=torch.Generator(device="cuda").manual_seed(13), device="cuda")
+    plan, fresh = (sw.swconv_plan_create(N, C, 13, 13, K, 4, 3, 1) for _ in range(2))
+    try:
+        assert set_device(plan, *patterns[0]) == sw.SWCONV_OK
+        passes(plan, x, g, K, len(patterns[0][2]), True)  # every buffer there is, larger than the second pattern needs
+        assert set_device(plan, *patterns[1]) == sw.SWCONV_OK
+        arrays = [torch.from_numpy(a).cuda() for a in patterns[1]]
+        out, din, dv = torch.empty_like(g), torch.empty_like(x), torch.empty(len(patterns[1][2]), device="cuda")
+        ptr = lambda t: ctypes.c_void_p(t.data_ptr())
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            st = torch.cuda.current_stream().cuda_stream
+            sw.swconv_forward(plan, st, x.data_ptr(), out.data_ptr())
+            status = [sw.lib().swconv_backward(plan, ctypes.c_void_p(st), ptr(x), ptr(g), ptr(din), ptr(dv)),
+                      sw.lib().swconv_set_weights_device(plan, ctypes.c_void_p(st), *(ptr(a) for a in arrays))]
+        assert status == [sw.SWCONV_EHIP, sw.SWCONV_EHIP]
+        sw.swconv_set_weights(fresh, *patterns[1])
+        for a, b in zip(*(passes(p, x, g, K, len(patterns[1][2]), True) for p in (plan, fresh))):
+            np.testing.assert_array_equal(a.view(np.uint32), b.view(np.uint32))
+    finally:
+        for p in (plan, fresh):
+            sw.swconv_plan_destroy(p)
+
+
 def test_malformed_device_arrays_are_refused_and_the_weights_stay():
     K, C = 130, 40
     rp, ci, va = synth.bernoulli_weights(36, K, C, 0.3, 3)
