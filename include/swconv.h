@@ -213,7 +213,12 @@ int swconv_prune_step(int64_t rows, const int32_t* rowptr_dev, const int32_t* co
  * swconv_set_weights for CSR arrays that live on the device (e.g. the output of swconv_prune_step): the arrays
  * are validated and re-packed by kernels on `hip_stream`, nothing but the sizes crosses to the host (layers of
  * more than 4096 output channels go through host copies).  Blocks the host until the packed weights are on the
- * device; the caller's arrays are not used after that.  Errors as for swconv_set_weights (a malformed CSR leaves
+ * device; the caller's arrays are not used after that.  The schedule of the sparse product is the
+ * one that swconv_set_weights makes (some hundred us of host work) for a plan's first pattern and
+ * for one that replaces a pattern of at least 512 passes; else, as in a loop that prunes, the device
+ * makes one that is ready at once and less even (passes 0 to 2 % longer, 5 % measured at most).  The
+ * results are the same.  To settle on the pattern that a pruning loop ended with, set it on a
+ * new plan, or again after those passes.  Errors as for swconv_set_weights (a malformed CSR leaves
  * the previous weights in place), EHIP for a failed copy or launch, and while `hip_stream` is being captured.
  */
 int swconv_set_weights_device(swconv_plan* plan, void* hip_stream, const int32_t* rowptr_dev,

@@ -197,7 +197,9 @@ struct swconv_plan {
   size_t partial_floats = 0;
   // swconv_update_values: the device streams hold newer values than the host copies
   bool host_values_stale = false;
-  bool host_pattern = true;  // the weights came through swconv_set_weights
+  // Passes since the weights were set, and whether the pattern is expected to stay for many (see pattern_stays)
+  int64_t passes = 0;
+  bool stays = true;
   // packing on the device: what launch 1 reports (pinned host memory), and the transpose's bit matrix
   PackReport* h_report = nullptr;
   int32_t* h_bad_cols = nullptr;
@@ -624,8 +626,8 @@ ScheduleShape schedule_shape(const PackedMatrix& pm, int P, int ntb) {
 // a new panel costs one panel load.  The smallest feasible cost per
 // range is found by bisection.  A range touches at most a few panels, consecutive ranges share
 // panels and weights (and, through xcd_contiguous_id, an XCD's L2), and the split adapts by
-// itself to positions of very different density.  (The cut that the device makes for patterns that live
-// there, cut_schedule, has a closed form instead of the search: up to 5 % less even, and 300 us faster.)
+// itself to positions of very different density.  (The cut that the device makes for patterns that a pruning
+// loop replaces again, cut_schedule, has a closed form instead of the search; pattern_stays weighs the two.)
 void build_schedule(PackedMatrix* pm, int P, int ntb) {
   const int spp = pm->rows_padded / kSliceRows;
   const ScheduleShape shape = schedule_shape(*pm, P, ntb);
@@ -1134,8 +1136,7 @@ int prepare_backward(swconv_plan* pl, hipStream_t st) {
                           pl->fw.d_slices, fw_spp, K, C, bt.rows_padded, words, bt.tables, shape.slice_ovh,
                           (uint2*)pl->d_bits, rank_table(bt, P))))
     return rc;
-  if (pl->host_pattern) {
-    // a pattern set from the host stays for many passes: its transpose gets the more even cut of the host as well
+  if (pl->stays) {
     HIP_TRY(hipStreamSynchronize(st));
     if ((rc = schedule_on_host(&bt, P, pl->n_tau_blocks))) return rc;
     shape.n_launch = 0;  // nothing left to cut for launch 2
@@ -1269,7 +1270,21 @@ void weights_replaced(swconv_plan* pl) {
   pl->fz.ready = false;
   pl->m_current = false;
   pl->ran_forward = false;
+  pl->passes = 0;
 }
+
+// Whether a pattern that comes from the device is expected to stay, which decides who cuts its schedules.  The host's
+// search is the more even one, the closed form that the device cuts is there sooner.  Per operand, set call and passes
+// timed with either (us, closed form and search):
+//   256 -> 384, N = 32, 13 x 13, 10 %:  set  63 and  491; forward 30.3 and 29.9; forward + backward  80.6 and  79.7
+//   384 -> 256, N = 64, 13 x 13, 30 %:  set  54 and  353; forward 80.8 and 78.9; forward + backward 230.3 and 227.9
+//   192 -> 320, N = 8, 28 x 28, 15 %:                     forward 28.5 and 28.2; forward + backward  72.5 and  69.0
+//   256 -> 256, N = 32, 56 x 56, 10 %:  set  60 and 1398; forward 250.9 and 250.5; forward + backward 604.8 and 603.9
+// so the search pays from some hundred passes on.  Nothing says how long the new pattern will stay: as long as the one
+// that it replaces, is the guess, and a plan's first one is taken to stay, as in a program that loads its weights and
+// serves.  (The replays of a graph are not counted.)
+constexpr int64_t kPassesToStay = 512;
+bool pattern_stays(const swconv_plan* pl) { return !pl->fw.packed || pl->passes >= kPassesToStay; }
 
 // swconv_set_weights_device for sizes beyond the packing kernels: through host copies of the arrays.
 int set_weights_through_host(swconv_plan* pl, void* hip_stream, const int32_t* rowptr_dev, const int32_t* colidx_dev,
@@ -1457,7 +1472,7 @@ int swconv_set_weights(swconv_plan* pl, const int32_t* rowptr, const int32_t* co
   if (rc) return rc;
   size_grid(&pl->fw, (int64_t)pl->P * pl->n_tau_blocks * (pl->fw.rows_padded / kSliceRows));
   weights_replaced(pl);
-  pl->host_pattern = true;
+  pl->stays = true;
   try {
     pack_matrix(&pl->fw, pl->P, pl->n_tau_blocks, rowptr, colidx, vals);
     pack_fused(pl, rowptr, colidx, vals);
@@ -1483,6 +1498,7 @@ int swconv_forward(swconv_plan* pl, void* hip_stream, const float* in_dev, float
   }
   pl->ran_forward = true;
   pl->m_current = !fused_runs(pl);
+  ++pl->passes;
   return SWCONV_OK;
 }
 
@@ -1506,6 +1522,7 @@ int swconv_forward_noalloc(swconv_plan* pl, void* hip_stream, const float* in_de
   // the plan's own workspaces hold nothing of this pass
   pl->ran_forward = false;
   pl->m_current = false;
+  ++pl->passes;
   return SWCONV_OK;
 }
 
@@ -1560,6 +1577,7 @@ int swconv_backward(swconv_plan* pl, void* hip_stream, const float* in_dev, cons
       return rc;
   pl->ran_forward = false;  // the V workspace no longer holds I_F
   pl->ran_backward = true;
+  ++pl->passes;
   return SWCONV_OK;
 }
 
@@ -1666,8 +1684,8 @@ int swconv_set_weights_device(swconv_plan* pl, void* hip_stream, const int32_t* 
   if (bad || (rep.nnz > 0 && (!colidx_dev || !vals_dev))) return SWCONV_EINVAL;
 
   HIP_TRY(hipDeviceSynchronize());  // a pass still in flight may read the buffers that are overwritten below
+  pl->stays = pattern_stays(pl);
   weights_replaced(pl);
-  pl->host_pattern = false;
   fw.on_device = fw.packed = fw.index_current = fw.host_current = false;
   uint64_t batches = 2;  // the product fetches up to two batches past a slice's end
   int longest = 0;
@@ -1680,6 +1698,10 @@ int swconv_set_weights_device(swconv_plan* pl, void* hip_stream, const int32_t* 
   PackedOut out;
   if ((rc = reserve_packed(&fw, P, pl->n_tau_blocks, batches, &out, &shape))) return rc;
   fw.nnz = rep.nnz;
+  if (pl->stays) {
+    if ((rc = schedule_on_host(&fw, P, pl->n_tau_blocks))) return rc;
+    shape.n_launch = 0;  // nothing left to cut for launch 2
+  }
   if ((rc = launch_kernel(pack_fill_kernel, dim3(1 + kPackSpareWgs + P * ((shape.spp + 15) / 16)), dim3(kPackThreads), 0,
                           to, rowptr_dev, colidx_dev, vals_dev, K, fw.rows_padded, fw.tables, out, shape, pl->h_report)))
     return rc;
@@ -1695,8 +1717,10 @@ int swconv_set_weights_device(swconv_plan* pl, void* hip_stream, const int32_t* 
       return rc;
   }
   HIP_TRY(hipStreamSynchronize(st));  // the caller's arrays are his again, and a pass on any stream finds the weights
-  fw.n_items = rep.items;
-  fw.max_item = (int64_t)rep.heaviest_steps * kSliceRows;
+  if (!pl->stays) {
+    fw.n_items = rep.items;
+    fw.max_item = (int64_t)rep.heaviest_steps * kSliceRows;
+  }
   fw.packed = fw.on_device = fw.index_current = true;
   fz.ready = fused;
   return SWCONV_OK;

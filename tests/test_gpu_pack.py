@@ -81,6 +81,32 @@ def test_device_packing_equals_host_packing(N, C, K, m, r, H, W, density, skew):
             sw.swconv_plan_destroy(pl)
 
 
+def test_schedule_of_a_pattern_that_stays_is_the_hosts():
+    """A plan's first pattern, and one that replaces a pattern of 512 passes, get the schedule that swconv_set_weights
+    makes; the patterns of a loop get the device's.  The results are the same."""
+    N, K, C = 32, 96, 64
+    rp, ci, va = synth.bernoulli_weights(36, K, C, 0.1, 21)
+    x = torch.from_numpy(synth.activations(N, C, 13, 13, 22)).cuda()
+    g = torch.randn((N, K, 13, 13), generator=torch.Generator(device="cuda").manual_seed(23), device="cuda")
+    host, dev = (sw.swconv_plan_create(N, C, 13, 13, K, 4, 3, 1) for _ in range(2))
+    try:
+        sw.swconv_set_weights(host, rp, ci, va)
+        want, stats = passes(host, x, g, K, len(va), True), sw.swconv_plan_weight_stats(host)
+        for turn, even in enumerate((True, False, True)):
+            assert set_device(dev, rp, ci, va) == sw.SWCONV_OK
+            assert (sw.swconv_plan_weight_stats(dev) == stats) == even, turn
+            for a, b in zip(passes(dev, x, g, K, len(va), True), want):
+                np.testing.assert_array_equal(a.view(np.uint32), b.view(np.uint32))
+            sw.swconv_debug_check_schedule(dev)
+            if turn == 1:
+                out = torch.empty_like(g)
+                for _ in range(510):  # with the forward and the backward pass above: 512
+                    sw.swconv_forward(dev, 0, x.data_ptr(), out.data_ptr())
+    finally:
+        for p in (host, dev):
+            sw.swconv_plan_destroy(p)
+
+
 def test_queries_of_a_device_packed_plan_read_the_plan_and_nothing_else():
     K, C = 96, 64
     rp, ci, va = synth.bernoulli_weights(36, K, C, 0.1, 9)
