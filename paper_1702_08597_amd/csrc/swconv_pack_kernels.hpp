@@ -194,7 +194,7 @@ struct PackReport {
   int32_t bad_rows[kMaxPositions];  // a row of the position leaves [0, nnz], is too long or runs backwards
   // after launch 2, of the schedule
   int32_t items;
-  unsigned long long heaviest_steps;  // slice steps of the workgroup with the most of them
+  uint32_t heaviest_steps;  // slice steps of the workgroup with the most of them
 };
 
 // Launch 1 of a forward operand.  Grid (P, 1 + ceil(K / kPackCheckRows)): workgroup (p, 0) sorts position p,
@@ -268,23 +268,24 @@ __device__ __forceinline__ int position_batch0(const PositionStats* stats, int p
 __device__ inline void cut_schedule(const ScheduleShape& s, const PackTables& t, WorkItem* items, RangeHeader* ranges,
                                     PackReport* report) {
   __shared__ double block_cost[kMaxPositions + 1];
-  __shared__ int64_t work_before[kMaxPositions + 1];  // the same without the panels
-  __shared__ unsigned long long heaviest;
+  __shared__ uint32_t work_before[kMaxPositions];  // the same without the panels, modulo 2^32
+  __shared__ uint32_t steps_at[kPackMaxWgs + 1];   // slice steps in front of a cut, modulo 2^32
+  __shared__ uint32_t heaviest;
   __shared__ int32_t cut[kPackMaxWgs + 1];
   __shared__ double dpart[17];
   __shared__ int32_t ipart[17];
   const int r = threadIdx.x;
   if (r == 0) {
     double sum = 0;
-    int64_t work = 0;
+    uint32_t work = 0;
     for (int p = 0; p < s.P; ++p) {
       block_cost[p] = sum;
       work_before[p] = work;
       sum += (double)s.ntb * ((double)s.panel_cost + t.stats[p].cost);
-      work += (int64_t)s.ntb * t.stats[p].cost;
+      work += (uint32_t)s.ntb * (uint32_t)t.stats[p].cost;
     }
     block_cost[s.P] = sum;
-    work_before[s.P] = work;
+    steps_at[s.n_launch] = work - (uint32_t)s.slice_ovh * (uint32_t)(s.P * s.ntb * s.spp);
     heaviest = 0;
   }
   __syncthreads();
@@ -315,13 +316,31 @@ __device__ inline void cut_schedule(const ScheduleShape& s, const PackTables& t,
   }
   v = min(v, units - n) + r;
   __syncthreads();
-  if (r < n) cut[r] = v;
+  if (r < n) {
+    cut[r] = v;
+    if (report != nullptr) {
+      // a range holds less than 2^32 steps (V and M have 32-bit sizes), so differences may wrap on the way
+      const int pt = v / s.spp, p = pt / s.ntb;
+      const int32_t* c = t.cost_pre + (size_t)p * (s.spp + 1);
+      steps_at[r] = work_before[p] + (uint32_t)(pt - p * s.ntb) * (uint32_t)c[s.spp] + (uint32_t)c[v - pt * s.spp] -
+                    (uint32_t)s.slice_ovh * (uint32_t)v;
+    }
+  }
   if (r == 0) cut[n] = units;
   __syncthreads();
   int count = 0;
   if (r < n) count = for_items(cut[r], cut[r + 1], s, [](int, const WorkItem&) {});
+  if (report != nullptr) {
+    uint32_t steps = r < n ? steps_at[r + 1] - steps_at[r] : 0u;
+    for (int d = 32; d > 0; d >>= 1) steps = max(steps, (uint32_t)__shfl_xor((int)steps, d));
+    if ((r & 63) == 0) atomicMax(&heaviest, steps);
+  }
   int all;
-  const int first = block_scan(count, ipart, &all);
+  const int first = block_scan(count, ipart, &all);  // its barriers also stand between the maximum and its reader
+  if (r == 0 && report != nullptr) {  // now, not at the end: the way to the host's memory overlaps with the items
+    report->items = all;
+    report->heaviest_steps = heaviest;
+  }
   if (r < n) {
     RangeHeader h{};
     h.item_begin = first;
@@ -331,23 +350,6 @@ __device__ inline void cut_schedule(const ScheduleShape& s, const PackTables& t,
       if (i == 0) h.first = w;
     });
     ranges[r] = h;
-  }
-  if (report == nullptr) return;
-  auto work_in_front = [&](int u) -> int64_t {  // slice costs of the units before u
-    const int pt = u / s.spp, p = pt / s.ntb;
-    if (p >= s.P) return work_before[s.P];
-    const int32_t* c = t.cost_pre + (size_t)p * (s.spp + 1);
-    return work_before[p] + (int64_t)(pt - p * s.ntb) * c[s.spp] + c[u - pt * s.spp];
-  };
-  if (r < n) {
-    const int64_t steps =
-        work_in_front(cut[r + 1]) - work_in_front(cut[r]) - (int64_t)s.slice_ovh * (cut[r + 1] - cut[r]);
-    atomicMax(&heaviest, (unsigned long long)steps);
-  }
-  __syncthreads();
-  if (r == 0) {
-    report->items = all;
-    report->heaviest_steps = heaviest;
   }
 }
 
