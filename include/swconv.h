@@ -243,9 +243,11 @@ int swconv_update_values(swconv_plan* plan, void* hip_stream, const float* vals_
  *             0 for kernels the call does not run (din_dev or dvals_dev NULL).  Sampled products
  *             and transposed sparse product are one kernel where both run: the third and the fifth
  *             value are its parts, by their shares of its inner loop.  Where the image
- *             planes fit LDS (3x3 filters) the last two run as one kernel that keeps no patch
+ *             planes fit LDS (3x3 filters, and F(4x4,5x5) where it pays: images of at most 64 tiles, or
+ *             enough images and channels) the last two run as one kernel that keeps no patch
  *             buffer: the sixth value is its time and the seventh is 0 (the environment
- *             variable SWCONV_FUSE_INPUT_GRAD=0, read by swconv_plan_create, keeps two kernels).
+ *             variable SWCONV_FUSE_INPUT_GRAD, read by swconv_plan_create: 0 keeps two kernels, 2 takes
+ *             the one wherever it can run).
  * Blocks the host.  Errors as for swconv_backward; EINVAL for iters < 1.
  */
 int swconv_profile_backward(swconv_plan* plan, void* hip_stream, const float* in_dev, const float* dout_dev,

@@ -1313,6 +1313,22 @@ int set_weights_through_host(swconv_plan* pl, void* hip_stream, const int32_t* r
   }
 }
 
+// Whether dL/dI_F -> dL/dI runs as one kernel (input_grad_kernel) where that kernel can run.  With 3x3 filters: always.
+// F(4x4,5x5): a pass over 64 tiles is a chain of about 5 us there (64 values per lane, fetched and transformed), the
+// workgroups' passes come one after the other, and an image has as many as its tiles need; the patch and gather kernels
+// take 8 us at least and grow with the whole.  Images of one pass always gain (1 of 13 x 13, 16 channels: 5.9 us
+// against 8.4; 64 of 27 x 27: 8.2 against 14.9), the others where enough workgroups share the chain: 8 of 40 x 40 with
+// 48 channels (2 passes, 96 workgroups) 12.1 against 14.5, 16 of 64 x 64 with 64 (4, 256) 24.3 against 36.1, 32 of
+// 80 x 80 with 32 (7, 256) 45.6 against 68.0; but 2 of 40 x 40 with 64 (2, 32) 11.7 against 9.3, 16 of 64 x 64 with 32
+// (4, 128) 22.1 against 20.6, 8 of 72 x 72 with 64 (6, 128) 32.8 against 25.6, 1 of 96 x 96 with 16 (9, 4) 46.6 against 9.4.
+bool one_input_grad_kernel_pays(const swconv_plan* pl, int images_per_group) {
+  if (pl->r == 3) return true;
+  const Geometry& g = pl->g;
+  const int64_t passes = ((int64_t)images_per_group * g.tpi + 63) / 64;
+  const int64_t wgs = (int64_t)((g.N + images_per_group - 1) / images_per_group) * ((g.C + 3) / 4);
+  return passes == 1 || wgs >= std::min<int64_t>(48 * passes, 192);
+}
+
 }  // namespace
 
 extern "C" {
@@ -1408,8 +1424,10 @@ int swconv_plan_create(swconv_plan** out, int N, int C, int H, int W, int K, int
     const int G = (int)std::min<int64_t>(N, std::max<int64_t>(1, 64 / g.tpi));
     const int64_t wave_floats = ((int64_t)G * H * W + 63) / 64 * 64 + 64;
     // (the kernel sums over direct neighbours: F(2x2,5x5), whose patches reach two tiles back, takes the two kernels)
-    if (4 * wave_floats * (int64_t)sizeof(float) <= kMaxLdsBytes && (t - 1) / m == 1 &&
-        env_int("SWCONV_FUSE_INPUT_GRAD", 1) != 0) {
+    // SWCONV_FUSE_INPUT_GRAD: 0 never, 1 where it pays, 2 wherever the kernel can run.
+    const int fuse = env_int("SWCONV_FUSE_INPUT_GRAD", 1);
+    if (4 * wave_floats * (int64_t)sizeof(float) <= kMaxLdsBytes && (t - 1) / m == 1 && fuse != 0 &&
+        (fuse == 2 || one_input_grad_kernel_pays(pl, G))) {
       try {
         GradTile none;
         none.org = 0;

@@ -43,3 +43,36 @@ def test_patches_meet(H, W, m, r, pad):
         np.testing.assert_array_equal(got, ref)
     else:
         assert np.abs(got - ref).max() <= 1e-4 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("H,W,pad", [(33, 31, 2), (17, 52, 0), (40, 4, 2), (54, 35, 2), (56, 56, 2), (64, 64, 0)])
+@pytest.mark.parametrize("fuse", ["0", "2"])
+def test_patches_of_5x5_filters_in_one_kernel_and_in_two(H, W, pad, fuse, monkeypatch):
+    """F(4x4,5x5) by either route, whichever of them the plan would take: images of several passes of 64 tiles."""
+    monkeypatch.setenv("SWCONV_FUSE_INPUT_GRAD", fuse)
+    test_patches_meet(H, W, 4, 5, pad)
+
+
+@pytest.mark.parametrize("N,C,H,W,one", [
+    (1, 5, 27, 27, True),        # one pass of 64 tiles
+    (1, 128, 32, 32, True),      # 64 tiles: still one
+    (1, 128, 33, 32, False),     # two passes, 32 workgroups
+    (24, 16, 40, 40, True),      # two passes, 96 workgroups
+    (19, 17, 40, 40, False),     # ... and 95
+    (48, 16, 64, 64, True),      # four passes, 192
+    (16, 44, 64, 64, False),     # ... and 176
+    (3, 256, 88, 88, True),      # eight passes: 192 are enough
+    (1, 16, 96, 96, False),
+])
+def test_route_of_5x5_filters(N, C, H, W, one):
+    K, P = 4, 64
+    rp, ci, va = synth.bernoulli_weights(P, K, C, 0.05, 1)
+    x, out = torch.zeros((N, C, H, W), device="cuda"), torch.zeros((N, K, H, W), device="cuda")
+    din = torch.empty_like(x)
+    plan = sw.swconv_plan_create(N, C, H, W, K, 4, 5, 2)
+    try:
+        sw.swconv_set_weights(plan, rp, ci, va)
+        ms = sw.swconv_profile_backward(plan, 0, x.data_ptr(), out.data_ptr(), din.data_ptr(), 0, 1)
+        assert ms[5] > 0 and (ms[6] == 0) == one
+    finally:
+        sw.swconv_plan_destroy(plan)
