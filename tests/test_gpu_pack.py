@@ -107,6 +107,37 @@ def test_schedule_of_a_pattern_that_stays_is_the_hosts():
             sw.swconv_plan_destroy(p)
 
 
+@pytest.mark.parametrize("from_device", [False, True])
+def test_backward_buffers_are_sized_by_the_batches_there_are(from_device):
+    """The partial sums of dL/dW_F: one float per tile block and pair of the transpose's batches, of which a slice of
+    four rows has ceil(longest / 16).  No more of them are held than there are."""
+    N, C, H, W, K, m, r = 256, 48, 27, 27, 128, 4, 5
+    rp, ci, va = synth.bernoulli_weights(64, K, C, 0.094, 31)
+    batches = 0
+    for p in range(64):
+        lens = np.bincount(ci[rp[p * K]:rp[(p + 1) * K]], minlength=C)
+        batches += int(np.ceil(np.sort(lens)[::-1][::4] / 16).sum())
+    x, out = torch.zeros((N, C, H, W), device="cuda"), torch.zeros((N, K, H, W), device="cuda")
+    din, dv = torch.empty_like(x), torch.empty(len(va), device="cuda")
+    plan = sw.swconv_plan_create(N, C, H, W, K, m, r, 2)
+    try:
+        if from_device:
+            assert set_device(plan, rp, ci, va) == sw.SWCONV_OK
+        else:
+            sw.swconv_set_weights(plan, rp, ci, va)
+        sw.swconv_forward(plan, 0, x.data_ptr(), out.data_ptr())
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        sw.swconv_backward(plan, 0, 0, out.data_ptr(), din.data_ptr(), dv.data_ptr())
+        torch.cuda.synchronize()
+        held = before - torch.cuda.mem_get_info()[0]
+        tiles = -(-sw.swconv_plan_sizes(plan)[1] // 128) * 128
+        gradient, partial = 64 * C * tiles * 4, tiles // 64 * (batches + 2) * 64 * 4
+        assert gradient + partial <= held <= gradient + partial + (24 << 20)  # and the packed weights, tables, rounding
+    finally:
+        sw.swconv_plan_destroy(plan)
+
+
 def test_queries_of_a_device_packed_plan_read_the_plan_and_nothing_else():
     K, C = 96, 64
     rp, ci, va = synth.bernoulli_weights(36, K, C, 0.1, 9)
