@@ -516,6 +516,8 @@ __device__ __forceinline__ void product_dots_group(const float* panel, uint32_t 
 // a <- in the lanes of the banks (groups of four lanes of a row of 16) of LO: a + a of the lane given by
 // CTRL_LO; in the others: b + b of the lane given by CTRL_HI.  The bank masks of the two instructions do the
 // selecting.  Two wait states lie between the vector-ALU write of a register and its read through DPP.
+// The sums are written before the b are read: they must not share registers, not even where the compiler knows both
+// to hold the same value (the zeros of steps that are not run), hence the early clobbers.
 #define SWCONV_FOLD(LO_CTRL, LO, HI_CTRL, HI)                                  \
   asm("s_nop 1\n"                                                              \
       "v_add_f32_dpp %0, %0, %0 " LO_CTRL " row_mask:0xf bank_mask:" LO "\n"    \
@@ -526,7 +528,7 @@ __device__ __forceinline__ void product_dots_group(const float* panel, uint32_t 
       "v_add_f32_dpp %1, %5, %5 " HI_CTRL " row_mask:0xf bank_mask:" HI "\n"    \
       "v_add_f32_dpp %2, %6, %6 " HI_CTRL " row_mask:0xf bank_mask:" HI "\n"    \
       "v_add_f32_dpp %3, %7, %7 " HI_CTRL " row_mask:0xf bank_mask:" HI           \
-      : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3)                                 \
+      : "+&v"(a0), "+&v"(a1), "+&v"(a2), "+&v"(a3)                             \
       : "v"(b0), "v"(b1), "v"(b2), "v"(b3))
 __device__ __forceinline__ void fold_bit3(float& a0, float& a1, float& a2, float& a3, float b0, float b1, float b2, float b3) {
   SWCONV_FOLD("row_ror:8", "0x3", "row_ror:8", "0xc");  // partner lane ^ 8
