@@ -35,7 +35,7 @@ def stage_models(cfg, nnz):
     ]
 
 
-def backward_stage_models(cfg, nnz, padded_entries):
+def backward_stage_models(cfg, nnz):
     """Algorithmic bytes and flops of the seven backward kernels for one launch (launch order)."""
     N, C, H, W, K = cfg["N"], cfg["C"], cfg["H"], cfg["W"], cfg["K"]
     P, T, Ho, Wo = cfg["P"], cfg["T"], cfg["Ho"], cfg["Wo"]
@@ -43,9 +43,10 @@ def backward_stage_models(cfg, nnz, padded_entries):
     return [
         dict(bytes=4 * (N * K * Ho * Wo + P * K * T), flops=0),                      # dZ = A dO A^T
         dict(bytes=4 * (N * C * H * W + P * C * T), flops=0),                        # I_F again
-        dict(bytes=4 * (P * C * T + P * K * T) + 8 * nnz + 4 * ntb * nnz, flops=2 * nnz * T),  # sampled products
+        # dL/dW_F per tile block and dI_F = W_F^T dZ: dZ, I_F and the stream in, dI_F and the partial sums out
+        dict(bytes=4 * (P * K * T + 2 * P * C * T) + 8 * nnz + 4 * ntb * nnz, flops=4 * nnz * T),
         dict(bytes=4 * ntb * nnz + 8 * nnz, flops=0),                                # reduction to CSR order
-        dict(bytes=4 * (P * K * T + P * C * T) + 8 * nnz, flops=2 * nnz * T),        # dI_F = W_F^T dZ
+        dict(bytes=4 * (P * K * T + P * C * T) + 8 * nnz, flops=2 * nnz * T),        # dI_F = W_F^T dZ alone
         dict(bytes=8 * P * C * T, flops=0),                                          # patches = B dI_F B^T
         dict(bytes=4 * (P * C * T + N * C * H * W), flops=0),                        # gather
     ]
@@ -83,15 +84,15 @@ def run_backward(args, sw, synth, torch, np, plan, cfg, name, x, xd, rp, ci, va,
                    "path": "backward (dL/dI and dL/dW_F)"},
     }
     stage_ms = sw.swconv_profile_backward(*a, args.steps)
-    st = sw.swconv_plan_weight_stats(plan)
-    models = backward_stage_models(cfg, nnz, st["padded_nnz"])
+    models = backward_stage_models(cfg, nnz)
     names = list(sw.BACKWARD_STAGES)
     if stage_ms[6] == 0 and stage_ms[5] > 0:
         # Eq. 6's last two lines ran as one kernel (image planes in LDS, no patch buffer)
         names[5] = "input_grad_kernel"
         models[5] = dict(bytes=4 * (cfg["P"] * cfg["C"] * cfg["T"] + cfg["N"] * cfg["C"] * cfg["H"] * cfg["W"]), flops=0)
     stages = []
-    ran = [i for i in range(len(names)) if stage_ms[i] > 0]     # kernels of the pass that were launched
+    # kernels of the pass that were launched: the transposed product by itself only where the third did not make it
+    ran = [i for i in range(len(names)) if stage_ms[i] > 0 and not (i == 4 and stage_ms[2] > 0)]
     names, models, stage_ms = [names[i] for i in ran], [models[i] for i in ran], stage_ms[ran]
     for nm, ms, mdl in zip(names, stage_ms.tolist(), models):
         gbs = mdl["bytes"] / (ms * 1e-3) / 1e9 if ms > 0 else 0.0

@@ -238,11 +238,13 @@ int swconv_update_values(swconv_plan* plan, void* hip_stream, const float* vals_
 /*
  * Measurement helper for the backward pass: `iters` passes with every kernel launched with its own
  * pair of HIP events (as swconv_profile_forward); mean milliseconds per kernel, in launch order:
- *   stage_ms  HOST, 7 floats: dL/dZ transform, input transform (I_F again), sampled products,
- *             reduction to CSR order, transposed sparse product, patch transform, gather;
- *             0 for kernels the call does not run (din_dev or dvals_dev NULL).  Sampled products
- *             and transposed sparse product are one kernel where both run: the third and the fifth
- *             value are its parts, by their shares of its inner loop.  Where the image
+ *   stage_ms  HOST, 7 floats: dL/dZ transform, input transform (I_F again), both sparse products
+ *             (the partial sums of dL/dW_F and dL/dI_F, one kernel), reduction to CSR order,
+ *             transposed sparse product (dL/dI_F alone), patch transform, gather;
+ *             0 for kernels the call does not run (din_dev or dvals_dev NULL).  With dvals_dev the
+ *             third value is the whole time of the kernel that makes both, and the fifth, which is
+ *             then no part of a pass, what the transposed product takes by itself: it is launched
+ *             `iters` times more behind the passes.  Where the image
  *             planes fit LDS (3x3 filters, and F(4x4,5x5) where it pays: images of at most 64 tiles, or
  *             enough images and channels) the last two run as one kernel that keeps no patch
  *             buffer: the sixth value is its time and the seventh is 0 (the environment

@@ -142,13 +142,14 @@ def swconv_set_weights_device(plan, stream, rowptr_dev, colidx_dev, vals_dev):
            "swconv_set_weights_device")
 
 
-BACKWARD_STAGES = ("output_grad_transform_kernel", "input_transform_kernel", "spmm_kernel<sampled>",
+BACKWARD_STAGES = ("output_grad_transform_kernel", "input_transform_kernel", "spmm_kernel<both gradients>",
                    "weight_grad_reduce_kernel", "spmm_kernel<transposed>", "input_grad_patch_kernel",
                    "input_grad_gather_kernel")
 
 
 def swconv_profile_backward(plan, stream, in_dev_ptr, dout_dev_ptr, din_dev_ptr, dvals_dev_ptr, iters):
-    """-> numpy float32[7]: mean milliseconds of each backward kernel, in launch order (BACKWARD_STAGES)."""
+    """-> numpy float32[7]: mean milliseconds of each backward kernel, in launch order (BACKWARD_STAGES).
+    With dvals the fifth is no part of a pass: the third made its result, and it was launched by itself."""
     ms = np.zeros(7, dtype=np.float32)
     _check(lib().swconv_profile_backward(plan, _vp(stream), _vp(in_dev_ptr), _vp(dout_dev_ptr),
                                          _vp(din_dev_ptr or None), _vp(dvals_dev_ptr or None), int(iters),
