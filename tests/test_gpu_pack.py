@@ -138,6 +138,64 @@ def test_backward_buffers_are_sized_by_the_batches_there_are(from_device):
         sw.swconv_plan_destroy(plan)
 
 
+@pytest.mark.parametrize("N,C,H,W,K,m,r,density,fuse", [
+    (3, 48, 27, 27, 128, 2, 5, 0.094, None),  # the fused product + output transform: one batch per slice, two at most
+    (2, 40, 13, 13, 70, 2, 3, 0.3, None),     # ... rows of up to 32 entries, a broken chunk of 64 rows
+    (2, 64, 13, 13, 96, 4, 3, 0.1, "2"),      # the fused kernel of F(4x4,3x3), where asked for: whole units of two batches
+    (1, 200, 13, 13, 65, 4, 3, 0.55, "2"),    # ... rows of more than 96 entries, one row in the last chunk
+    (2, 64, 13, 13, 96, 4, 3, 0.1, None),
+])
+def test_values_updated_in_a_device_packed_plan(N, C, H, W, K, m, r, density, fuse, monkeypatch):
+    """swconv_update_values goes through the index that the packing wrote with every packed copy - stream, transpose and,
+    where steps 2 and 3 run fused, packages: the same bits as a plan given the new values by the host."""
+    if fuse:
+        monkeypatch.setenv("SWCONV_FUSE_OUTPUT", fuse)
+    P = (m + r - 1) ** 2
+    rp, ci, va = synth.bernoulli_weights(P, K, C, density, 41)
+    new = np.random.default_rng(42).standard_normal(len(va)).astype(np.float32)
+    x = torch.from_numpy(synth.activations(N, C, H, W, 43)).cuda()
+    plans = [sw.swconv_plan_create(N, C, H, W, K, m, r, r // 2) for _ in range(2)]
+    try:
+        Ho, Wo = sw.swconv_plan_sizes(plans[0])[2:]
+        g = torch.randn((N, K, Ho, Wo), generator=torch.Generator(device="cuda").manual_seed(44), device="cuda")
+        sw.swconv_set_weights(plans[0], rp, ci, new)
+        assert set_device(plans[1], rp, ci, va) == sw.SWCONV_OK
+        out, fused = torch.empty_like(g), fuse is not None or m == 2
+        ms = sw.swconv_profile_forward(plans[1], 0, x.data_ptr(), out.data_ptr(), 1)
+        assert (ms[2] == 0) == fused  # the route that the case is here for
+        for before_backward in (True, False):  # the transpose is packed by the first backward pass
+            values = torch.from_numpy(new if not before_backward else -new).cuda()
+            sw.swconv_update_values(plans[1], 0, values.data_ptr())
+            got = passes(plans[1], x, g, K, len(va), True)
+        for a, b in zip(got, passes(plans[0], x, g, K, len(va), True)):
+            np.testing.assert_array_equal(a.view(np.uint32), b.view(np.uint32))
+    finally:
+        for pl in plans:
+            sw.swconv_plan_destroy(pl)
+
+
+@pytest.mark.parametrize("N,C,H,W,K,density", [(32, 64, 27, 27, 96, 0.1), (24, 96, 30, 26, 100, 0.05)])
+def test_device_cut_of_a_transpose_with_two_workgroups_per_cu(N, C, H, W, K, density):
+    """More than 32 units per compute unit: both operands run two workgroups on each, by the device's cut."""
+    rp, ci, va = synth.bernoulli_weights(36, K, C, density, 51)
+    x = torch.from_numpy(synth.activations(N, C, H, W, 52)).cuda()
+    g = torch.randn((N, K, H, W), generator=torch.Generator(device="cuda").manual_seed(53), device="cuda")
+    plans = [sw.swconv_plan_create(N, C, H, W, K, 4, 3, 1) for _ in range(2)]
+    try:
+        tiles = sw.swconv_plan_sizes(plans[0])[1]
+        assert 36 * -(-tiles // 64) * (C // 4) >= 32 * torch.cuda.get_device_properties(0).multi_processor_count
+        sw.swconv_set_weights(plans[0], rp, ci, va)
+        for _ in range(2):  # the second one is a loop's: the device cuts
+            assert set_device(plans[1], rp, ci, va) == sw.SWCONV_OK
+        for a, b in zip(*(passes(pl, x, g, K, len(va), True) for pl in plans)):
+            np.testing.assert_array_equal(a.view(np.uint32), b.view(np.uint32))
+        for pl in plans:
+            sw.swconv_debug_check_schedule(pl)
+    finally:
+        for pl in plans:
+            sw.swconv_plan_destroy(pl)
+
+
 def test_queries_of_a_device_packed_plan_read_the_plan_and_nothing_else():
     K, C = 96, 64
     rp, ci, va = synth.bernoulli_weights(36, K, C, 0.1, 9)
