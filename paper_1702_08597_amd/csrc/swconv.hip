@@ -1110,7 +1110,19 @@ int prepare_backward(swconv_plan* pl, hipStream_t st) {
   bt.n_wgs = std::min(bt.n_wgs, kPackMaxWgs);
   const int spp = bt.rows_padded / kSliceRows;
   ScheduleShape shape = schedule_shape(bt, P, pl->n_tau_blocks);
+  PackedOut out{};
   if ((rc = reserve_tables(&bt, P))) return rc;
+  if (!pl->stays) {
+    // The transpose's batches.  A pattern that stays is worth the wait for their number (below).  For the others there
+    // is a bound that needs no wait: the rows are sorted, so the slices' lengths sum to at most one longest row plus a
+    // quarter of the entries per position, and rounding adds less than a batch each.  (Stream, partial sums and their
+    // reduction are sized by it: 6608 batches for 4761 on the 256 -> 256, 56 x 56 layer at 10 %, 1919 for 857 on the
+    // F(4x4,5x5) group of 48 -> 128 channels at 9.4 %.)  Allocated before launch 1: beside a running kernel the five
+    // allocations of a plan's first backward pass took 200 us longer.
+    const uint64_t batches =
+        ((uint64_t)P * K + (uint64_t)pl->fw.nnz / kSliceRows) / kBatchSteps + (uint64_t)P * (spp + 1) + 2;
+    if ((rc = reserve_packed(&bt, P, pl->n_tau_blocks, batches, &out, &shape))) return rc;
+  }
   const int words = (K + 31) / 32 | 1;  // odd: the rows of the bit matrix start on different LDS banks
   if ((rc = reserve((void**)&pl->d_bits, &pl->cap_bits, (size_t)P * C * words * sizeof(uint2)))) return rc;
   if (!pl->dD) {
@@ -1132,23 +1144,14 @@ int prepare_backward(swconv_plan* pl, hipStream_t st) {
                           pl->fw.d_slices, fw_spp, K, C, bt.rows_padded, words, bt.tables, shape.slice_ovh,
                           (uint2*)pl->d_bits, rank_table(bt, P))))
     return rc;
-  // The transpose's batches.  A pattern that stays is worth the wait for their number.  For the others there is a bound
-  // that needs no wait: the rows are sorted, so the slices' lengths sum to at most one longest row plus a quarter of
-  // the entries per position, and rounding adds less than a batch each.  (Stream, partial sums and their reduction are
-  // sized by it: 6608 batches for 4761 on the 256 -> 256, 56 x 56 layer at 10 %, 1919 for 857 on the F(4x4,5x5) group
-  // of 48 -> 128 channels at 9.4 %.)
-  uint64_t batches = ((uint64_t)P * K + (uint64_t)pl->fw.nnz / kSliceRows) / kBatchSteps + (uint64_t)P * (spp + 1) + 2;
   if (pl->stays) {
     PositionStats stats[kMaxPositions];
     HIP_TRY(hipStreamSynchronize(st));
     HIP_TRY(hipMemcpy(stats, bt.tables.stats, (size_t)P * sizeof(PositionStats), hipMemcpyDeviceToHost));
-    batches = 2;  // the product fetches up to two batches past a slice's end
+    uint64_t batches = 2;  // the product fetches up to two batches past a slice's end
     for (int p = 0; p < P; ++p) batches += (uint64_t)stats[p].batches;
-  }
-  PackedOut out;
-  if ((rc = reserve_packed(&bt, P, pl->n_tau_blocks, batches, &out, &shape))) return rc;
-  if (pl->stays) {
-    if ((rc = schedule_on_host(&bt, P, pl->n_tau_blocks))) return rc;
+    if ((rc = reserve_packed(&bt, P, pl->n_tau_blocks, batches, &out, &shape)) || (rc = schedule_on_host(&bt, P, pl->n_tau_blocks)))
+      return rc;
     shape.n_launch = 0;  // nothing left to cut for launch 2
   }
   const int chunks = (std::max(spp, fw_spp) + 15) / 16;
