@@ -38,8 +38,8 @@ int env_int(const char* name, int dflt) {
   return (end && *end == 0) ? (int)v : dflt;
 }
 
-// Host threads for the re-packing of the weights (a plan's set_weights is a few milliseconds of
-// host work on a pruned AlexNet layer; a training loop that prunes every step calls it every step).
+// Host threads for the packing of weights that come from the host (1 to 2 ms on a pruned AlexNet layer; a training
+// loop that prunes packs on the device).
 int host_threads() {
   const int hw = (int)std::thread::hardware_concurrency();
   return std::max(1, std::min(16, env_int("SWCONV_HOST_THREADS", hw > 0 ? hw : 1)));
@@ -348,7 +348,10 @@ int launch_spmm_t(const swconv_plan* pl, const PackedMatrix& pm, const LaunchTar
 }
 
 // The registers that hold a panel on its way are sized in steps: a piece that no panel needs costs its register
-// and an instruction per item (48 channels, 12 waves: one piece of seven).
+// and an instruction per item.  12 waves take 48 channels to a piece.  Up to 96 channels two pieces, the 5x5 layers'
+// case; beyond, six up to 288 and seven up to 319.  Three to five pieces between them measured 3 to 7 % faster for the
+// product and the joint pass at 112 to 160 channels (128 channels, N = 16, 28 x 28: 9.0 against 9.5 us and 11.9 against
+// 12.6) and the same at 192 and 224 (13.0 and 22.3, 15.4 and 23.2 us either way); they are not built.
 template <bool DOTS>
 int launch_spmm(const swconv_plan* pl, const PackedMatrix& pm, const LaunchTarget& to, const SpmmArgs& a) {
   const int threads = pm.waves * 64, pieces = (pm.cols * (kTileBlock / 4) + threads - 1) / threads;

@@ -189,7 +189,8 @@ __global__ __launch_bounds__(256) void input_grad_gather_kernel(const float* __r
 // workgroups fit a CU's LDS); 64 of 13 x 13, 384 channels: 21.1 -> 16.2 us; F(4x4,5x5), 32 of 27 x 27, 48 channels, whose
 // indices of whole patches overflowed the registers: 10.4 us against 16.5 for the patch and gather kernels.
 // PREFETCH: groups of more than one pass ask for the next pass's values before they work on the present one's, at
-// t^2 registers that groups of one pass spend on more waves per SIMD.
+// t^2 registers that groups of one pass spend on more waves per SIMD.  F(4x4,5x5), with 64 values per lane, spills 53
+// to 56 scalar registers into vector lanes (nothing goes to memory).
 // Block = 4 waves = 4 channels of the same image group.
 struct GradTile {
   int32_t org;  // float offset of pixel (0, 0) of the tile's image inside the wave's LDS area

@@ -199,7 +199,7 @@ __device__ __forceinline__ void stage_quads(const BlockImage* bi, int slots, flo
       src[i] = make_rsrc(pt.src, (uint32_t)(span[i] & ~3) * 4u);
       dst[i] = my + pt.off;
       max_span = max(max_span, span[i]);
-      if (span[i] & 3)  // lanes past the span read 0 into the run's padding
+      if (span[i] & 3)  // one to three lanes of this are used
         tail[i] = buffer_load_f32(make_rsrc(pt.src, (uint32_t)span[i] * 4u), lane * 4u, (uint32_t)(span[i] & ~3) * 4u);
     }
     for (int e0 = 0; e0 < max_span; e0 += 256 * EL) {
@@ -571,6 +571,10 @@ __device__ __forceinline__ float product_dots_batch(const float* panel, uint32_t
 // of V (dL/dZ) over that tile block; `partial_stride` entries per block.  An entry's dot product does not
 // depend on which of the two tensors is the panel, so dL/dZ, the weights and every LDS value are read once for
 // both gradients: 177 vector-ALU instructions per 16 steps against 80 + 125 in two passes, half the LDS reads.
+// What is left in the way with DOTS at 12 waves and their 80 registers: <12,6> keeps two of its registers in scratch (12
+// bytes a lane, <12,7> 16), whose reload in front of the next panel's requests waits for all vector memory, and the
+// panel's offset sits in a vector register, so that each request runs in a readfirstlane loop.  The variants of 16
+// waves spill nothing, the product alone has neither.
 template <int NWAVES, int PIECES, bool DOTS>
 __global__ __launch_bounds__(NWAVES * 64, NWAVES == 12 ? 6 : 4) void spmm_kernel(
     const float* __restrict__ V, float* __restrict__ Mbuf, const uint32_t* __restrict__ stream, uint32_t stream_bytes,

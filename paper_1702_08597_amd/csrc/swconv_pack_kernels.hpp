@@ -4,8 +4,9 @@
 // A training loop that prunes changes the pattern in every step, so this is on its path.  On the host the
 // same work (copy to the host, sort, fill, cut the schedule, copy back) took 2.6 ms for the forward operand
 // of the 256 -> 384, N = 32, F(4x4,3x3) layer at 10 % density and 2.2 ms for its transpose; here the two take
-// 64 us (the waits for the host's part included) and about 45 us.  Everything is a gather or scatter of a few
-// MB, so what bounds it is the number of dependent launches: two per operand.
+// 63 us (20 + 12 us of kernels, the rest are the two waits for the host's part) and 35 us (23 + 12).  Everything is a
+// gather or scatter of a few MB; what bounds it are the two sorts, one workgroup per position, so that 16 to 64 of 256
+// CUs work, on a chain of LDS reads.
 //   launch 1  one workgroup per position sorts the rows by length and takes the prefix sums over its slices
 //             (forward: the column indices are validated by further workgroups of the same launch)
 //   launch 2  slice descriptors and stream, one wave per slice; one more workgroup cuts the schedule
@@ -143,8 +144,9 @@ __device__ __forceinline__ T block_scan(T x, T* part, T* total) {
 
 // Sorts one position's rows by length, longest first, equal ones in their order, and takes the prefix sums
 // over its slices.  key[i] = (length + 1) << 12 | (4095 - i), zero from `rows` to the next multiple of four: a
-// row's rank is the number of larger keys, counted by reading all keys as broadcasts, four at a time (384
-// rows: 96 reads per thread, about 2 us; no serial step).  sorted: rows_padded words of LDS.
+// row's rank is the number of larger keys, counted by reading all keys as broadcasts, four at a time.  That is most
+// of the kernel: 384 rows are 96 reads per thread, each waited for, and take 15 of pack_sort_kernel's 20 us (without
+// the loop 5.1 us; without the column checks or with the report in device memory still 20).  sorted: rows_padded words.
 __device__ inline void sort_position(int p, int rows, int rows_padded, const uint32_t* key, uint32_t* sorted,
                                      const PackTables& t, int slice_ovh) {
   __shared__ int32_t part[17];

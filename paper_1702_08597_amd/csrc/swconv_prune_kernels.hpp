@@ -23,7 +23,7 @@ __device__ __forceinline__ float pruned_value(float w, float g, float eta, float
 // wave then read whole lines of the CSR arrays, and a row of 25 entries is two rounds of independent loads.
 // With one thread per row every load of a wave touched 64 lines and a row was a chain of 25 loads; with the
 // serial scan below, the step took 77 us on the 13 824 rows and 354 k entries of the 256 -> 384, F(4x4,3x3) layer,
-// and takes 15 us now - three launches, of which none moves more than 7 MB.
+// and takes 16 us now (4.5 + 7.2 + 4.3) - three launches, of which none moves more than 7 MB.
 
 // The lanes of the calling lane's row that say `keep`, as a 16-bit mask.
 __device__ __forceinline__ unsigned kept_in_row(bool keep) {
@@ -59,7 +59,7 @@ __global__ __launch_bounds__(256) void prune_update_kernel(int64_t rows, const i
 // Inclusive scan of rowptr_out[1 .. rows] in place: one workgroup of 1024 threads takes 16 x 1024 values at a
 // time, all loads in flight at once, scans every run of 64 in its wave and the 256 runs' totals in LDS.  (A
 // device-wide scan would need storage between its launches that the entry point does not have; 13 824 rows are one
-// round here and take 5 us, of which 3 are the launch.)
+// round here and take 7 us, of which 3 are the launch.)
 __global__ __launch_bounds__(1024) void prune_scan_kernel(int64_t rows, int32_t* __restrict__ rowptr_out) {
   constexpr int U = 16, W = 1024 / 64;
   __shared__ int32_t run[U * W];  // run j * W + w: the values of wave w in the j-th 1024

@@ -23,7 +23,7 @@ constexpr int kPruneThreads = 256;
 constexpr int kPruneRows = kPruneThreads / kPruneRowLanes;
 
 // Their workgroups: one per kPruneRows rows up to 2^23 (a launch holds less than 2^32 threads); beyond 2^27 rows a
-// workgroup takes more than one turn.  Any row count that int32 row pointers can number.
+// workgroup takes more than one turn (as one launch of more threads, its grid wrapped).  Any row count that int32 row pointers can number.
 constexpr unsigned prune_groups(int64_t rows) {
   const int64_t groups = (rows + kPruneRows - 1) / kPruneRows, most = (int64_t)1 << 23;
   return (unsigned)(groups < most ? groups : most);
