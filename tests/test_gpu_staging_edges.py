@@ -1,4 +1,4 @@
-"""The rows of a tile block go to LDS in dwords where a part of an image is short and in quads where it is longer than 192
+"""The rows of a tile block go to LDS in dwords where a part of an image is short and in quads where it is longer than 256
 floats, one to many images to a block; a span's last one to three floats travel by themselves.  Widths and heights
 around that line and around whole quads and whole rounds of loads; odd planes put the channels on every alignment.
 Tolerance: dL/dZ and the gradients against the oracle, the contract of the other backward tests, 1e-4 of the largest
@@ -25,6 +25,12 @@ def test_staged_rows_of_every_length(H, W, m):
     G = rng.standard_normal((N, K, H, W)).astype(np.float32)
     # the forward pass inside leaves I_F, the gradient of the weights reads it, dL/dI reads the staged dL/dO
     check(N, C, H, W, K, m, 1, x, rp, ci, va, G)
+
+
+@pytest.mark.parametrize("H,W", [(16, 16), (17, 15), (16, 17), (8, 32), (8, 33)])
+@pytest.mark.parametrize("m", [2, 4])
+def test_staged_rows_around_the_line(H, W, m):
+    test_staged_rows_of_every_length(H, W, m)
 
 
 @pytest.mark.parametrize("H,W,m,r", [(13, 13, 4, 3), (56, 56, 4, 3), (30, 22, 2, 3), (24, 28, 4, 5), (32, 32, 2, 5)])
