@@ -444,6 +444,7 @@ int launch_stage(const swconv_plan* pl, const LaunchTarget& to, int stage, const
 void build_transform_tables(swconv_plan* pl) {
   Geometry& g = pl->g;
   g.in_area = g.out_area = 64;
+  g.in_longest = g.out_longest = 0;
   const int m = pl->m, t = pl->t, nblk = g.Tp / 64;
   TileInfo pad_tile;
   pad_tile.in_org = 0;
@@ -481,6 +482,8 @@ void build_transform_tables(swconv_plan* pl) {
       out_off += (bi.out_span + 63) / 64 * 64;
       g.in_area = std::max(g.in_area, in_off);
       g.out_area = std::max(g.out_area, out_off);
+      g.in_longest = std::max(g.in_longest, bi.in_span);
+      g.out_longest = std::max(g.out_longest, bi.out_span);
       for (int tl = t_lo; tl <= t_hi; ++tl) {
         const int ty = tl / g.tw, tx = tl % g.tw;
         const int y0 = ty * m - g.pad, x0 = tx * m - g.pad;

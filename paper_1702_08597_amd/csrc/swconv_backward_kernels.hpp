@@ -40,7 +40,7 @@ __global__ __launch_bounds__(256) void output_grad_transform_kernel(const float*
     auto part = [&](const BlockImage& b) {
       return StagedPart{dout + (size_t)max(b.n, 0) * g.out_image_stride + k * plane + b.out_elem0, b.out_span, b.out_off};
     };
-    stage_parts<1>(bi, g.slots, g.out_area, my, lane, part);
+    stage_parts<1>(bi, g.slots, g.out_longest, my, lane, part);
   }
   __syncthreads();
   if (k >= g.K) return;

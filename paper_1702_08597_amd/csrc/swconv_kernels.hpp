@@ -41,6 +41,7 @@ struct Geometry {
   // wave's staging area, each rounded up to a multiple of 64 floats; `in_area` / `out_area` =
   // floats of the largest such area over all blocks
   int slots, in_area, out_area;
+  int in_longest, out_longest;  // floats of the longest run of an image in any block
   uint32_t v_bytes, m_bytes;  // sizes of the V and M workspaces (both below 4 GiB)
   uint32_t wo_magic;          // ceil(2^32 / Wo): e / Wo == umulhi(e, wo_magic) for every staged element index
   int m_shift;                // log2(m)
@@ -222,19 +223,21 @@ __device__ __forceinline__ void stage_quads(const BlockImage* bi, int slots, flo
       if (lane < (span[i] & 3)) dst[i][(span[i] & ~3) + lane] = tail[i];
   }
 }
-// Which of them: quads where the parts are longer than 256 floats on average of the largest block.  Up to there the
+// Which of them: quads where some part of an image is longer than 256 floats.  Up to there the
 // four dword loads in flight need one round trip to memory too, and every lane of them carries something (64 images of
 // 13 x 13, 384 channels: input transform 12.2 us against 12.6, output gradient transform 14.5 against 15.8; 32 of
 // 15 x 15, 256 channels: 7.4 against 7.9; 64 of 7 x 28, 512 channels: 16.3 against 16.8 and 18.2 against 20.1).  Beyond it
 // they go to memory in rounds, six in a row for the 26 rows of 56 pixels that a block touches: 32 images of 56 x 56,
 // 256 channels: 75 -> 63 us and 69 -> 60 us with quads (5.3 and 5.5 TB/s); 11 of 29 x 23, 131 channels: 10.3 -> 9.8 us.
+// The longest part decides, not an average: blocks of F(2x2,5x5) on 27 x 27 reach into a second image now and then, and
+// lose 1 us of 14 with dwords.
 // (The output gradient transform has a band, 18 to 28 MB of dL/dO, where dwords stay up to 12 % ahead - 62 images of
 // 28 x 28, 128 channels: 14.9 against 15.9 us - between sizes where quads are: 5 % at 6, 35 and 50 MB, 8 % at 75 and 100.)
 // <2, 4> for blocks of at most two images, <4, 2> for the others: 32 registers either way.
 // DWORD_IMAGES: images in flight on the dword path; the output gradient's 13 x 13 planes go faster one by one.
 template <int DWORD_IMAGES, typename Part>
-__device__ __forceinline__ void stage_parts(const BlockImage* bi, int slots, int area, float* my, int lane, Part part) {
-  if (area <= 256 * slots)
+__device__ __forceinline__ void stage_parts(const BlockImage* bi, int slots, int longest, float* my, int lane, Part part) {
+  if (longest <= 256)
     stage_dwords<DWORD_IMAGES, 4>(bi, slots, my, lane, part);
   else if (slots <= 2)
     stage_quads<2, 4>(bi, slots, my, lane, part);
@@ -270,7 +273,7 @@ __global__ __launch_bounds__(256) void input_transform_kernel(const float* __res
     auto part = [&](const BlockImage& b) {
       return StagedPart{in + (size_t)max(b.n, 0) * g.in_image_stride + c * plane + b.in_elem0, b.in_span, b.in_off};
     };
-    stage_parts<4>(bi, g.slots, g.in_area, my, lane, part);
+    stage_parts<4>(bi, g.slots, g.in_longest, my, lane, part);
   }
   __syncthreads();
   if (c >= g.C) return;
