@@ -277,18 +277,27 @@ __device__ inline void cut_schedule(const ScheduleShape& s, const PackTables& t,
   __shared__ double dpart[17];
   __shared__ int32_t ipart[17];
   const int r = threadIdx.x;
-  if (r == 0) {
-    double sum = 0;
-    uint32_t work = 0;
-    for (int p = 0; p < s.P; ++p) {
-      block_cost[p] = sum;
-      work_before[p] = work;
-      sum += (double)s.ntb * ((double)s.panel_cost + t.stats[p].cost);
-      work += (uint32_t)s.ntb * (uint32_t)t.stats[p].cost;
+  if (r < 64) {  // one position per lane (kMaxPositions); the sums are of whole numbers, so their order does not matter
+    const int32_t cost = r < s.P ? t.stats[r].cost : 0;
+    const double own = r < s.P ? (double)s.ntb * ((double)s.panel_cost + cost) : 0;
+    const uint32_t own_work = (uint32_t)s.ntb * (uint32_t)cost;
+    double sum = own;
+    uint32_t work = own_work;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const double up = __shfl_up(sum, d);
+      const uint32_t up_work = (uint32_t)__shfl_up((int)work, d);
+      if (r >= d) sum += up, work += up_work;
     }
-    block_cost[s.P] = sum;
-    steps_at[s.n_launch] = work - (uint32_t)s.slice_ovh * (uint32_t)(s.P * s.ntb * s.spp);
-    heaviest = 0;
+    if (r < s.P) {
+      block_cost[r] = sum - own;
+      work_before[r] = work - own_work;
+    }
+    if (r == s.P - 1) {
+      block_cost[s.P] = sum;
+      steps_at[s.n_launch] = work - (uint32_t)s.slice_ovh * (uint32_t)(s.P * s.ntb * s.spp);
+      heaviest = 0;
+    }
   }
   __syncthreads();
   const double total = block_cost[s.P];
