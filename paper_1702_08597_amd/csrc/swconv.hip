@@ -1156,8 +1156,8 @@ int prepare_backward(swconv_plan* pl, hipStream_t st) {
     HIP_TRY(hipMemcpy(stats, bt.tables.stats, (size_t)P * sizeof(PositionStats), hipMemcpyDeviceToHost));
     uint64_t batches = 2;  // the product fetches up to two batches past a slice's end
     for (int p = 0; p < P; ++p) batches += (uint64_t)stats[p].batches;
-    if ((rc = reserve_packed(&bt, P, pl->n_tau_blocks, batches, &out, &shape)) || (rc = schedule_on_host(&bt, P, pl->n_tau_blocks)))
-      return rc;
+    if ((rc = reserve_packed(&bt, P, pl->n_tau_blocks, batches, &out, &shape))) return rc;
+    if ((rc = schedule_on_host(&bt, P, pl->n_tau_blocks))) return rc;
     shape.n_launch = 0;  // nothing left to cut for launch 2
   }
   const int chunks = (std::max(spp, fw_spp) + 15) / 16;
@@ -1684,8 +1684,8 @@ int swconv_prune_step(int64_t rows, const int32_t* rowptr_dev, const int32_t* co
   const LaunchTarget to{(hipStream_t)hip_stream, nullptr, nullptr};
   const dim3 grid(prune_groups(rows));
   int rc;
-  if ((rc = launch_kernel(prune_update_kernel, grid, dim3(kPruneThreads), 0, to, rows, rowptr_dev, vals_dev, grad_dev, eta, lambda,
-                          eps, beta, updated_dev, rowptr_out_dev)))
+  if ((rc = launch_kernel(prune_update_kernel, grid, dim3(kPruneThreads), 0, to, rows, rowptr_dev, vals_dev, grad_dev,
+                          eta, lambda, eps, beta, updated_dev, rowptr_out_dev)))
     return rc;
   if ((rc = launch_kernel(prune_scan_kernel, dim3(1), dim3(1024), 0, to, rows, rowptr_out_dev))) return rc;
   return launch_kernel(prune_compact_kernel, grid, dim3(kPruneThreads), 0, to, rows, rowptr_dev, colidx_dev, vals_dev, grad_dev,

@@ -22,8 +22,8 @@ constexpr int kPruneRowLanes = 16;
 constexpr int kPruneThreads = 256;
 constexpr int kPruneRows = kPruneThreads / kPruneRowLanes;
 
-// Their workgroups: one per kPruneRows rows up to 2^23 (a launch holds less than 2^32 threads); beyond 2^27 rows a
-// workgroup takes more than one turn (as one launch of more threads, its grid wrapped).  Any row count that int32 row pointers can number.
+// Their workgroups: one per kPruneRows rows up to 2^23; beyond 2^27 rows a workgroup takes more than one turn.  A launch
+// of 2^32 threads or more wraps: rows were skipped without an error.  Any row count that int32 row pointers can number.
 constexpr unsigned prune_groups(int64_t rows) {
   const int64_t groups = (rows + kPruneRows - 1) / kPruneRows, most = (int64_t)1 << 23;
   return (unsigned)(groups < most ? groups : most);
