@@ -121,6 +121,7 @@ struct PackedMatrix {
   bool packed = false, on_device = false;
   size_t n_pairs = 0;                 // (row offset, weight) pairs of the stream, spare ones included
   int n_slices = 0;
+  int longest = 0;                    // stored entries of the longest row, or a bound
   // The host copies below: what pack_matrix made, or nothing yet after a packing on the device
   // (fetch_packed_host brings them over when something reads them).
   bool host_current = false;
@@ -331,11 +332,11 @@ struct SpmmArgs {
   float* partial;      // their sums, per tile block and stream entry
 };
 
-template <int NW, int PIECES, bool DOTS>
+template <int NW, int PIECES, bool DOTS, bool LONG>
 int launch_spmm_t(const swconv_plan* pl, const PackedMatrix& pm, const LaunchTarget& to, const SpmmArgs& a) {
   if (pm.n_wgs_used == 0) return SWCONV_OK;
   const size_t lds = (size_t)pm.cols * kTileBlock * sizeof(float) + kSpmmLdsExtra + (size_t)pm.item_cap * sizeof(Slice);
-  auto kern = spmm_kernel<NW, PIECES, DOTS>;
+  auto kern = spmm_kernel<NW, PIECES, DOTS, LONG>;
   static bool attr_set = false;
   if (!attr_set) {
     HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes));
@@ -352,16 +353,24 @@ int launch_spmm_t(const swconv_plan* pl, const PackedMatrix& pm, const LaunchTar
 // case; beyond, six up to 288 and seven up to 319.  Three to five pieces between them measured 3 to 7 % faster for the
 // product and the joint pass at 112 to 160 channels (128 channels, N = 16, 28 x 28: 9.0 against 9.5 us and 11.9 against
 // 12.6) and the same at 192 and 224 (13.0 and 22.3, 15.4 and 23.2 us either way); they are not built.
-template <bool DOTS>
-int launch_spmm(const swconv_plan* pl, const PackedMatrix& pm, const LaunchTarget& to, const SpmmArgs& a) {
+template <bool DOTS, bool LONG>
+int launch_spmm_pieces(const swconv_plan* pl, const PackedMatrix& pm, const LaunchTarget& to, const SpmmArgs& a) {
   const int threads = pm.waves * 64, pieces = (pm.cols * (kTileBlock / 4) + threads - 1) / threads;
   if (pm.waves == 12)
-    return pieces <= 2   ? launch_spmm_t<12, 2, DOTS>(pl, pm, to, a)
-           : pieces <= 6 ? launch_spmm_t<12, 6, DOTS>(pl, pm, to, a)
-                         : launch_spmm_t<12, kPanelPieces12, DOTS>(pl, pm, to, a);
+    return pieces <= 2   ? launch_spmm_t<12, 2, DOTS, LONG>(pl, pm, to, a)
+           : pieces <= 6 ? launch_spmm_t<12, 6, DOTS, LONG>(pl, pm, to, a)
+                         : launch_spmm_t<12, kPanelPieces12, DOTS, LONG>(pl, pm, to, a);
   if (pm.waves == 16)
-    return pieces <= 6 ? launch_spmm_t<16, 6, DOTS>(pl, pm, to, a) : launch_spmm_t<16, kPanelPieces, DOTS>(pl, pm, to, a);
-  return launch_spmm_t<8, kPanelPieces, DOTS>(pl, pm, to, a);
+    return pieces <= 6 ? launch_spmm_t<16, 6, DOTS, LONG>(pl, pm, to, a)
+                       : launch_spmm_t<16, kPanelPieces, DOTS, LONG>(pl, pm, to, a);
+  return launch_spmm_t<8, kPanelPieces, DOTS, LONG>(pl, pm, to, a);
+}
+
+template <bool DOTS>
+int launch_spmm(const swconv_plan* pl, const PackedMatrix& pm, const LaunchTarget& to, const SpmmArgs& a) {
+  if constexpr (!DOTS)
+    if (pm.longest <= kUnitSteps) return launch_spmm_pieces<DOTS, false>(pl, pm, to, a);
+  return launch_spmm_pieces<DOTS, true>(pl, pm, to, a);
 }
 
 // Y[p] = A[p] * X[p]
@@ -806,6 +815,8 @@ void pack_matrix(PackedMatrix* pm, int P, int ntb, const int32_t* rowptr, const 
       sl.len = (pm->sorted_len[sl.row0] + kStepGroup - 1) / kStepGroup * kStepGroup;
     }
   });
+  pm->longest = 0;
+  for (const int32_t l : pm->sorted_len) pm->longest = std::max(pm->longest, (int)l);
   // where each slice's batches start in the stream
   uint64_t cursor = 0;  // 512-byte batches
   pm->padded_nnz = 0;
@@ -1115,6 +1126,7 @@ int prepare_backward(swconv_plan* pl, hipStream_t st) {
   size_grid(&bt, (int64_t)P * pl->n_tau_blocks * (bt.rows_padded / kSliceRows));
   bt.n_wgs = std::min(bt.n_wgs, kPackMaxWgs);
   const int spp = bt.rows_padded / kSliceRows;
+  int longest = K;
   ScheduleShape shape = schedule_shape(bt, P, pl->n_tau_blocks);
   PackedOut out{};
   if ((rc = reserve_tables(&bt, P))) return rc;
@@ -1155,7 +1167,11 @@ int prepare_backward(swconv_plan* pl, hipStream_t st) {
     HIP_TRY(hipStreamSynchronize(st));
     HIP_TRY(hipMemcpy(stats, bt.tables.stats, (size_t)P * sizeof(PositionStats), hipMemcpyDeviceToHost));
     uint64_t batches = 2;  // the product fetches up to two batches past a slice's end
-    for (int p = 0; p < P; ++p) batches += (uint64_t)stats[p].batches;
+    longest = 0;
+    for (int p = 0; p < P; ++p) {
+      batches += (uint64_t)stats[p].batches;
+      longest = std::max(longest, (int)stats[p].longest);
+    }
     if ((rc = reserve_packed(&bt, P, pl->n_tau_blocks, batches, &out, &shape))) return rc;
     if ((rc = schedule_on_host(&bt, P, pl->n_tau_blocks))) return rc;
     shape.n_launch = 0;  // nothing left to cut for launch 2
@@ -1166,6 +1182,7 @@ int prepare_backward(swconv_plan* pl, hipStream_t st) {
                           (const uint2*)pl->d_bits, rank_table(bt, P), bt.tables, out, shape)))
     return rc;
   bt.nnz = pl->fw.nnz;
+  bt.longest = longest;
   bt.host_current = false;
   bt.index_current = bt.packed = bt.on_device = true;
   pl->bt_current = true;
@@ -1737,6 +1754,7 @@ int swconv_set_weights_device(swconv_plan* pl, void* hip_stream, const int32_t* 
   PackedOut out;
   if ((rc = reserve_packed(&fw, P, pl->n_tau_blocks, batches, &out, &shape))) return rc;
   fw.nnz = rep.nnz;
+  fw.longest = longest;
   if (pl->stays) {
     if ((rc = schedule_on_host(&fw, P, pl->n_tau_blocks))) return rc;
     shape.n_launch = 0;  // nothing left to cut for launch 2

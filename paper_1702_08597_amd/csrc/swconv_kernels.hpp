@@ -130,6 +130,7 @@ constexpr int kMaxItemSlices = 256;  // slices per work item: their descriptors 
                                      // pieces each, one piece per thread of the smallest workgroup (512 threads)
 constexpr int kMinItemSlices = 8;    // the least the LDS left over by a large panel must hold
 constexpr int kXcds = 8;
+constexpr int kGroupPieces = 2;  // panel pieces that a wave asks for in front of one slice
 
 // Workgroup ids are dealt round-robin to the 8 XCDs; remap them so that each XCD gets one
 // contiguous range of virtual ids (neighbours in the work list then share an L2).
@@ -345,14 +346,11 @@ __global__ __launch_bounds__(256) void input_transform_kernel(const float* __res
 // Lanes <-> tiles (Section 5: vectorise over tiles), four tiles per lane and four rows per wave:
 // a slice has four rows and each quarter of a wave (16 lanes) works on one of them.  Lane (q, s)
 // owns row q and the tiles 4s .. 4s+3 of the 64-tile block, so one 16-byte LDS read per lane
-// feeds four FMAs, and one address addition serves four non-zeros x 64 tiles: 5 vector-ALU
-// instructions per 256 tile-FMAs.  That matters because the vector ALU (one wave instruction per
-// SIMD per 4 clocks) and LDS (a 16-byte-per-lane read per 4.8 clocks per CU, whether the quarters
-// read one row or four different ones) are both close to saturated by this loop.
+// feeds four FMAs, and one LDS address serves four non-zeros x 64 tiles.  LDS delivers such a read per 4.1 clocks
+// per CU, whether the quarters read one row or four different ones: 16.3 clocks of a SIMD, the longest part of a step.
 // The (row offset, weight) pairs differ between the quarters, so they travel through vector
-// memory, 16 steps per load: lane (q, s) fetches the pair of row q, step 16 b + s, and at step i
-// every lane of a quarter takes the pair from lane i of its quarter with a DPP row broadcast,
-// folded into the address addition and into the FMAs.
+// memory, 16 steps per load: lane (q, s) fetches the pair of row q, step 16 b + s, and the matrix unit broadcasts
+// the pairs of four steps at a time to all lanes of the quarters (swconv_mfma_units.inc).
 //
 // Stream layout: per slice, batches of 512 bytes; batch b holds [q][s] -> (offset, weight) of row
 // q, step 16 b + s; rows shorter than the slice are padded with (0, +0.0f).  A slice's length is
@@ -445,8 +443,7 @@ __device__ __forceinline__ void quarter_batch(const float* panel, uint32_t lane_
 // The rolling unit of the inner loop (see swconv_rolling_unit.inc): the same steps as quarter_batch over
 // two batches, as one pipeline with four reads always in flight, in assembly with the sixteen registers
 // of those reads fixed: v[112:127], the top of the 128 registers of the fused F(4x4,3x3) kernel, whose
-// other registers are full of accumulators.  (In the stand-alone product kernel below the compiler's
-// group-by-group code is as fast: there memory, not the inner loop, sets the pace.)
+// other registers are full of accumulators, so that it has none for the broadcasts of the matrix unit.
 constexpr int kUnitSteps = 2 * kBatchSteps;
 #define SWCONV_UNIT_NAME unit_rolling_hi
 #define SWCONV_XR0 112
@@ -483,6 +480,7 @@ constexpr int kUnitSteps = 2 * kBatchSteps;
 #undef SWCONV_XR13
 #undef SWCONV_XR14
 #undef SWCONV_XR15
+#include "swconv_mfma_units.inc"
 
 // ---- dot products (backward pass, Eq. 5 second line): dL/dW_F at the stored entries ----
 // The same walk over a packed operand, but every stored entry (row, column) gets the dot product of a
@@ -495,28 +493,6 @@ constexpr int kUnitSteps = 2 * kBatchSteps;
 template <int CTRL>
 __device__ __forceinline__ float dpp_add(float x, float send) {
   return x + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, send), CTRL, 0xf, 0xf, true));
-}
-
-// Steps G*kStepGroup .. +kStepGroup-1 of the batch (boff, bw): the lane's share (its four tiles) of each
-// step's dot product with z, and the products.
-template <int G>
-__device__ __forceinline__ void product_dots_group(const float* panel, uint32_t lane_sub, const u32x2_t& b, const f32x4_t& z,
-                                              float (&d)[kBatchSteps], Acc4& acc) {
-  constexpr int I0 = G * kStepGroup;
-  const Group4 g = quarter_reads<G>(panel, lane_sub, b.x);
-  quarter_fma<I0 + 0, true>(acc, b.y, g.x0);
-  quarter_fma<I0 + 1, false>(acc, b.y, g.x1);
-  quarter_fma<I0 + 2, false>(acc, b.y, g.x2);
-  quarter_fma<I0 + 3, false>(acc, b.y, g.x3);
-  const f32x4_t* x[4] = {&g.x0, &g.x1, &g.x2, &g.x3};
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const f32x4_t& v = *x[i];
-    float p = z[0] * v[0];
-    p = fmaf(z[1], v[1], p);
-    p = fmaf(z[2], v[2], p);
-    d[I0 + i] = fmaf(z[3], v[3], p);
-  }
 }
 
 // a <- in the lanes of the banks (groups of four lanes of a row of 16) of LO: a + a of the lane given by
@@ -551,15 +527,10 @@ __device__ __forceinline__ void fold_bit2(float& a0, float& a1, float& a2, float
 // bit 3 (2, 1, 0) and adds the partner's values for that half, so 8 + 4 + 2 + 1 sums leave the total
 // of step i in lane i: 33 instructions, as the bank masks of DPP select for free in the first two
 // stages, against 45 with selects in all four and 80 for a reduction step by step.
-__device__ __forceinline__ float product_dots_batch(const float* panel, uint32_t lane_sub, const u32x2_t& b, int steps,
-                                               const f32x4_t& z, int lane_in_quarter, Acc4& acc) {
+__device__ __forceinline__ float product_dots_batch(const f32x4_t& lane_base4, float one, const u32x2_t& b, int steps,
+                                                    const f32x4_t& z, int lane_in_quarter, Acc4& acc) {
   float d[kBatchSteps];
-#pragma unroll
-  for (int i = 0; i < kBatchSteps; ++i) d[i] = 0.0f;
-  product_dots_group<0>(panel, lane_sub, b, z, d, acc);
-  if (steps > 1 * kStepGroup) product_dots_group<1>(panel, lane_sub, b, z, d, acc);
-  if (steps > 2 * kStepGroup) product_dots_group<2>(panel, lane_sub, b, z, d, acc);
-  if (steps > 3 * kStepGroup) product_dots_group<3>(panel, lane_sub, b, z, d, acc);
+  unit_dots(lane_base4, one, b, min(steps, kBatchSteps), z, d, acc);
   fold_bit3(d[0], d[1], d[2], d[3], d[8], d[9], d[10], d[11]);
   fold_bit3(d[4], d[5], d[6], d[7], d[12], d[13], d[14], d[15]);
   fold_bit2(d[0], d[1], d[2], d[3], d[4], d[5], d[6], d[7]);
@@ -576,12 +547,30 @@ __device__ __forceinline__ float product_dots_batch(const float* panel, uint32_t
 // partial[tau_block][stream entry] = the entry's dot product of its row of `zrows` (I_F) with its column's row
 // of V (dL/dZ) over that tile block; `partial_stride` entries per block.  An entry's dot product does not
 // depend on which of the two tensors is the panel, so dL/dZ, the weights and every LDS value are read once for
-// both gradients: 177 vector-ALU instructions per 16 steps against 80 + 125 in two passes, half the LDS reads.
-// What is left in the way with DOTS at 12 waves and their 80 registers: <12,6> keeps two of its registers in scratch (12
-// bytes a lane, <12,7> 16), whose reload in front of the next panel's requests waits for all vector memory, and the
-// panel's offset sits in a vector register, so that each request runs in a readfirstlane loop.  The variants of 16
-// waves spill nothing, the product alone has neither.
-template <int NWAVES, int PIECES, bool DOTS>
+// both gradients.
+//
+// EARLY (16 waves, one workgroup per CU): the next item's panel is asked for while this one is worked on, kGroupPieces
+// of a thread's pieces in front of each of the wave's first slices, since nothing else on the CU covers its way from
+// memory.  Vector-memory results come back in issue order and the stream batches use the same path; the pieces are few
+// at a time and the batches two to four ahead, so that a batch is seldom waited for because of a piece.  Workgroups of
+// 12 waves have no registers for that (80 each); two of them share a CU, so one computes while the other loads.
+// LONG: slices may have more than kUnitSteps steps.  Then four batches are on their way (two units), else two: a
+// slice of a few steps would fetch 2 KB to use the first 512 bytes (11 x 29 x 23, 131 -> 187 channels at 7 %: 9.6
+// against 10.3 us).
+// What it takes (us, before: DPP broadcasts, panel pieces written to LDS by 4-byte words because the array's declared
+// alignment was that of a float, the panel asked for behind an item's last slice, and a draw of a slice 25 instructions
+// longer): 64 x 13 x 13, 384 -> 384 at 10 %: 42.1 -> 37; 384 -> 256 at 30 %: 67 -> 59.5 (37 TFLOP/s); 32 x 13 x 13,
+// 256 -> 384: 18.8 -> 16.8; 32 x 56 x 56, 256 -> 256: 142 -> 132, of which 118 remain without the inner loop (V and M
+// go through memory).  Both gradients in one pass: 69 -> 65, 222 -> 204 (56 x 56), 30.1 -> 26.6.
+// Tried and not kept: a wave of its own that loads panels straight into one of two LDS buffers, one barrier an item
+// (15 waves compute): 16.0 for 16.8 and 9.1 for 9.7 us on the two small layers, 135 for 132 and 220 for 205 on the
+// 56 x 56 one; drawing a slice under the unit in front instead of before it: 17.2 for 16.6.
+template <typename T>
+__device__ __forceinline__ __attribute__((address_space(3))) T* lds_at(uint32_t byte) {
+  return (__attribute__((address_space(3))) T*)(uintptr_t)byte;
+}
+
+template <int NWAVES, int PIECES, bool DOTS, bool LONG>
 __global__ __launch_bounds__(NWAVES * 64, NWAVES == 12 ? 6 : 4) void spmm_kernel(
     const float* __restrict__ V, float* __restrict__ Mbuf, const uint32_t* __restrict__ stream, uint32_t stream_bytes,
     const Slice* __restrict__ slices, int n_slices, const WorkItem* __restrict__ items,
@@ -589,12 +578,24 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 12 ? 6 : 4) void spmm_kernel
     const float* __restrict__ zrows, float* __restrict__ partial, uint32_t partial_stride) {
   constexpr int NT = NWAVES * 64;
   constexpr int TB = kTileBlock;
+  constexpr bool EARLY = NWAVES == 16;
+  constexpr int kBatchRegs = !DOTS && LONG ? 4 : 2;
   typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
-  // LDS: the panel [C][64] at offset 0 of the workgroup, the slice counter (64 bytes), then the
+  // LDS: the slice counter (64 bytes; at offset 0, where the appending draw can address it), the panel [C][64], then the
   // descriptors of the item's slices
-  extern __shared__ float panel[];
-  int* next_slice = reinterpret_cast<int*>(panel + (size_t)C * TB);
-  u32x4_t* desc = reinterpret_cast<u32x4_t*>(panel + (size_t)C * TB + 16);
+  extern __shared__ __attribute__((aligned(16))) float panel[];
+  // byte addresses in LDS (opaque: the array's address as a symbol costs an addition per access)
+  uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)panel;
+  asm volatile("" : "+s"(lds0));
+  const uint32_t panel0 = lds0 + 64u, desc0 = panel0 + (uint32_t)C * (TB * 4u);
+  int drawn_before = -NWAVES;  // draws of the items before, less the first slices, which are not drawn
+  // the thread's index, opaque: what is formed from it is formed where it is used instead of held in registers that the
+  // inner loop needs
+  auto thread_index = [&]() -> uint32_t {
+    uint32_t t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+  };
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const RangeHeader hdr = ranges[xcd_contiguous_id(blockIdx.x, n_wgs)];
@@ -605,26 +606,15 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 12 ? 6 : 4) void spmm_kernel
   const __amdgpu_buffer_rsrc_t dr = make_rsrc(slices, (uint32_t)n_slices * (uint32_t)sizeof(Slice));
   const uint32_t lane8 = (uint32_t)lane * 8u;
 
-  // Panel staging: thread i moves the 16-byte pieces i, i + NT, ... of a panel; their offsets
-  // inside a panel are the same for every item, so they are computed once.  The next item's panel
-  // travels through registers.  Vector-memory results come back in issue order and the stream
-  // batches use the same path, so a wave asks for the next panel only after its last slice of the
-  // item: a wait on a batch never has a panel load in front of it.  (Surplus pieces are parked
-  // past the end of the buffer and read 0 without touching memory.)  The descriptors of the item's
-  // slices (32 bytes each, at most kMaxItemSlices) are staged the same way, one 16-byte piece per
+  // Panel staging: thread i moves the 16-byte pieces i, i + NT, ... of a panel, through registers.  The descriptors
+  // of the item's slices (32 bytes each, at most kMaxItemSlices) are staged the same way, one 16-byte piece per
   // thread: drawing a slice then costs an LDS atomic and an LDS read, and no scalar-memory load -
   // which shares its counter with the LDS reads of the inner loop - is in flight while it runs.
-  constexpr int v4_per_row = TB / 4;
-  const int total = C * v4_per_row;
-  const __amdgpu_buffer_rsrc_t vr = make_rsrc(V, v_bytes);
-  constexpr int rows_per_piece = NT / v4_per_row;
-  const int row0 = threadIdx.x / v4_per_row;
-  const uint32_t voff0 = ((uint32_t)row0 * Tp + (threadIdx.x % v4_per_row) * 4) * 4u;
+  constexpr int rows_per_piece = NT / (TB / 4);
   const uint32_t piece_stride = (uint32_t)rows_per_piece * (uint32_t)Tp * 4u;
-  auto load_piece = [&](int u, uint32_t soff) -> u32x4_t {
-    uint32_t at = row0 + u * rows_per_piece < C ? voff0 : 0xfffffff0u;
-    asm volatile("" : "+v"(at));  // formed where it is used: kept ready, one per piece, they cost the loop its registers
-    return __builtin_amdgcn_raw_buffer_load_b128(vr, (int)at, (int)(soff + (uint32_t)u * piece_stride), 0);
+  // the panel's rows as a buffer of their own: what reaches past the last one reads 0 and touches no memory
+  auto panel_rsrc = [&](const WorkItem& w) {
+    return make_rsrc(V + ((size_t)w.p * C * Tp + (size_t)w.tau_block * TB), ((uint32_t)(C - 1) * (uint32_t)Tp + TB) * 4u);
   };
   u32x4_t piece[PIECES], desc_piece;
   auto load_batch = [&](uint32_t byte_off) -> u32x2_t {
@@ -638,44 +628,51 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 12 ? 6 : 4) void spmm_kernel
     int len;        // steps
     int k;          // per lane
   };
-  auto quarter_k = [&](int k0, int k1, int k2, int k3) {
-    return quarter == 0 ? k0 : quarter == 1 ? k1 : quarter == 2 ? k2 : k3;
+  // The wave's first slice of an item, from the descriptors in memory (clamped: unconditional, in bounds).
+  auto first_slice = [&](const WorkItem& w) -> Cur {
+    const Slice sl = slices[min(w.slice_begin + wave, n_slices - 1)];
+    const int k = quarter == 0 ? sl.k[0] : quarter == 1 ? sl.k[1] : quarter == 2 ? sl.k[2] : sl.k[3];
+    return Cur{sl.batch0 * 512u, sl.len, k};
   };
-
-  // Start of an item, issued as early as the item is known (for the first one: right after the
-  // range header; for the others: after the wave's last slice of the item before): the panel
-  // pieces and the descriptor piece, then the wave's first slice descriptor and its first two
-  // batches, which arrive right behind the panel, so the first slice starts without another
-  // memory round trip.
-  Cur cur;
-  u32x2_t b0 = {0u, 0u}, b1 = {0u, 0u};
-  // dot products: the lane's four tiles of the row of its quarter (zeros for a padding row)
-  f32x4_t z_cur = {0.0f, 0.0f, 0.0f, 0.0f};
   auto row_offset = [&](int p, int tau0, int k) -> uint32_t {  // quarters of padding rows are parked beyond the buffer
     return k >= 0 ? (((uint32_t)p * K + (uint32_t)k) * Tp + tau0) * 4u + lane_sub : 0xfffffff0u;
   };
   auto load_z = [&](int p, int tau0, int k) -> f32x4_t {
     return __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(zr, (int)row_offset(p, tau0, k), 0, 0));
   };
-  auto start_item = [&](const WorkItem& w) {
-    const uint32_t soff = ((uint32_t)w.p * C * Tp + (uint32_t)w.tau_block * TB) * 4u;
+  // Group g of an item's requests: the descriptors with the first, kGroupPieces panel pieces each.
+  constexpr int kGroups = (PIECES + kGroupPieces - 1) / kGroupPieces;
+  auto request_group = [&](int g, const WorkItem& w, __amdgpu_buffer_rsrc_t vr) {
+    const uint32_t tid = thread_index();
+    const uint32_t voff0 = ((tid / (TB / 4)) * (uint32_t)Tp + (tid % (TB / 4)) * 4u) * 4u;
+    if (g == 0)
+      desc_piece = __builtin_amdgcn_raw_buffer_load_b128(
+          dr, (int)((int)tid < 2 * (w.slice_end - w.slice_begin) ? tid * 16u : 0xfffffff0u),
+          (int)((uint32_t)w.slice_begin * (uint32_t)sizeof(Slice)), 0);
 #pragma unroll
-    for (int u = 0; u < PIECES; ++u) piece[u] = load_piece(u, soff);
-    const int n_desc_pieces = 2 * (w.slice_end - w.slice_begin);
-    desc_piece = __builtin_amdgcn_raw_buffer_load_b128(
-        dr, (int)((int)threadIdx.x < n_desc_pieces ? threadIdx.x * 16u : 0xfffffff0u),
-        (int)((uint32_t)w.slice_begin * (uint32_t)sizeof(Slice)), 0);
-    const Slice sl = slices[min(w.slice_begin + wave, n_slices - 1)];  // clamped: unconditional, in bounds
-    cur.base = sl.batch0 * 512u;
-    cur.len = sl.len;
-    cur.k = quarter_k(sl.k[0], sl.k[1], sl.k[2], sl.k[3]);
-    b0 = load_batch(cur.base);
-    b1 = load_batch(cur.base + 512u);
-    if constexpr (DOTS) z_cur = load_z(w.p, w.tau_block * TB, cur.k);
+    for (int u = g * kGroupPieces; u < (g + 1) * kGroupPieces; ++u)
+      if (u < PIECES)
+        piece[u] = __builtin_amdgcn_raw_buffer_load_b128(vr, (int)voff0, (int)((uint32_t)u * piece_stride), 0);
   };
 
+  // Start of the first item: the panel pieces and the descriptor piece, then the wave's first slice descriptor and
+  // its first two batches, which arrive right behind the panel.
   WorkItem it = hdr.first;
-  start_item(it);
+#pragma unroll
+  for (int g = 0; g < kGroups; ++g) request_group(g, it, panel_rsrc(it));
+  WorkItem it_next = items[min(hdr.item_begin + 1, hdr.item_end - 1)];
+  Cur cur = first_slice(it);
+  u32x2_t b0 = load_batch(cur.base), b1 = load_batch(cur.base + 512u);
+  u32x2_t b2 = {0u, 0u}, b3 = {0u, 0u};
+  if constexpr (kBatchRegs == 4) b2 = load_batch(cur.base + 1024u), b3 = load_batch(cur.base + 1536u);
+  f32x4_t lane_base4;
+  lane_base4[0] = lane_base4[1] = lane_base4[2] = lane_base4[3] = __uint_as_float(panel0 + lane_sub);
+  float one = 1.0f;
+  asm volatile("" : "+v"(lane_base4), "+v"(one));
+  // dot products: the lane's four tiles of the row of its quarter (zeros for a padding row)
+  f32x4_t z_cur = {0.0f, 0.0f, 0.0f, 0.0f};
+  if constexpr (DOTS) z_cur = load_z(it.p, it.tau_block * TB, cur.k);
+
   for (int item = hdr.item_begin;; ++item) {
     const int tau0 = it.tau_block * TB;
     const int n_item_slices = it.slice_end - it.slice_begin;
@@ -683,74 +680,121 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 12 ? 6 : 4) void spmm_kernel
     const __amdgpu_buffer_rsrc_t pr =
         make_rsrc(DOTS ? partial + (size_t)it.tau_block * partial_stride : nullptr, DOTS ? partial_stride * 4u : 0u);
     const bool has_next = item + 1 < hdr.item_end;
-    const WorkItem it_next = items[has_next ? item + 1 : item];
+    // scalar loads: they arrive while the panel is written
+    const WorkItem it_after = items[min(item + 2, hdr.item_end - 1)];
+    Cur next_first = first_slice(it_next);
+    if (!has_next) next_first.base = 0xfffff000u;
     if (item != hdr.item_begin) __syncthreads();  // every wave is done with the previous panel and descriptors
+    const uint32_t tid = thread_index(), tid16 = tid * 16u;
 #pragma unroll
     for (int u = 0; u < PIECES; ++u) {
-      const int idx = threadIdx.x + u * NT;
-      if (idx < total) *reinterpret_cast<u32x4_t*>(panel + idx * 4) = piece[u];
+      if ((int)tid < C * (TB / 4) - u * NT) *lds_at<u32x4_t>(panel0 + tid16 + (uint32_t)u * (NT * 16u)) = piece[u];
     }
-    if ((int)threadIdx.x < 2 * n_item_slices) desc[threadIdx.x] = desc_piece;
-    if (threadIdx.x == 0) *next_slice = NWAVES;  // item-local index of the first slice to be drawn
+    if ((int)tid < 2 * n_item_slices) *lds_at<u32x4_t>(desc0 + tid16) = desc_piece;
+    if (tid == 0 && item == hdr.item_begin) *lds_at<int>(lds0) = 0;
     __syncthreads();
 
     // Waves take slices dynamically, longest first: the first one by wave number, every further
     // one from a counter in LDS.  The next slice is drawn before the current one is computed.
-    if (wave < n_item_slices) {
-      while (true) {
-        int drawn = 0;
-        if (lane == 0) drawn = __hip_atomic_fetch_add(next_slice, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        const int i_next = __builtin_amdgcn_readfirstlane(drawn);
-        const bool more = i_next < n_item_slices;
-        const int i_desc = min(i_next, n_item_slices - 1);  // clamped: the read stays inside the staged part
-        const u32x4_t d_head = desc[2 * i_desc], d_k = desc[2 * i_desc + 1];  // all lanes read the same 32 bytes
-        Acc4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-        // Two batch registers in turn: batch j of a slice sits in register j % 2.  A register is
-        // refilled right after its batch is consumed, unconditionally, with the batch two ahead -
-        // or, when the slice has no such batch, with batch 0 / 1 of the NEXT slice (parked past
-        // the end of the stream when there is none: reads 0, touches no memory).  So the batches
-        // of a slice are always on their way one or two batches of work before they are needed,
-        // and no wait in the loop ever has more than one younger load in front of it.
-        Cur nxt;
-        nxt.base = more ? (uint32_t)__builtin_amdgcn_readfirstlane((int)d_head.x) * 512u : 0xfffff000u;
-        nxt.len = __builtin_amdgcn_readfirstlane((int)d_head.y);
-        nxt.k = quarter_k((int)d_k.x, (int)d_k.y, (int)d_k.z, (int)d_k.w);
-        const int batches = (cur.len + kBatchSteps - 1) / kBatchSteps;
-        f32x4_t z_next = {0.0f, 0.0f, 0.0f, 0.0f};
-        if constexpr (DOTS) z_next = load_z(it.p, tau0, more ? nxt.k : -1);
-        for (int j = 0, remaining = cur.len; j < batches; j += 2, remaining -= 2 * kBatchSteps) {
-          if constexpr (DOTS) {
-            const float r0 = product_dots_batch(panel, lane_sub, b0, remaining, z_cur, lane & 15, acc);
-            buffer_store_f32<SWCONV_AUX_M>(pr, lane * 4u, cur.base / 2u + (uint32_t)j * 256u, r0);
-          } else {
-            quarter_batch(panel, lane_sub, b0, remaining, acc);
-          }
-          b0 = load_batch(j + 2 < batches ? cur.base + (uint32_t)(j + 2) * 512u : nxt.base);
-          if (j + 1 < batches) {
-            if constexpr (DOTS) {
-              const float r1 = product_dots_batch(panel, lane_sub, b1, remaining - kBatchSteps, z_cur, lane & 15, acc);
-              buffer_store_f32<SWCONV_AUX_M>(pr, lane * 4u, cur.base / 2u + (uint32_t)(j + 1) * 256u, r1);
-            } else {
-              quarter_batch(panel, lane_sub, b1, remaining - kBatchSteps, acc);
-            }
-          }
-          b1 = load_batch(j + 3 < batches ? cur.base + (uint32_t)(j + 3) * 512u : nxt.base + 512u);
+    // Returns whether another one was drawn.
+    auto run_slice = [&]() -> bool {
+      const int drawn = __builtin_amdgcn_ds_append(lds_at<int>(lds0));  // adds 64, one per lane
+      Acc4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+      Cur nxt;
+      bool more;
+      auto take_drawn = [&]() {
+        const int i_next = (__builtin_amdgcn_readfirstlane(drawn) >> 6) - drawn_before;
+        more = i_next < n_item_slices;
+        const uint32_t d = desc0 + 32u * (uint32_t)min(i_next, n_item_slices - 1);  // clamped: stays inside the staged part
+        const u32x2_t d_head = *lds_at<u32x2_t>(d);  // all lanes read the same 8 bytes
+        const int d_k = *lds_at<int>(d + 16u + (uint32_t)quarter * 4u);
+        nxt.base = more ? (uint32_t)__builtin_amdgcn_readfirstlane((int)d_head.x) * 512u : next_first.base;
+        nxt.len = more ? __builtin_amdgcn_readfirstlane((int)d_head.y) : next_first.len;
+        nxt.k = more ? d_k : next_first.k;
+      };
+      const int len = cur.len;
+      // Batch registers in turn: a register is refilled right after its batch is consumed, unconditionally, with the
+      // batch kBatchRegs ahead - or, when the slice has no such batch, with the batch of the same register of the NEXT
+      // slice: the one drawn, or the wave's first of the next item (parked past the end of the stream when there is
+      // none: reads 0, touches no memory).
+      auto refill = [&](int j) -> u32x2_t {
+        return load_batch(LONG && j * kBatchSteps < len ? cur.base + (uint32_t)j * 512u
+                                                        : nxt.base + (uint32_t)(j & (kBatchRegs - 1)) * 512u);
+      };
+      // The first batches stand in front of the loop: what the wave has requested between them and their use
+      // (panel pieces, a row store) then need not arrive first - a wait in a loop is as strict as its strictest way in.
+      f32x4_t z_next = {0.0f, 0.0f, 0.0f, 0.0f};
+      if constexpr (DOTS) {
+        take_drawn();
+        z_next = more ? load_z(it.p, tau0, nxt.k) : load_z(it_next.p, it_next.tau_block * TB, nxt.k);
+        auto consume = [&](const u32x2_t& b, int j) {
+          const float r = product_dots_batch(lane_base4, one, b, len - j * kBatchSteps, z_cur, lane & 15, acc);
+          buffer_store_f32<SWCONV_AUX_M>(pr, lane * 4u, cur.base / 2u + (uint32_t)j * 256u, r);
+        };
+        if (len > 0) consume(b0, 0);
+        b0 = refill(2);
+        if (len > kBatchSteps) consume(b1, 1);
+        b1 = refill(3);
+        for (int j = 2; j * kBatchSteps < len; j += 2) {
+          consume(b0, j);
+          b0 = refill(j + 2);
+          if ((j + 1) * kBatchSteps < len) consume(b1, j + 1);
+          b1 = refill(j + 3);
         }
-        if (batches == 0) {  // an all-empty slice consumed nothing: fetch the next slice's batches here
-          b0 = load_batch(nxt.base);
-          b1 = load_batch(nxt.base + 512u);
+      } else {
+        auto consume = [&](const u32x2_t& x, const u32x2_t& y, int j) {
+          unit_mfma(lane_base4, one, x, y, min(len - j * kBatchSteps, kUnitSteps), acc);
+        };
+        take_drawn();
+        if (len > 0) consume(b0, b1, 0);
+        b0 = refill(kBatchRegs);
+        b1 = refill(kBatchRegs + 1);
+        if constexpr (LONG) {
+          if (len > kUnitSteps) consume(b2, b3, 2);
+          b2 = refill(6);
+          b3 = refill(7);
+          for (int j = 4; j * kBatchSteps < len; j += 4) {
+            consume(b0, b1, j);
+            b0 = refill(j + 4);
+            b1 = refill(j + 5);
+            if ((j + 2) * kBatchSteps < len) consume(b2, b3, j + 2);
+            b2 = refill(j + 6);
+            b3 = refill(j + 7);
+          }
         }
-        const u32x4v_t result = {__float_as_uint(acc.a0), __float_as_uint(acc.a1), __float_as_uint(acc.a2),
-                                 __float_as_uint(acc.a3)};
-        __builtin_amdgcn_raw_buffer_store_b128(result, mr, (int)row_offset(it.p, tau0, cur.k), 0, SWCONV_AUX_M);
-        if (!more) break;
-        cur = nxt;
-        z_cur = z_next;
+      }
+      const u32x4v_t result = {__float_as_uint(acc.a0), __float_as_uint(acc.a1), __float_as_uint(acc.a2),
+                               __float_as_uint(acc.a3)};
+      __builtin_amdgcn_raw_buffer_store_b128(result, mr, (int)row_offset(it.p, tau0, cur.k), 0, SWCONV_AUX_M);
+      cur = nxt;
+      z_cur = z_next;
+      return more;
+    };
+    bool more = wave < n_item_slices;
+    if (!more) {  // nothing to do here: on to the next item's first slice
+      cur = next_first;
+      b0 = load_batch(cur.base);
+      b1 = load_batch(cur.base + 512u);
+      if constexpr (kBatchRegs == 4) b2 = load_batch(cur.base + 1024u), b3 = load_batch(cur.base + 1536u);
+      if constexpr (DOTS) z_cur = load_z(it_next.p, it_next.tau_block * TB, cur.k);
+    }
+    const __amdgpu_buffer_rsrc_t next_panel = panel_rsrc(it_next);
+    if constexpr (EARLY) {
+#pragma unroll
+      for (int g = 0; g < kGroups; ++g) {
+        if (has_next) request_group(g, it_next, next_panel);
+        if (more) more = run_slice();
       }
     }
+    while (more) more = run_slice();
     if (!has_next) break;
+    drawn_before += n_item_slices;  // a slice, a draw
+    if constexpr (!EARLY) {
+#pragma unroll
+      for (int g = 0; g < kGroups; ++g) request_group(g, it_next, next_panel);
+    }
     it = it_next;
-    start_item(it);
+    it_next = it_after;
   }
 }
 
