@@ -1151,10 +1151,10 @@ int prepare_backward(swconv_plan* pl, hipStream_t st) {
   if (pl->grad_images_per_group > 0 && !pl->d_gtiles && (rc = upload(&pl->d_gtiles, pl->gtiles))) return rc;
   const LaunchTarget to{st, nullptr, nullptr};
   const int fw_spp = pl->fw.rows_padded / kSliceRows;
-  const size_t lds = ((size_t)(C * words + 3) / 4 * 4 + 2 * (size_t)bt.rows_padded) * sizeof(uint32_t);
+  const size_t lds = ((size_t)(C * words + 3) / 4 * 4 + 3 * (size_t)bt.rows_padded) * sizeof(uint32_t);
   static bool attr_set = false;
   if (!attr_set) {
-    // up to 638 x 21 words and two row tables, besides a few static words
+    // up to 638 x 21 words and three row tables, besides a few static words
     HIP_TRY(hipFuncSetAttribute((const void*)transpose_sort_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024));
     attr_set = true;
   }
@@ -1729,7 +1729,7 @@ int swconv_set_weights_device(swconv_plan* pl, void* hip_stream, const int32_t* 
   }
   ScheduleShape shape = schedule_shape(fw, P, pl->n_tau_blocks);
   if ((rc = launch_kernel(pack_sort_kernel, dim3(P, 1 + checks), dim3(kPackThreads),
-                          2 * (size_t)fw.rows_padded * sizeof(uint32_t), to, rowptr_dev, colidx_dev, P, K,
+                          3 * (size_t)fw.rows_padded * sizeof(uint32_t), to, rowptr_dev, colidx_dev, P, K,
                           fw.rows_padded, C, fw.tables, shape.slice_ovh, pl->h_report, pl->h_bad_cols)))
     return rc;
   HIP_TRY(hipStreamSynchronize(st));
