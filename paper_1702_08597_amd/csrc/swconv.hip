@@ -1701,12 +1701,16 @@ int swconv_prune_step(int64_t rows, const int32_t* rowptr_dev, const int32_t* co
   const LaunchTarget to{(hipStream_t)hip_stream, nullptr, nullptr};
   const dim3 grid(prune_groups(rows));
   int rc;
-  if ((rc = launch_kernel(prune_update_kernel, grid, dim3(kPruneThreads), 0, to, rows, rowptr_dev, vals_dev, grad_dev,
-                          eta, lambda, eps, beta, updated_dev, rowptr_out_dev)))
-    return rc;
-  if ((rc = launch_kernel(prune_scan_kernel, dim3(1), dim3(1024), 0, to, rows, rowptr_out_dev))) return rc;
-  return launch_kernel(prune_compact_kernel, grid, dim3(kPruneThreads), 0, to, rows, rowptr_dev, colidx_dev, vals_dev, grad_dev,
-                       eta, lambda, eps, beta, (const int32_t*)rowptr_out_dev, colidx_out_dev, vals_out_dev);
+  auto step = [&](auto local) -> int {
+    constexpr bool LOCAL = decltype(local)::value;
+    if ((rc = launch_kernel(prune_update_kernel<LOCAL>, grid, dim3(kPruneThreads), 0, to, rows, rowptr_dev, vals_dev, grad_dev,
+                            eta, lambda, eps, beta, updated_dev, rowptr_out_dev)))
+      return rc;
+    if (!LOCAL && (rc = launch_kernel(prune_scan_kernel, dim3(1), dim3(1024), 0, to, rows, rowptr_out_dev))) return rc;
+    return launch_kernel(prune_compact_kernel<LOCAL>, grid, dim3(kPruneThreads), 0, to, rows, rowptr_dev, colidx_dev, vals_dev,
+                         grad_dev, eta, lambda, eps, beta, rowptr_out_dev, colidx_out_dev, vals_out_dev);
+  };
+  return rows <= kPruneLocalRows ? step(std::true_type{}) : step(std::false_type{});
 }
 
 int swconv_set_weights_device(swconv_plan* pl, void* hip_stream, const int32_t* rowptr_dev, const int32_t* colidx_dev,

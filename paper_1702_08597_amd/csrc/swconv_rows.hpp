@@ -22,6 +22,12 @@ constexpr int kPruneRowLanes = 16;
 constexpr int kPruneThreads = 256;
 constexpr int kPruneRows = kPruneThreads / kPruneRowLanes;
 
+// Up to here the second of them finds its row pointers itself, from one sum per workgroup of the first: a thread then
+// reads at most kPruneLocalTurns of them.  (The sums that all workgroups read together grow with the square of the rows:
+// at 65536 rows 4096 workgroups of at most 16 KB, 32 MB through the L2s; beyond, the scan's launch costs less.)
+constexpr int kPruneLocalTurns = 16;
+constexpr int64_t kPruneLocalRows = (int64_t)kPruneLocalTurns * kPruneThreads * kPruneRows;
+
 // Their workgroups: one per kPruneRows rows up to 2^23; beyond 2^27 rows a workgroup takes more than one turn.  A launch
 // of 2^32 threads or more wraps: rows were skipped without an error.  Any row count that int32 row pointers can number.
 constexpr unsigned prune_groups(int64_t rows) {
