@@ -1203,9 +1203,19 @@ int prepare_weight_grad(swconv_plan* pl) {
   return SWCONV_OK;
 }
 
+// The partial sums that stage 2 of the backward pass leaves.
+PartialSums partial_sums(const swconv_plan* pl, float* dvals) {
+  return PartialSums{pl->d_partial, pl->n_tau_blocks, (uint32_t)pl->bt.n_pairs, pl->bt.d_index, (uint32_t)pl->bt.n_pairs, dvals};
+}
+
+// LDS of a workgroup of the one-kernel input gradient.
+size_t input_grad_lds(const swconv_plan* pl) {
+  return (size_t)4 * (((size_t)pl->grad_images_per_group * pl->g.H * pl->g.W + 63) / 64 * 64 + 64) * sizeof(float);
+}
+
 template <int M, int R>
 int launch_backward_transforms(swconv_plan* pl, const LaunchTarget& to, int which, const float* dout,
-                                      float* din) {
+                                      float* din, float* dvals_with_din = nullptr) {
   const Geometry& g = pl->g;
   if (which == 0) {  // dL/dZ = A dL/dO~ A^T into the M workspace
     auto kern = output_grad_transform_kernel<M, R>;
@@ -1220,16 +1230,28 @@ int launch_backward_transforms(swconv_plan* pl, const LaunchTarget& to, int whic
   if constexpr ((M + R - 2) / M == 1) {  // the other plans have no grad_images_per_group
     if (which == 1 && pl->grad_images_per_group > 0) {  // both remaining steps at once, planes in LDS
       const int G = pl->grad_images_per_group;
-      const size_t lds = (size_t)4 * (((size_t)G * g.H * g.W + 63) / 64 * 64 + 64) * sizeof(float);
-      auto kern = G * g.tpi > 64 ? input_grad_kernel<M, R, true> : input_grad_kernel<M, R, false>;
-      static bool attr_set = false;
-      if (!attr_set) {
-        for (const void* k : {(const void*)input_grad_kernel<M, R, true>, (const void*)input_grad_kernel<M, R, false>})
-          HIP_TRY(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes));
-        attr_set = true;
-      }
-      return launch_kernel(kern, dim3((g.N + G - 1) / G, (g.C + 3) / 4), dim3(256), lds, to, (const float*)pl->dD, din,
-                           (const GradTile*)pl->d_gtiles, G, g);
+      auto launch = [&](auto prefetch, auto sums) -> int {
+        auto kern = input_grad_kernel<M, R, decltype(prefetch)::value, decltype(sums)::value>;
+        static bool attr_set = false;
+        if (!attr_set) {
+          HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes));
+          attr_set = true;
+        }
+        const unsigned groups = (unsigned)((g.N + G - 1) / G);
+        PartialSums s{};
+        unsigned rows = (unsigned)((g.C + 3) / 4);
+        if (decltype(sums)::value) {
+          s = partial_sums(pl, dvals_with_din);
+          const unsigned blocks = (s.n_entries + kReduceThreads - 1) / kReduceThreads;
+          rows += (blocks + groups - 1) / groups;
+        }
+        return launch_kernel(kern, dim3(groups, rows), dim3(256), input_grad_lds(pl), to, (const float*)pl->dD, din,
+                             (const GradTile*)pl->d_gtiles, G, g, s);
+      };
+      using std::false_type;
+      using std::true_type;
+      if (G * g.tpi > 64) return launch(true_type{}, false_type{});
+      return dvals_with_din ? launch(false_type{}, true_type{}) : launch(false_type{}, false_type{});
     }
   }
   if (which == 1)  // dL/dI~ = B dL/dI_F B^T, from the dL/dI_F workspace into the V workspace
@@ -1271,8 +1293,22 @@ int backward_ready(swconv_plan* pl, hipStream_t st, const float* in_dev, const f
   return dvals_dev ? prepare_weight_grad(pl) : SWCONV_OK;
 }
 
+// Whether the launch of stage 5 does the work of stage 3 as well: where the one-kernel input gradient makes one pass of
+// 64 tiles its workgroups hold at most 18 KB of LDS, so that as many of the sums' workgroups share a CU as by themselves.
+// Both then take little more than the longer of them (64 x 13 x 13, 384 -> 384: 11.4 + 15.8 -> 24.1 us; 32 x 13 x 13,
+// 256 -> 384: 6.9 + 7.2 -> 10.3; F(4x4,5x5), 32 x 27 x 27, 48 -> 128: 4.5 + 10.6 -> 11.8).  The kernels of several passes leave room for two or three workgroups a CU, which a
+// sum of 120 MB would be slower with.
+bool sums_with_input_grad(const swconv_plan* pl, const float* in, const float* din, const float* dvals) {
+  const int G = pl->grad_images_per_group;
+  if (!backward_stage_runs(pl, 3, in, din, dvals) || !backward_stage_runs(pl, 5, in, din, dvals)) return false;
+  if (G < 1 || G * pl->g.tpi > 64) return false;
+  const int64_t groups = (pl->g.N + G - 1) / G, blocks = ((int64_t)pl->bt.n_pairs + kReduceThreads - 1) / kReduceThreads;
+  return (pl->g.C + 3) / 4 + (blocks + groups - 1) / groups < 65536;  // gridDim.y
+}
+
+// `together`: stage 5 with stage 3 (sums_with_input_grad).
 int launch_backward_stage(swconv_plan* pl, const LaunchTarget& to, int stage, const float* in_dev,
-                          const float* dout_dev, float* din_dev, float* dvals_dev) {
+                          const float* dout_dev, float* din_dev, float* dvals_dev, bool together = false) {
   if (!backward_stage_runs(pl, stage, in_dev, din_dev, dvals_dev)) return SWCONV_OK;
   switch (stage) {
     case 0:
@@ -1284,15 +1320,15 @@ int launch_backward_stage(swconv_plan* pl, const LaunchTarget& to, int stage, co
       return launch_spmm<true>(pl, pl->bt, to,
                                SpmmArgs{pl->dM, pl->g.m_bytes, pl->dD, pl->g.v_bytes, pl->dV, pl->d_partial});
     case 3: {
-      const uint32_t n_entries = (uint32_t)pl->bt.n_pairs;
-      return launch_kernel(weight_grad_reduce_kernel, dim3((n_entries + 255) / 256), dim3(256), 0, to,
-                           (const float*)pl->d_partial, pl->n_tau_blocks, n_entries,
-                           (const int32_t*)pl->bt.d_index, n_entries, dvals_dev);
+      if (together) return SWCONV_OK;
+      const PartialSums sums = partial_sums(pl, dvals_dev);
+      return launch_kernel(weight_grad_reduce_kernel, dim3((sums.n_entries + kReduceThreads - 1) / kReduceThreads),
+                           dim3(kReduceThreads), 0, to, sums);
     }
     case 4: return launch_product(pl, pl->bt, to, pl->dM, pl->g.m_bytes, pl->dD, pl->g.v_bytes);
     default:
       return dispatch_mr(pl, [&](auto M, auto R) {
-        return launch_backward_transforms<M(), R()>(pl, to, stage - 4, nullptr, din_dev);
+        return launch_backward_transforms<M(), R()>(pl, to, stage - 4, nullptr, din_dev, together ? dvals_dev : nullptr);
       });
   }
 }
@@ -1625,9 +1661,10 @@ int swconv_backward(swconv_plan* pl, void* hip_stream, const float* in_dev, cons
                     float* dvals_dev) {
   int rc = backward_ready(pl, (hipStream_t)hip_stream, in_dev, dout_dev, dvals_dev);
   if (rc) return rc;
+  const bool together = sums_with_input_grad(pl, in_dev, din_dev, dvals_dev);
   for (int stage = 0; stage < kBackwardStages; ++stage)
     if ((rc = launch_backward_stage(pl, LaunchTarget{(hipStream_t)hip_stream, nullptr, nullptr}, stage, in_dev,
-                                    dout_dev, din_dev, dvals_dev)))
+                                    dout_dev, din_dev, dvals_dev, together)))
       return rc;
   pl->ran_forward = false;  // the V workspace no longer holds I_F
   pl->ran_backward = true;
@@ -1795,15 +1832,21 @@ int swconv_update_values(swconv_plan* pl, void* hip_stream, const float* vals_de
   int rc;
   if ((rc = ensure_index(&pl->fw))) return rc;  // the pair -> CSR index map of W_F
   const LaunchTarget to{(hipStream_t)hip_stream, nullptr, nullptr};
+  RefreshStreams s{};
+  int n = 0;
+  uint32_t blocks = 0;
   auto refresh = [&](uint32_t* pairs, const int32_t* index, size_t n_pairs) {
-    return launch_kernel(refresh_values_kernel, dim3((unsigned)((n_pairs + 255) / 256)), dim3(256), 0, to, pairs, index,
-                         (uint32_t)n_pairs, vals_dev);
+    s.pairs[n] = pairs;
+    s.index[n] = index;
+    s.n_pairs[n] = (uint32_t)n_pairs;
+    s.first_block[n++] = blocks;
+    blocks += (unsigned)((n_pairs + 255) / 256);
   };
-  if ((rc = refresh(pl->fw.d_stream, pl->fw.d_index, pl->fw.n_pairs))) return rc;
-  if (pl->fz.ready && (rc = refresh(pl->fz.d_wpk, pl->fz.d_value_index, pl->fz.n_dwords / 2))) return rc;
-  if (pl->bt_current && pl->bt.on_device &&
-      (rc = refresh(pl->bt.d_stream, pl->bt.d_index, pl->bt.n_pairs)))
-    return rc;
+  refresh(pl->fw.d_stream, pl->fw.d_index, pl->fw.n_pairs);
+  if (pl->fz.ready) refresh(pl->fz.d_wpk, pl->fz.d_value_index, pl->fz.n_dwords / 2);
+  if (pl->bt_current && pl->bt.on_device) refresh(pl->bt.d_stream, pl->bt.d_index, pl->bt.n_pairs);
+  while (n <= kRefreshStreams) s.first_block[n++] = blocks;
+  if ((rc = launch_kernel(refresh_values_kernel, dim3(blocks), dim3(256), 0, to, s, vals_dev))) return rc;
   pl->host_values_stale = true;
   return SWCONV_OK;
 }

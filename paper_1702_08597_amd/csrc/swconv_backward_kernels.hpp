@@ -173,6 +173,41 @@ __global__ __launch_bounds__(256) void input_grad_gather_kernel(const float* __r
 }
 
 // ---------------------------------------------------------------------------------------------
+// Eq. 5, second line, last step: the per-tile-block partial sums of every stream entry (written by
+// the sparse kernel with DOTS) are added over the tile blocks, in ascending order, and go to
+// the entry's place in the caller's CSR order; padding entries (index -1) are skipped.
+struct PartialSums {
+  const float* partial;
+  int n_tau_blocks;
+  uint32_t stride;             // floats between tile blocks
+  const int32_t* entry_index;
+  uint32_t n_entries;
+  float* dvals;
+};
+constexpr int kReduceThreads = 256;
+__device__ __forceinline__ void reduce_partial_sums(const PartialSums& s, uint32_t block) {
+  const uint32_t e = block * (uint32_t)kReduceThreads + threadIdx.x;
+  if (e >= s.n_entries) return;
+  const int32_t q = s.entry_index[e];
+  if (q < 0) return;
+  // eight loads in flight, added in ascending order of the tile block
+  float sum = 0.0f;
+  int tb = 0;
+  for (; tb + 8 <= s.n_tau_blocks; tb += 8) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = s.partial[(size_t)(tb + u) * s.stride + e];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) sum += v[u];
+  }
+  for (; tb < s.n_tau_blocks; ++tb) sum += s.partial[(size_t)tb * s.stride + e];
+  s.dvals[q] = sum;
+}
+__global__ __launch_bounds__(kReduceThreads) void weight_grad_reduce_kernel(PartialSums s) {
+  reduce_partial_sums(s, blockIdx.x);
+}
+
+// ---------------------------------------------------------------------------------------------
 // Eq. 6, second and third line in one kernel, for images whose planes fit LDS: no patch buffer.
 // A wave owns one input channel and a group of G whole images (G = 64 / tiles per image, at least
 // 1), whose planes it builds up in LDS.  In passes of 64 consecutive tiles every lane reads the t*t
@@ -192,15 +227,22 @@ __global__ __launch_bounds__(256) void input_grad_gather_kernel(const float* __r
 // t^2 registers that groups of one pass spend on more waves per SIMD.  F(4x4,5x5), with 64 values per lane, spills 53
 // to 56 scalar registers into vector lanes (nothing goes to memory).
 // Block = 4 waves = 4 channels of the same image group.
+// SUMS: the workgroups behind those of the channels (blockIdx.y from ceil(C / 4) on) add up the weight gradient's partial
+// sums instead, which the kernel in front of this one has left too: one launch and its ramp less.
 struct GradTile {
   int32_t org;  // float offset of pixel (0, 0) of the tile's image inside the wave's LDS area
   int32_t yx0;  // as TileInfo::yx0; y0 = x0 = -32768 for tiles past the last image
 };
 
-template <int M, int R, bool PREFETCH>
+template <int M, int R, bool PREFETCH, bool SUMS>
 __global__ __launch_bounds__(256) void input_grad_kernel(const float* __restrict__ dV, float* __restrict__ din,
                                                          const GradTile* __restrict__ gtiles, int images_per_group,
-                                                         const Geometry g) {
+                                                         const Geometry g, const PartialSums sums) {
+  static_assert(kReduceThreads == 256, "the sums' workgroups are this kernel's");
+  if constexpr (SUMS) {
+    const uint32_t channel_wgs = (uint32_t)(g.C + 3) / 4u;
+    if (blockIdx.y >= channel_wgs) return reduce_partial_sums(sums, (blockIdx.y - channel_wgs) * gridDim.x + blockIdx.x);
+  }
   constexpr int t = Wino<M, R>::t;
   constexpr int ov = t - M;  // columns (rows) that a patch shares with the next one
   static_assert(ov <= M, "a patch reaches no further than its neighbour");
@@ -317,32 +359,6 @@ __global__ __launch_bounds__(256) void input_grad_kernel(const float* __restrict
         buffer_store_f32<SWCONV_AUX_OUT>(dst, lane * 4u, e0 * 4u, from[min(e0 + lane, plane - 1)]);
     }
   }
-}
-
-// ---------------------------------------------------------------------------------------------
-// Eq. 5, second line, last step: the per-tile-block partial sums of every stream entry (written by
-// the sparse kernel with DOTS) are added over the tile blocks, in ascending order, and go to
-// the entry's place in the caller's CSR order; padding entries (index -1) are skipped.
-__global__ __launch_bounds__(256) void weight_grad_reduce_kernel(const float* __restrict__ partial, int n_tau_blocks,
-                                                                 uint32_t partial_stride,
-                                                                 const int32_t* __restrict__ entry_index,
-                                                                 uint32_t n_entries, float* __restrict__ dvals) {
-  const uint32_t e = blockIdx.x * 256u + threadIdx.x;
-  if (e >= n_entries) return;
-  const int32_t q = entry_index[e];
-  if (q < 0) return;
-  // eight loads in flight, added in ascending order of the tile block
-  float sum = 0.0f;
-  int tb = 0;
-  for (; tb + 8 <= n_tau_blocks; tb += 8) {
-    float v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = partial[(size_t)(tb + u) * partial_stride + e];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) sum += v[u];
-  }
-  for (; tb < n_tau_blocks; ++tb) sum += partial[(size_t)tb * partial_stride + e];
-  dvals[q] = sum;
 }
 
 }  // namespace swconv
