@@ -110,12 +110,14 @@ int swconv_set_weights(swconv_plan* plan, const int32_t* rowptr, const int32_t* 
 /*
  * Forward pass of Eq. 4 with the sparse weights: three kernels (Section 5's steps 1-3)
  * enqueued on `hip_stream` (a hipStream_t; NULL = the default stream).  Asynchronous: returns
- * after enqueueing, does not synchronise.  For m = 2 layers with at most 128 input channels
- * whose rows have at most 32 stored entries (the 5x5 layer of Section 6) steps 2 and 3 run as
+ * after enqueueing, does not synchronise.  For m = 2 layers
+ * whose rows have at most 48 stored entries (the 5x5 layer of Section 6) steps 2 and 3 run as
  * ONE kernel that keeps the per-position products on chip (Section 5: a core that owns its
- * tiles through all steps can fuse the second and third); the environment variable
- * SWCONV_FUSE_OUTPUT=0, read by swconv_plan_create, keeps such a plan on three kernels.
- * SWCONV_FUSE_OUTPUT=2 also runs F(4x4,3x3) layers with C a multiple of 4, C <= 256 and rows of
+ * tiles through all steps can fuse the second and third), where that is the faster way by the number
+ * of tiles and stored entries; the results are the same bits either way.  The environment variable
+ * SWCONV_FUSE_OUTPUT=0, read by swconv_plan_create, keeps such a plan on three kernels;
+ * SWCONV_FUSE_OUTPUT=2 runs the one kernel whatever the sizes,
+ * and also runs F(4x4,3x3) layers with C a multiple of 4, C <= 256 and rows of
  * at most 224 stored entries through a fused kernel of their own (measured slower than the two
  * kernels on the layers tried, hence not the default).
  *   in_dev   DEVICE, N x C x H x W fp32, contiguous (W fastest), read-only.

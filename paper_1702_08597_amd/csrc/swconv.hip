@@ -152,7 +152,8 @@ struct PackedMatrix {
 // their natural order, 64 per workgroup, one package of 16-step batches per position.
 struct FusedProduct {
   int out_tile = 0;       // m of the kernel that would run: 2 (product_output_kernel) or 4 (product_output4_kernel)
-  bool eligible = false;  // the layer shape allows the kernel, and it pays or was asked for
+  bool eligible = false;  // the layer shape allows the kernel; m = 4: and it was asked for
+  bool always = false;    // m = 2: wherever the kernel can run
   bool ready = false;     // the current weights fit its format and are on the device
   int KC = 0;             // row chunks of kFusedRows
   int B = 0;              // batches per slice and position (the longest row decides)
@@ -379,30 +380,34 @@ int launch_product(const swconv_plan* pl, const PackedMatrix& pm, const LaunchTa
   return launch_spmm<false>(pl, pm, to, SpmmArgs{X, x_bytes, Y, y_bytes, nullptr, nullptr});
 }
 
-template <int R, int PP>
+template <int R, int NW, int B>
 int launch_product_output_t(const swconv_plan* pl, const LaunchTarget& to, const float* V, float* out) {
   const FusedProduct& fz = pl->fz;
   const Geometry& g = pl->g;
-  const size_t lds = (size_t)2 * ((size_t)g.C * kTileBlock * sizeof(float) + (size_t)kFusedWaves * fz.B * 512) + 1024;
-  auto kern = product_output_kernel<R, PP>;
-  static bool attr_set = false;
-  if (!attr_set) {
-    HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes));
-    attr_set = true;
-  }
-  const int n_wgs = pl->n_tau_blocks * fz.KC;
-  return launch_kernel(kern, dim3(n_wgs), dim3(kFusedWaves * 64), lds, to, V, out,
-                       (const uint32_t*)fz.d_wpk, (uint32_t)(fz.n_dwords * sizeof(uint32_t)),
-                       (const uint8_t*)fz.d_lens, (const OutTile*)fz.d_otiles, g.C, g.K, g.Tp, fz.KC, fz.B, n_wgs,
+  const int n_slices = (g.K + kSliceRows - 1) / kSliceRows;
+  return launch_kernel(product_output_kernel<R, NW, B>, dim3((unsigned)(pl->n_tau_blocks * n_slices)), dim3(NW * 64), 0, to,
+                       V, out, (const uint32_t*)fz.d_wpk, (uint32_t)(fz.n_dwords * sizeof(uint32_t)),
+                       (const uint8_t*)fz.d_lens, (const OutTile*)fz.d_otiles, g.C, g.K, g.Tp, fz.KC, n_slices,
                        g.v_bytes, (uint32_t)(g.Ho * g.Wo), g.Wo, (uint32_t)g.out_image_stride,
                        (uint32_t)((int64_t)g.N * g.out_image_stride * (int64_t)sizeof(float)));
 }
 
 int launch_product_output(const swconv_plan* pl, const LaunchTarget& to, const float* V, float* out) {
-  const bool one_piece = pl->g.C * (kTileBlock / 4) <= kFusedWaves * 64;
-  if (pl->r == 3)
-    return one_piece ? launch_product_output_t<3, 1>(pl, to, V, out) : launch_product_output_t<3, 2>(pl, to, V, out);
-  return one_piece ? launch_product_output_t<5, 1>(pl, to, V, out) : launch_product_output_t<5, 2>(pl, to, V, out);
+  // F(2x2,3x3), 16 positions: two to a wave, or one where there is at most one workgroup for each CU anyway (one image of
+  // 13 x 13, 256 -> 384: 6.9 against 8.0 us)
+  const bool one_each = (int64_t)pl->n_tau_blocks * ((pl->g.K + kSliceRows - 1) / kSliceRows) <= pl->fw.cus;
+  auto with = [&](auto b) {
+    constexpr int B = decltype(b)::value;
+    return pl->r == 5 ? launch_product_output_t<5, 12, B>(pl, to, V, out)
+           : one_each ? launch_product_output_t<3, 16, B>(pl, to, V, out)
+                      : launch_product_output_t<3, 8, B>(pl, to, V, out);
+  };
+  using std::integral_constant;
+  switch (pl->fz.B) {
+    case 1: return with(integral_constant<int, 1>{});
+    case 2: return with(integral_constant<int, 2>{});
+    default: return with(integral_constant<int, kGatherMaxBatches>{});
+  }
 }
 
 template <int G>
@@ -512,6 +517,18 @@ void build_transform_tables(swconv_plan* pl) {
   }
 }
 
+// Whether steps 2 and 3 of an m = 2 layer take less time as product_output_kernel, whose time grows with what it reads - 256
+// bytes a non-zero and tile block, 85 us a GB - than as two kernels, which write and read M: 0.4 us a MB while the
+// Infinity Cache holds it and V, about twice that beyond, and a launch.  Measured (reads / M in MB, us a forward pass as
+// two and as three kernels): F(2x2,5x5), 48 -> 128, 27 x 27: 1 image 17 / 3.4 10.5 and 13.6, 8 129 / 28 23.7 and 26.5, 16 254 / 55
+// 36.2 and 36.3, 32 502 / 110 54.1 and 59.8, 64 1000 / 220 97 and 165; F(2x2,3x3), 27 x 27, 64 -> 128: 8 82 / 12 15.7 and
+// 20.7, 32 317 / 49 38.1 and 36.9; 13 x 13, 128 -> 384: 64 960 / 74 70 and 48; 256 -> 384: 1 67 / 1 11.5 and 12.5, 4 155 / 5
+// 17.8 and 16.2; 64 of 56 x 56, 64 -> 64: 1256 / 196 153 and 219; 32 -> 32 at 20 %: 628 / 98 66 and 93.
+bool gather_pays(const swconv_plan* pl) {
+  const double mb = 1 << 20, reads = (double)pl->fw.nnz * pl->n_tau_blocks * 256.0 / mb, m = pl->g.m_bytes / mb;
+  return reads <= (m >= 96 ? 8 * m : 100 + 2.5 * m);
+}
+
 // Sizes of W_F's package format for the fused kernel; false (and the three-kernel path runs) when the layer is
 // not eligible or a row is longer than the kernel's batches hold.
 bool size_fused(swconv_plan* pl, int longest_row) {
@@ -520,8 +537,12 @@ bool size_fused(swconv_plan* pl, int longest_row) {
   const bool units = fz.out_tile == 4;  // F(4x4,3x3): whole units of two batches
   fz.KC = (pl->g.K + kFusedRows - 1) / kFusedRows;
   fz.B = std::max(1, (longest_row + kBatchSteps - 1) / kBatchSteps);
-  if (units) fz.B = (fz.B + 1) / 2 * 2;
-  if (fz.B > (units ? kFused4MaxBatches : kFusedMaxBatches)) return false;
+  if (units) {
+    fz.B = (fz.B + 1) / 2 * 2;
+    if (fz.B > kFused4MaxBatches) return false;
+  } else if (fz.B > kGatherMaxBatches || !(fz.always || gather_pays(pl))) {
+    return false;
+  }
   fz.n_dwords = (size_t)pl->P * fz.KC * fz.B * kFusedWaves * 128;
   return fz.n_dwords * 4 < ((size_t)1 << 32) - 4096;
 }
@@ -1468,8 +1489,7 @@ int swconv_plan_create(swconv_plan** out, int N, int C, int H, int W, int K, int
   g.m_shift = m == 4 ? 2 : 1;
   g.in_image_stride = (int64_t)C * H * W;
   g.out_image_stride = (int64_t)K * Ho * Wo;
-  // steps 2 and 3 in one kernel: m = 2 (16 output accumulators per lane) and a panel of at most
-  // kFusedMaxPieces 16-byte pieces per thread
+  // steps 2 and 3 in one kernel: m = 2, rows that fit the packages, and where it pays (gather_pays: the weights decide),
   // or F(4x4,3x3) with two C x 64 panels in LDS and whole groups of four panel rows.
   // SWCONV_FUSE_OUTPUT: 0 never, 1 where it pays (m = 2), 2 wherever a kernel can run.  The F(4x4,3x3) kernel runs only
   // where asked for: with 64 + 16 accumulators per lane it holds 16 waves per CU, its vector ALU stays at about two
@@ -1478,10 +1498,12 @@ int swconv_plan_create(swconv_plan** out, int N, int C, int H, int W, int K, int
   // values and of every new pattern on layers of 256 channels.
   const int fuse_mode = env_int("SWCONV_FUSE_OUTPUT", 1);
   pl->fz.out_tile = m;
-  if (m == 2)
-    pl->fz.eligible = C * (kTileBlock / 4) <= kFusedMaxPieces * kFusedWaves * 64 && fuse_mode != 0;
-  else
+  if (m == 2) {
+    pl->fz.eligible = fuse_mode != 0;
+    pl->fz.always = fuse_mode == 2;
+  } else {
     pl->fz.eligible = r == 3 && C % 4 == 0 && C <= kFused4MaxC && fuse_mode == 2;  // and its staging area, see below
+  }
   try {
     if (pl->fz.eligible && m == 2) pl->fz.otiles.assign((size_t)g.Tp, OutTile{0, 0u, 0u, 0u});
     build_transform_tables(pl);

@@ -400,48 +400,13 @@ __device__ __forceinline__ void quarter_fma(Acc4& acc, uint32_t bw, const f32x4_
 #undef SWCONV_QFMA
 }
 
-// The four panel reads of steps G*kStepGroup .. +kStepGroup-1 of the batch whose row offsets are in
-// boff, issued back to back.
+// Four steps' reads.
 struct Group4 {
   f32x4_t x0, x1, x2, x3;
 };
-template <int G>
-__device__ __forceinline__ Group4 quarter_reads(const float* panel, uint32_t lane_sub, uint32_t boff) {
-  constexpr int I0 = G * kStepGroup;
-  static_assert(kStepGroup == 4, "four steps per group");
-  const char* base = reinterpret_cast<const char*>(panel);
-  Group4 g;
-  g.x0 = *reinterpret_cast<const f32x4_t*>(base + (quarter_bcast<I0 + 0>(boff) + lane_sub));
-  g.x1 = *reinterpret_cast<const f32x4_t*>(base + (quarter_bcast<I0 + 1>(boff) + lane_sub));
-  g.x2 = *reinterpret_cast<const f32x4_t*>(base + (quarter_bcast<I0 + 2>(boff) + lane_sub));
-  g.x3 = *reinterpret_cast<const f32x4_t*>(base + (quarter_bcast<I0 + 3>(boff) + lane_sub));
-  return g;
-}
 
-// Steps G*kStepGroup .. +kStepGroup-1 of the batch held in (boff, bw): the reads, then the FMAs as
-// the data arrives.
-template <int G>
-__device__ __forceinline__ void quarter_group(const float* panel, uint32_t lane_sub, uint32_t boff, uint32_t bw,
-                                              Acc4& acc) {
-  constexpr int I0 = G * kStepGroup;
-  const Group4 g = quarter_reads<G>(panel, lane_sub, boff);
-  quarter_fma<I0 + 0, true>(acc, bw, g.x0);
-  quarter_fma<I0 + 1, false>(acc, bw, g.x1);
-  quarter_fma<I0 + 2, false>(acc, bw, g.x2);
-  quarter_fma<I0 + 3, false>(acc, bw, g.x3);
-}
-
-// The first `steps` (a positive multiple of kStepGroup, wave-uniform) steps of one batch.
-__device__ __forceinline__ void quarter_batch(const float* panel, uint32_t lane_sub, const u32x2_t& b, int steps,
-                                              Acc4& acc) {
-  quarter_group<0>(panel, lane_sub, b.x, b.y, acc);
-  if (steps > 1 * kStepGroup) quarter_group<1>(panel, lane_sub, b.x, b.y, acc);
-  if (steps > 2 * kStepGroup) quarter_group<2>(panel, lane_sub, b.x, b.y, acc);
-  if (steps > 3 * kStepGroup) quarter_group<3>(panel, lane_sub, b.x, b.y, acc);
-}
-
-// The rolling unit of the inner loop (see swconv_rolling_unit.inc): the same steps as quarter_batch over
-// two batches, as one pipeline with four reads always in flight, in assembly with the sixteen registers
+// The rolling unit of the inner loop (see swconv_rolling_unit.inc): the steps of
+// two batches as one pipeline with four reads always in flight, in assembly with the sixteen registers
 // of those reads fixed: v[112:127], the top of the 128 registers of the fused F(4x4,3x3) kernel, whose
 // other registers are full of accumulators, so that it has none for the broadcasts of the matrix unit.
 constexpr int kUnitSteps = 2 * kBatchSteps;
