@@ -1406,19 +1406,25 @@ int set_weights_through_host(swconv_plan* pl, void* hip_stream, const int32_t* r
   }
 }
 
-// Whether dL/dI_F -> dL/dI runs as one kernel (input_grad_kernel) where that kernel can run.  With 3x3 filters: always.
-// F(4x4,5x5): a pass over 64 tiles is a chain of about 5 us there (64 values per lane, fetched and transformed), the
-// workgroups' passes come one after the other, and an image has as many as its tiles need; the patch and gather kernels
-// take 8 us at least and grow with the whole.  Images of one pass always gain (1 of 13 x 13, 16 channels: 5.9 us
-// against 8.4; 64 of 27 x 27: 8.2 against 14.9), the others where enough workgroups share the chain: 8 of 40 x 40 with
-// 48 channels (2 passes, 96 workgroups) 12.1 against 14.5, 16 of 64 x 64 with 64 (4, 256) 24.3 against 36.1, 32 of
-// 80 x 80 with 32 (7, 256) 45.6 against 68.0; but 2 of 40 x 40 with 64 (2, 32) 11.7 against 9.3, 16 of 64 x 64 with 32
-// (4, 128) 22.1 against 20.6, 8 of 72 x 72 with 64 (6, 128) 32.8 against 25.6, 1 of 96 x 96 with 16 (9, 4) 46.6 against 9.4.
+// Whether dL/dI_F -> dL/dI runs as one kernel (input_grad_kernel) where that kernel can run.  A workgroup's passes over 64
+// tiles come one after the other, and an image has as many as its tiles need; the patch and gather kernels take 8 us at
+// least and grow with the whole.  So: images of few passes, and others where enough workgroups share the chain.
+// 3x3 filters: a pass is a chain of 1.2 us with m = 2, of 2.7 us with m = 4.  Whole fine-tuning steps, one kernel against
+// two (passes, workgroups), in us: F(2x2,3x3) 4, 4 25.8 and 28.6; 5, 32 43.3 and 42.1; 6, 60 73.4 and 72.7; 7, 64 40.6 and
+// 41.5; 13, 16 40.4 and 30.5; 13, 64 48.2 and 48.5; 16, 64 49.0 and 48.1; 16, 128 69.8 and 75.7; F(4x4,3x3) 2, 4 31.0 and
+// 31.6; 3, 4 33.2 and 32.1; 3, 64 51.5 and 54.0; 4, 16 39.0 and 35.4; 4, 63 71.4 and 70.7; 4, 64 47.6 and 47.6; 4, 128 54.0
+// and 60.9.  (At three passes with m = 4 few workgroups lose 1 us and many gain 2.5: the line is above them.)
+// F(4x4,5x5): a pass is a chain of about 5 us (64 values per lane, fetched and transformed).  The kernels alone, in us:
+// images of one pass always gain (1 of 13 x 13, 16 channels: 5.9 against 8.4; 64 of 27 x 27: 8.2 against 14.9), the others
+// where enough workgroups share the chain: 8 of 40 x 40 with 48 channels (2 passes, 96 workgroups) 12.1 against 14.5, 16 of
+// 64 x 64 with 64 (4, 256) 24.3 against 36.1, 32 of 80 x 80 with 32 (7, 256) 45.6 against 68.0; but 2 of 40 x 40 with 64
+// (2, 32) 11.7 against 9.3, 16 of 64 x 64 with 32 (4, 128) 22.1 against 20.6, 8 of 72 x 72 with 64 (6, 128) 32.8 against
+// 25.6, 1 of 96 x 96 with 16 (9, 4) 46.6 against 9.4.
 bool one_input_grad_kernel_pays(const swconv_plan* pl, int images_per_group) {
-  if (pl->r == 3) return true;
   const Geometry& g = pl->g;
   const int64_t passes = ((int64_t)images_per_group * g.tpi + 63) / 64;
   const int64_t wgs = (int64_t)((g.N + images_per_group - 1) / images_per_group) * ((g.C + 3) / 4);
+  if (pl->r == 3) return passes <= (pl->m == 2 ? 4 : 3) || wgs >= std::max<int64_t>(64, 5 * passes);
   return passes == 1 || wgs >= std::min<int64_t>(48 * passes, 192);
 }
 
