@@ -247,7 +247,7 @@ int swconv_update_values(swconv_plan* plan, void* hip_stream, const float* vals_
  *             third value is the whole time of the kernel that makes both, and the fifth, which is
  *             then no part of a pass, what the transposed product takes by itself: it is launched
  *             `iters` times more behind the passes.  Where the image
- *             planes fit LDS (3x3 filters, and F(4x4,5x5) where it pays: images of at most 64 tiles, or
+ *             planes fit LDS (3x3 filters and F(4x4,5x5), where it pays: images of few tiles, or
  *             enough images and channels) the last two run as one kernel that keeps no patch
  *             buffer: the sixth value is its time and the seventh is 0 (the environment
  *             variable SWCONV_FUSE_INPUT_GRAD, read by swconv_plan_create: 0 keeps two kernels, 2 takes
