@@ -753,6 +753,7 @@ void build_schedule(PackedMatrix* pm, int P, int ntb) {
     h.item_begin = pm->wg_begin[b];
     h.item_end = pm->wg_begin[b + 1];
     h.first = pm->items[h.item_begin];
+    h.second_slice = pm->items[std::min(h.item_begin + 1, h.item_end - 1)].slice_begin;
   }
   pm->n_items = (int)pm->items.size();
   pm->max_item = heaviest_range(pm->slices, pm->items, pm->wg_begin);
@@ -977,8 +978,9 @@ int check_schedule(const PackedMatrix& pm, int P, int ntb, bool with_stats) {
     std::vector<Slice> slices(pm.slices);
     std::vector<WorkItem> items(pm.items);
     std::vector<int32_t> wg_begin(pm.wg_begin);
+    std::vector<RangeHeader> ranges(pm.ranges);
     if (!pm.host_current) {
-      std::vector<RangeHeader> ranges((size_t)pm.n_wgs_used);
+      ranges.resize((size_t)pm.n_wgs_used);
       slices.resize((size_t)pm.n_slices);
       HIP_TRY(hipDeviceSynchronize());
       HIP_TRY(hipMemcpy(slices.data(), pm.d_slices, slices.size() * sizeof(Slice), hipMemcpyDeviceToHost));
@@ -993,6 +995,12 @@ int check_schedule(const PackedMatrix& pm, int P, int ntb, bool with_stats) {
       HIP_TRY(hipMemcpy(items.data(), pm.d_items, items.size() * sizeof(WorkItem), hipMemcpyDeviceToHost));
     }
     if (!is_partition(pm, P, ntb, items, wg_begin)) return SWCONV_EINVAL;
+    for (const RangeHeader& h : ranges) {  // what a workgroup starts from says the same as the list
+      const WorkItem &w = items[h.item_begin], &second = items[std::min(h.item_begin + 1, h.item_end - 1)];
+      if (h.first.p != w.p || h.first.tau_block != w.tau_block || h.first.slice_begin != w.slice_begin ||
+          h.first.slice_end != w.slice_end || h.second_slice != second.slice_begin)
+        return SWCONV_EINVAL;
+    }
     if (with_stats) {
       int64_t padded = 0;
       for (const Slice& sl : slices) padded += (int64_t)sl.len * kSliceRows;

@@ -113,11 +113,12 @@ struct WorkItem {
 };
 
 // What a persistent workgroup needs to start, in one 32-byte scalar load: its range of work
-// items and the first of them.
+// items, the first of them and where the slices of the second begin.
 struct RangeHeader {
   int32_t item_begin, item_end;  // indices into the work-item list; never empty for a launched workgroup
   WorkItem first;                // = items[item_begin]
-  int32_t pad[2];
+  int32_t second_slice;          // slice_begin of the item behind it, or its own where there is none
+  int32_t pad;
 };
 
 constexpr int kSliceRows = 4;    // rows per slice = quarters of a wave
@@ -579,7 +580,8 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 12 ? 6 : 4) void spmm_kernel
   const uint32_t piece_stride = (uint32_t)rows_per_piece * (uint32_t)Tp * 4u;
   // the panel's rows as a buffer of their own: what reaches past the last one reads 0 and touches no memory
   auto panel_rsrc = [&](const WorkItem& w) {
-    return make_rsrc(V + ((size_t)w.p * C * Tp + (size_t)w.tau_block * TB), ((uint32_t)(C - 1) * (uint32_t)Tp + TB) * 4u);
+    const uint32_t at = (uint32_t)w.p * ((uint32_t)C * (uint32_t)Tp) + (uint32_t)w.tau_block * TB;  // of less than 2^30 floats
+    return make_rsrc(V + at, ((uint32_t)(C - 1) * (uint32_t)Tp + TB) * 4u);
   };
   u32x4_t piece[PIECES], desc_piece;
   auto load_batch = [&](uint32_t byte_off) -> u32x2_t {
@@ -596,8 +598,8 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 12 ? 6 : 4) void spmm_kernel
   // The wave's first slice of an item, from the descriptors in memory (clamped: unconditional, in bounds).  Its four
   // channels are taken from scalar registers at once: left to itself the compiler loads each in a branch of its quarter,
   // three latencies one after the other in front of every item's barrier (forward passes of 32 x 13 x 13, 256 -> 384:
-  // 29.4 -> 28.1 us; 64 x 13 x 13, 384 -> 384: 73.2 -> 71.5; 64 x 20 x 20, 24 -> 48: 22.8 -> 22.2).
-  auto first_index = [&](const WorkItem& w) { return min(w.slice_begin + wave, n_slices - 1); };
+  // 29.4 -> 28.1 us; 64 x 13 x 13, 384 -> 384: 73.2 -> 71.5).
+  auto first_index = [&](int slice_begin) { return min(slice_begin + wave, n_slices - 1); };
   auto take_slice = [&](const Slice& sl) -> Cur {
     int k0 = sl.k[0], k1 = sl.k[1], k2 = sl.k[2], k3 = sl.k[3];
     asm volatile("" : "+s"(k0), "+s"(k1), "+s"(k2), "+s"(k3));
@@ -629,12 +631,20 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 12 ? 6 : 4) void spmm_kernel
   // its first two batches, which arrive right behind the panel.
   WorkItem it = hdr.first;
   Cur cur;
-  cur.k = (int)__builtin_amdgcn_raw_buffer_load_b32(dr, quarter * 4 + 16, first_index(it) * (int)sizeof(Slice), 0);
+  {
+    const __amdgpu_buffer_rsrc_t first_panel = panel_rsrc(it);
 #pragma unroll
-  for (int g = 0; g < kGroups; ++g) request_group(g, it, panel_rsrc(it));
+    for (int g = 0; g < kGroups; ++g) request_group(g, it, first_panel);
+  }
+  cur.k = (int)__builtin_amdgcn_raw_buffer_load_b32(dr, quarter * 4 + 16, first_index(it.slice_begin) * (int)sizeof(Slice), 0);
+  // the scalar loads depend on the header only: one latency in front of the first batches and the first barrier
   WorkItem it_next = items[min(hdr.item_begin + 1, hdr.item_end - 1)];
-  cur.base = slices[first_index(it)].batch0 * 512u;
-  cur.len = slices[first_index(it)].len;
+  WorkItem it_after = items[min(hdr.item_begin + 2, hdr.item_end - 1)];
+  Slice next_slice = slices[first_index(hdr.second_slice)];
+  cur.base = slices[first_index(it.slice_begin)].batch0 * 512u;
+  cur.len = slices[first_index(it.slice_begin)].len;
+  asm volatile(""
+               : "+s"(cur.base), "+s"(cur.len), "+s"(it_next.slice_begin), "+s"(it_after.slice_begin), "+s"(next_slice.batch0));
   u32x2_t b0 = load_batch(cur.base), b1 = load_batch(cur.base + 512u);
   u32x2_t b2 = {0u, 0u}, b3 = {0u, 0u};
   if constexpr (kBatchRegs == 4) b2 = load_batch(cur.base + 1024u), b3 = load_batch(cur.base + 1536u);
@@ -646,6 +656,27 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 12 ? 6 : 4) void spmm_kernel
   f32x4_t z_cur = {0.0f, 0.0f, 0.0f, 0.0f};
   if constexpr (DOTS) z_cur = load_z(it.p, it.tau_block * TB, cur.k);
 
+  // The panel and the descriptors go to LDS.
+  auto stage_item = [&](int n_item_slices) {
+    const uint32_t tid = thread_index(), tid16 = tid * 16u;
+#pragma unroll
+    for (int u = 0; u < PIECES; ++u) {
+      if ((int)tid < C * (TB / 4) - u * NT) *lds_at<u32x4_t>(panel0 + tid16 + (uint32_t)u * (NT * 16u)) = piece[u];
+    }
+    if ((int)tid < 2 * n_item_slices) *lds_at<u32x4_t>(desc0 + tid16) = desc_piece;
+  };
+  // The first item's staging stands in front of the loop: a wait in a loop is as strict as its strictest way in, and
+  // inside it these writes also waited for the batches behind the pieces, in every first item (the second workgroup of a CU
+  // had its panel in LDS 3.0 us after the launch began instead of 2.2: 64 x 20 x 20, 24 -> 48 channels).
+  stage_item(it.slice_end - it.slice_begin);
+  // (used behind their conditional writes too, the pieces are asked for in front of them and not inside)
+#pragma unroll
+  for (int u = 0; u < PIECES; ++u) asm volatile("" ::"v"(piece[u]));
+  asm volatile("" ::"v"(desc_piece));
+  if (thread_index() == 0) *lds_at<int>(lds0) = 0;
+  Cur next_first = take_slice(next_slice);
+  __syncthreads();
+
   for (int item = hdr.item_begin;; ++item) {
     const int tau0 = it.tau_block * TB;
     const int n_item_slices = it.slice_end - it.slice_begin;
@@ -653,20 +684,7 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 12 ? 6 : 4) void spmm_kernel
     const __amdgpu_buffer_rsrc_t pr =
         make_rsrc(DOTS ? partial + (size_t)it.tau_block * partial_stride : nullptr, DOTS ? partial_stride * 4u : 0u);
     const bool has_next = item + 1 < hdr.item_end;
-    // scalar loads: they arrive while the panel is written
-    const WorkItem it_after = items[min(item + 2, hdr.item_end - 1)];
-    const Slice next_slice = slices[first_index(it_next)];
-    if (item != hdr.item_begin) __syncthreads();  // every wave is done with the previous panel and descriptors
-    const uint32_t tid = thread_index(), tid16 = tid * 16u;
-#pragma unroll
-    for (int u = 0; u < PIECES; ++u) {
-      if ((int)tid < C * (TB / 4) - u * NT) *lds_at<u32x4_t>(panel0 + tid16 + (uint32_t)u * (NT * 16u)) = piece[u];
-    }
-    if ((int)tid < 2 * n_item_slices) *lds_at<u32x4_t>(desc0 + tid16) = desc_piece;
-    Cur next_first = take_slice(next_slice);
     if (!has_next) next_first.base = 0xfffff000u;
-    if (tid == 0 && item == hdr.item_begin) *lds_at<int>(lds0) = 0;
-    __syncthreads();
 
     // Waves take slices dynamically, longest first: the first one by wave number, every further
     // one from a counter in LDS.  The next slice is drawn before the current one is computed.
@@ -744,23 +762,33 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 12 ? 6 : 4) void spmm_kernel
       z_cur = z_next;
       return more;
     };
-    bool more = wave < n_item_slices;
-    if (!more) {  // nothing to do here: on to the next item's first slice
+    auto skip_item = [&]() {  // nothing to do here: on to the next item's first slice
       cur = next_first;
       b0 = load_batch(cur.base);
       b1 = load_batch(cur.base + 512u);
       if constexpr (kBatchRegs == 4) b2 = load_batch(cur.base + 1024u), b3 = load_batch(cur.base + 1536u);
       if constexpr (DOTS) z_cur = load_z(it_next.p, it_next.tau_block * TB, cur.k);
-    }
+    };
+    bool more = wave < n_item_slices;
     const __amdgpu_buffer_rsrc_t next_panel = panel_rsrc(it_next);
     if constexpr (EARLY) {
+      if (!more) skip_item();
 #pragma unroll
       for (int g = 0; g < kGroups; ++g) {
         if (has_next) request_group(g, it_next, next_panel);
         if (more) more = run_slice();
       }
+      while (more) more = run_slice();
+    } else if (more) {
+      // The item's first batches have arrived: on the way round the loop the youngest request is then the row store of the
+      // slice before, and no slice waits for it (the wait in the loop was vmcnt(0) and is vmcnt(1); a write-through store
+      // takes 600 clocks).
+      __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+      while (run_slice()) {
+      }
+    } else {
+      skip_item();
     }
-    while (more) more = run_slice();
     if (!has_next) break;
     drawn_before += n_item_slices;  // a slice, a draw
     if constexpr (!EARLY) {
@@ -769,6 +797,13 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 12 ? 6 : 4) void spmm_kernel
     }
     it = it_next;
     it_next = it_after;
+    // scalar loads: they arrive while the panel is written
+    it_after = items[min(item + 3, hdr.item_end - 1)];
+    next_slice = slices[first_index(it_next.slice_begin)];
+    __syncthreads();  // every wave is done with the previous panel and descriptors
+    stage_item(it.slice_end - it.slice_begin);
+    next_first = take_slice(next_slice);
+    __syncthreads();
   }
 }
 

@@ -387,6 +387,7 @@ __device__ inline void cut_schedule(const ScheduleShape& s, const PackTables& t,
     for_items(cut[r], cut[r + 1], s, [&](int i, const WorkItem& w) {
       items[first + i] = w;
       if (i == 0) h.first = w;
+      if (i <= 1) h.second_slice = w.slice_begin;
     });
     ranges[r] = h;
   }
