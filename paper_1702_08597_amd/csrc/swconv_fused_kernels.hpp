@@ -4,6 +4,9 @@
 // 2 and 3 run fused, out of cache.  Here a workgroup has some rows of W_F (output channels) and one block of 64 tiles
 // through ALL positions: product_output_kernel four rows, for m = 2; product_output4_kernel 64, for F(4x4,3x3).
 #pragma once
+#include <type_traits>
+#include <utility>
+
 #include "swconv_kernels.hpp"
 
 namespace swconv {
@@ -32,14 +35,16 @@ __device__ __forceinline__ void acc_fma(Acc4& y, float c, const Acc4& x) {
 //
 // A workgroup has one slice of one tile block and its NW waves share the positions, P / NW each.  Nothing is staged: a
 // wave reads the row of V of a non-zero - 256 bytes a quarter - from the L2 when it multiplies by it, up to
-// sixteen steps in flight.  The products of all positions meet in LDS, where four waves, one a row, transform them and
+// sixteen steps in flight, or 24 where workgroups have a CU to themselves.  The products of all positions meet in LDS, where four waves, one a row, transform them and
 // store the outputs.  The sums are those of the product and the output transform as two kernels, bit for bit.
 // What bounds it is the way of the rows: 256 bytes for every non-zero and tile block, without reuse, at 12 TB/s over all
 // CUs (32 x 27 x 27, 48 -> 128 channels: 502 MB in 41.8 us), and for the smallest layers two such ways one after the other
-// (packages, rows).  24 waves a CU: 16 steps in flight take 64 registers of a lane's 80.
+// (packages, rows).  24 waves a CU: 16 steps in flight take 64 registers of a lane's 80.  One image of 13 x 13, 256 -> 384
+// (96 workgroups, slices of 24 to 44 steps), with 16 steps in flight, each batch waited for before the next, and all three
+// batches asked for in front of the lengths: 9.4 us in a rotation of plans that no cache holds and 8.1 repeated; now 8.1 and 7.0.
 // Before, a workgroup of 16 waves had 64 rows of a tile block, a panel and weights in LDS and a barrier per position: 44.9
 // us for that layer, but 36.8 for one image (now 6.2) and 133 for 64 x 56 x 56, 64 -> 64, F(2x2,3x3) (now 107).
-constexpr int kGatherMaxBatches = 3;
+constexpr int kGatherMaxBatches = 3;  // a slice's first two batches are asked for at once, the third by its length
 
 // The lane's four tiles of the rows of steps 4 G .. 4 G + 3: rows of V at `soff`, addressed by the pair's offset, which
 // counts 256 bytes a row, times row_scale.
@@ -79,9 +84,48 @@ __device__ __forceinline__ void gather_batch(__amdgpu_buffer_rsrc_t vr, uint32_t
   if (steps > 3 * kStepGroup) multiply_group<3>(g3, b.y, acc);
 }
 
+template <typename F, int... I>
+__device__ __forceinline__ void for_each_index(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+// The first `steps` (16 (N - 1) + 4 .. 16 N) steps of N batches as one pipeline, the rows of 24 steps in flight together: for
+// workgroups that have a CU to themselves, where nothing else covers the way of the rows and 128 registers are there.  (The
+// scheduling barriers keep it so: left to itself the compiler asks for 12 steps' rows at a time, in 67 registers.)
+template <int N>
+__device__ __forceinline__ void gather_batches(__amdgpu_buffer_rsrc_t vr, uint32_t soff, uint32_t row_scale, uint32_t lane_sub,
+                                               const u32x2_t* b, int steps, Acc4& acc) {
+  constexpr int kGroups = N * kBatchSteps / kStepGroup, kAhead = 6;
+  Group4 g[kGroups];
+  auto load = [&](auto i) {
+    constexpr int I = decltype(i)::value;
+    if constexpr (I < kGroups) g[I] = gather_group<I % 4>(vr, soff, row_scale, lane_sub, b[I / 4].x);
+  };
+  for_each_index(load, std::make_integer_sequence<int, kAhead>{});
+  __builtin_amdgcn_sched_barrier(0);
+  for_each_index(
+      [&](auto i) {
+        constexpr int I = decltype(i)::value;
+        if (I <= 4 * (N - 1) || steps > I * kStepGroup) multiply_group<I % 4>(g[I], b[I / 4].y, acc);
+        load(std::integral_constant<int, I + kAhead>{});
+        __builtin_amdgcn_sched_barrier(0);
+      },
+      std::make_integer_sequence<int, kGroups>{});
+}
+template <int B>
+__device__ __forceinline__ void gather_slice(__amdgpu_buffer_rsrc_t vr, uint32_t soff, uint32_t row_scale, uint32_t lane_sub,
+                                             const u32x2_t (&b)[B], int steps, Acc4& acc) {
+  if (steps > 2 * kBatchSteps) {
+    if constexpr (B == 3) gather_batches<3>(vr, soff, row_scale, lane_sub, b, steps, acc);
+  } else if (steps > kBatchSteps) {
+    if constexpr (B >= 2) gather_batches<2>(vr, soff, row_scale, lane_sub, b, steps, acc);
+  } else if (steps > 0) {
+    gather_batch(vr, soff, row_scale, lane_sub, b[0], steps, acc);
+  }
+}
+
 // Grid: tile blocks * slices.  B batches a slice.
 template <int R, int NW, int B>
-__global__ __launch_bounds__(NW * 64, 6) void product_output_kernel(
+__global__ __launch_bounds__(NW * 64, NW == 16 ? 4 : 6) void product_output_kernel(
     const float* __restrict__ V, float* __restrict__ out, const uint32_t* __restrict__ wpk, uint32_t wpk_bytes,
     const uint8_t* __restrict__ lens, const OutTile* __restrict__ otiles, int C, int K, int Tp, int KC,
     int n_slices, uint32_t v_bytes, uint32_t plane, int Wo, uint32_t out_image_stride, uint32_t out_bytes) {
@@ -98,25 +142,41 @@ __global__ __launch_bounds__(NW * 64, 6) void product_output_kernel(
   const int kc = slice / kFusedWaves, w = slice % kFusedWaves;
   const __amdgpu_buffer_rsrc_t vr = make_rsrc(V, v_bytes), wr = make_rsrc(wpk, wpk_bytes);
   const u32x4_t o = *reinterpret_cast<const u32x4_t*>(otiles + (size_t)tb * TB + lane);  // (n, pix, valid, -)
+  // The first two batches come with the lengths, a third where the length says that there is one (parked otherwise: no
+  // memory is touched).
+  constexpr int kAtOnce = B < 2 ? B : 2;
   u32x2_t b[PPW][B];
   int len[PPW];
 #pragma unroll
   for (int i = 0; i < PPW; ++i) {
     const int p = wave * PPW + i;
-    len[i] = __builtin_amdgcn_readfirstlane((int)lens[((size_t)p * KC + kc) * kFusedWaves + w]);
+    len[i] = (int)lens[((size_t)p * KC + kc) * kFusedWaves + w];
 #pragma unroll
-    for (int u = 0; u < B; ++u)
+    for (int u = 0; u < kAtOnce; ++u)
       b[i][u] = __builtin_amdgcn_raw_buffer_load_b64(wr, lane * 8, (int)(((((uint32_t)p * KC + kc) * B + u) * kFusedWaves + w) * 512u), 0);
+  }
+#pragma unroll
+  for (int i = 0; i < PPW; ++i) {
+    len[i] = __builtin_amdgcn_readfirstlane(len[i]);
+    if constexpr (B > kAtOnce) {
+      const uint32_t at = ((((uint32_t)(wave * PPW + i) * KC + kc) * B + kAtOnce) * kFusedWaves + w) * 512u;
+      b[i][kAtOnce] =
+          __builtin_amdgcn_raw_buffer_load_b64(wr, lane * 8, (int)(len[i] > kAtOnce * kBatchSteps ? at : 0xfffff000u), 0);
+    }
   }
 #pragma unroll
   for (int i = 0; i < PPW; ++i) {
     const int p = wave * PPW + i;
     const uint32_t soff = ((uint32_t)p * C * Tp + (uint32_t)tb * TB) * 4u, scale = (uint32_t)Tp / TB;  // 256 c -> 4 c Tp
     Acc4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    if constexpr (NW == 16) {
+      gather_slice(vr, soff, scale, lane_sub, b[i], len[i], acc);
+    } else {
 #pragma unroll
-    for (int u = 0; u < B; ++u) {
-      const int steps = len[i] - u * kBatchSteps;
-      if (steps > 0) gather_batch(vr, soff, scale, lane_sub, b[i][u], steps, acc);
+      for (int u = 0; u < B; ++u) {
+        const int steps = len[i] - u * kBatchSteps;
+        if (steps > 0) gather_batch(vr, soff, scale, lane_sub, b[i][u], steps, acc);
+      }
     }
     const f32x4_t m = {acc.a0, acc.a1, acc.a2, acc.a3};
     *reinterpret_cast<f32x4_t*>(&m_lds[p][lane >> 4][(lane & 15) * 4]) = m;
