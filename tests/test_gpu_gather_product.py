@@ -52,6 +52,9 @@ def csr(P, K, C, length, rng):
     (2, 70, 9, 12, 131, 33, True),   # three
     (2, 70, 9, 12, 3, 49, False),    # longer than the packages hold: three kernels
     (7, 300, 10, 11, 259, 12, True),  # more workgroups than there are CUs
+    (7, 70, 10, 11, 259, 17, True),   # ... and two batches
+    (7, 70, 10, 11, 259, 33, True),   # ... and three
+    (7, 70, 10, 11, 259, 48, True),
 ])
 def test_equals_the_three_kernels(r, N, C, H, W, K, longest, one, monkeypatch):
     rng = np.random.default_rng(longest + r)
