@@ -518,15 +518,22 @@ void build_transform_tables(swconv_plan* pl) {
 }
 
 // Whether steps 2 and 3 of an m = 2 layer take less time as product_output_kernel, whose time grows with what it reads - 256
-// bytes a non-zero and tile block, 85 us a GB - than as two kernels, which write and read M: 0.4 us a MB while the
-// Infinity Cache holds it and V, about twice that beyond, and a launch.  Measured (reads / M in MB, us a forward pass as
-// two and as three kernels): F(2x2,5x5), 48 -> 128, 27 x 27: 1 image 17 / 3.4 10.5 and 13.6, 8 129 / 28 23.7 and 26.5, 16 254 / 55
-// 36.2 and 36.3, 32 502 / 110 54.1 and 59.8, 64 1000 / 220 97 and 165; F(2x2,3x3), 27 x 27, 64 -> 128: 8 82 / 12 15.7 and
-// 20.7, 32 317 / 49 38.1 and 36.9; 13 x 13, 128 -> 384: 64 960 / 74 70 and 48; 256 -> 384: 1 67 / 1 11.5 and 12.5, 4 155 / 5
-// 17.8 and 16.2; 64 of 56 x 56, 64 -> 64: 1256 / 196 153 and 219; 32 -> 32 at 20 %: 628 / 98 66 and 93.
-bool gather_pays(const swconv_plan* pl) {
-  const double mb = 1 << 20, reads = (double)pl->fw.nnz * pl->n_tau_blocks * 256.0 / mb, m = pl->g.m_bytes / mb;
-  return reads <= (m >= 96 ? 8 * m : 100 + 2.5 * m);
+// bytes a non-zero and tile block, about 6 us and 60 us a GB - than as two kernels, which read V and write and read M: 6 us,
+// 0.2 us a MB of V and 0.5 us a MB of M while the Infinity Cache holds them, about twice that beyond, and a launch.  In the
+// 5x5 kernel a wave has three positions one behind the other, and every further batch of a slice is another way to the L2
+// for each.  The line minimises the loss over 170 random layers of 1 to 64 images of 7 to 63 pixels, repeated and in
+// rotations of plans that no cache holds (mean loss against the better kernel 0.8 %, of one kernel always 1.5 %, of two always
+// 23 %).  Reads, V, M in MB and us a pass as one and as two kernels, repeated; in rotation: F(2x2,3x3), 13 x 13,
+// 256 -> 384, 1 image 38, 1, 2 11.2 and 12.2; 10.9 and 13.4, 4 images 154, 4, 6 17.4 and 15.9; 17.4 and 16.6; 56 x 56,
+// 32 -> 32 at 20 %, 24 images 235, 37, 37 29.4 and 37.6; 34.7 and 49.4, 62 images 608, 95, 95 62.4 and 85.1; 77 and 120; 27 x 27,
+// 64 -> 128, 32 images 314, 24, 49 36.3 and 34.7; 36.1 and 44.1; 13 x 13, 128 -> 384, 64 images 941, 24, 74 65.8 and 44.3; 70.9 and
+// 62.4; 56 x 56, 64 -> 64, 64 images 1254, 196, 196 157 and 209; 153 and 206; F(2x2,5x5), 27 x 27, 48 -> 128, 8 images 127,
+// 11, 28 23.4 and 26.0; 20.6 and 28.0, 32 images 497, 41, 110 52.7 and 56.5; 49.5 and 79.8; 33 x 33, 79 -> 33 at 19 % (two
+// batches), 13 images 257, 41, 17 36.2 and 28.2; 35.8 and 32.9.
+bool gather_pays(const swconv_plan* pl, int batches) {
+  const double mb = 1 << 20, reads = (double)pl->fw.nnz * pl->n_tau_blocks * 256.0 / mb;
+  const double v = pl->g.v_bytes / mb, m = pl->g.m_bytes / mb;
+  return reads <= 110 + 2.5 * v + 2.75 * m + std::max(0.0, v + m - 128) - (pl->r == 5 ? 30 * (batches - 1) : 0);
 }
 
 // Sizes of W_F's package format for the fused kernel; false (and the three-kernel path runs) when the layer is
@@ -540,7 +547,7 @@ bool size_fused(swconv_plan* pl, int longest_row) {
   if (units) {
     fz.B = (fz.B + 1) / 2 * 2;
     if (fz.B > kFused4MaxBatches) return false;
-  } else if (fz.B > kGatherMaxBatches || !(fz.always || gather_pays(pl))) {
+  } else if (fz.B > kGatherMaxBatches || !(fz.always || gather_pays(pl, fz.B))) {
     return false;
   }
   fz.n_dwords = (size_t)pl->P * fz.KC * fz.B * kFusedWaves * 128;

@@ -83,7 +83,7 @@ def test_inside_larger_tensors(r, monkeypatch):
 
 
 @pytest.mark.parametrize("N,C,H,W,K,r,density,one", [
-    (1, 256, 13, 13, 384, 3, 0.1, True),    # 67 MB of rows, M of 1 MB
+    (1, 256, 13, 13, 384, 3, 0.1, True),    # 38 MB of rows, M of 2 MB
     (4, 256, 13, 13, 384, 3, 0.1, False),   # 155 and 5: M is the smaller matter
     (32, 48, 27, 27, 128, 5, 0.094, True),  # 502 and 110
     (32, 64, 27, 27, 128, 3, 0.1, False),   # 317 and 49
@@ -92,3 +92,11 @@ def test_route_by_size(N, C, H, W, K, r, density, one, monkeypatch):
     rp, ci, va = synth.bernoulli_weights((r + 1) ** 2, K, C, density, 3)
     x = synth.activations(N, C, H, W, 5)
     assert forward("1", monkeypatch, x, rp, ci, va, K, r, r // 2)[1] == one
+
+
+@pytest.mark.parametrize("N", [24, 56, 61, 62, 64])
+def test_route_does_not_jump_with_the_batch(N, monkeypatch):
+    """56 x 56, 32 -> 32 channels at 20 %: M passes 96 MB between 62 and 63 images; one kernel is the faster way for all."""
+    rp, ci, va = synth.bernoulli_weights(16, 32, 32, 0.2, 3)
+    x = np.zeros((N, 32, 56, 56), np.float32)
+    assert forward("1", monkeypatch, x, rp, ci, va, 32, 3, 1)[1]
