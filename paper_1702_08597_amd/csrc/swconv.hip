@@ -1330,10 +1330,12 @@ int backward_ready(swconv_plan* pl, hipStream_t st, const float* in_dev, const f
 }
 
 // Whether the launch of stage 5 does the work of stage 3 as well: where the one-kernel input gradient makes one pass of
-// 64 tiles its workgroups hold at most 18 KB of LDS, so that as many of the sums' workgroups share a CU as by themselves.
-// Both then take little more than the longer of them (64 x 13 x 13, 384 -> 384: 11.4 + 15.8 -> 24.1 us; 32 x 13 x 13,
-// 256 -> 384: 6.9 + 7.2 -> 10.3; F(4x4,5x5), 32 x 27 x 27, 48 -> 128: 4.5 + 10.6 -> 11.8).  The kernels of several passes leave room for two or three workgroups a CU, which a
-// sum of 120 MB would be slower with.
+// 64 tiles.  The sums' workgroups then have that kernel's registers (134 with F(4x4,5x5): three workgroups a CU) and LDS (9
+// to 18 KB mostly, up to 66 KB where small unpadded images make one tile each), by themselves 18 registers and none; what
+// they lose by it is less than a launch and its ramp.  Whole fine-tuning steps, two launches against one, us: 64 x 13 x 13,
+// 384 -> 384 175.6 and 171.6; 32 x 13 x 13, 256 -> 384 85.2 and 80.7; F(4x4,5x5), 32 x 27 x 27, 48 -> 128 83.2 and 80.0; 64 x 16 x
+// 16, 128 -> 256 at 30 % 170.0 and 167.4; unpadded F(4x4,5x5), 8 x 8, 1024 images 154.8 and 151.1 (66 KB); F(4x4,3x3), 6 x 6,
+// 256 -> 384, 64 images 114.4 and 109.7, 2048 691 and 684 (37 KB).  The kernels of several passes are not built with the sums.
 bool sums_with_input_grad(const swconv_plan* pl, const float* in, const float* din, const float* dvals) {
   const int G = pl->grad_images_per_group;
   if (!backward_stage_runs(pl, 3, in, din, dvals) || !backward_stage_runs(pl, 5, in, din, dvals)) return false;
