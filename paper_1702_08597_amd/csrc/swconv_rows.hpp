@@ -23,9 +23,10 @@ constexpr int kPruneThreads = 256;
 constexpr int kPruneRows = kPruneThreads / kPruneRowLanes;
 
 // Up to here the second of them finds its row pointers itself, from one sum per workgroup of the first: a thread then
-// reads at most kPruneLocalTurns of them.  (The sums that all workgroups read together grow with the square of the rows:
-// at 65536 rows 4096 workgroups of at most 16 KB, 32 MB through the L2s; beyond, the scan's launch costs less.)
-constexpr int kPruneLocalTurns = 16;
+// reads at most kPruneLocalTurns of them.  (The sums that all workgroups read together grow with the square of the rows.
+// Whole steps without and with a scan between the two, 3 and 25 entries a row, us: 13 824 rows 8.6, 10.0 and 12.8, 14.3;
+// 24 576 12.3, 14.0 and 18.7, 20.9; 32 768 20.3, 23.3 and 19.7, 22.4; 49 152 36.3, 39.8 and 27.5, 31.7; 65 536 50.6, 55.8 and 34.5, 39.8.)
+constexpr int kPruneLocalTurns = 8;
 constexpr int64_t kPruneLocalRows = (int64_t)kPruneLocalTurns * kPruneThreads * kPruneRows;
 
 // Their workgroups: one per kPruneRows rows up to 2^23; beyond 2^27 rows a workgroup takes more than one turn.  A launch

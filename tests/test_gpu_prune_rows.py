@@ -1,5 +1,5 @@
 """Row counts around the workgroups (16 rows) and turns (256 workgroups) of the pruning step without a scan, and around
-the most rows it is used for (65536), each three times: which workgroups find their predecessors' entries already put
+the most rows it is used for (32768), and a power of two behind, each three times: which workgroups find their predecessors' entries already put
 right differs from run to run, the result does not.  Bit for bit against the oracle."""
 import numpy as np
 import pytest
@@ -10,7 +10,7 @@ from test_gpu_prune_parity import gpu_prune
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("rows", [1, 16, 17, 32, 4095, 4096, 4097, 8193, 65535, 65536, 65537])
+@pytest.mark.parametrize("rows", [1, 16, 17, 32, 4095, 4096, 4097, 8193, 32767, 32768, 32769, 65535, 65536, 65537])
 def test_row_pointers_without_a_scan(rows):
     rng = np.random.default_rng(rows)
     lens = rng.choice([0, 1, 5, 16, 17], size=rows)
