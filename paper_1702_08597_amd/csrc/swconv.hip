@@ -322,11 +322,10 @@ int launch_output_transform(const swconv_plan* pl, const LaunchTarget& to, const
   return launch_kernel(kern, grid, dim3(256), lds, to, Mbuf, out, pl->d_tiles, pl->d_blocks, pl->g);
 }
 
-// The operands of a pass over the packed operand `pm`: panels of X (pm.cols rows of Tp tiles per position,
-// x_bytes in all); Y and Z have pm.rows rows per position.
+// The operands of a pass over the packed operand `pm`: panels of X (pm.cols rows of Tp tiles per position);
+// Y and Z have pm.rows rows per position.
 struct SpmmArgs {
   const float* X;
-  uint32_t x_bytes;
   float* Y;            // products
   uint32_t y_bytes;
   const float* Z;      // rows of the dot products
@@ -345,7 +344,7 @@ int launch_spmm_t(const swconv_plan* pl, const PackedMatrix& pm, const LaunchTar
   }
   return launch_kernel(kern, dim3(pm.n_wgs_used), dim3(NW * 64), lds, to, a.X, a.Y, pm.d_stream,
                        (uint32_t)(pm.n_pairs * 2 * sizeof(uint32_t)), pm.d_slices, pm.n_slices,
-                       pm.d_items, pm.d_ranges, pm.n_wgs_used, pm.cols, pm.rows, pl->g.Tp, a.y_bytes, a.x_bytes, a.Z,
+                       pm.d_items, pm.d_ranges, pm.n_wgs_used, pm.cols, pm.rows, pl->g.Tp, a.y_bytes, a.Z,
                        a.partial, (uint32_t)pm.n_pairs);
 }
 
@@ -375,9 +374,9 @@ int launch_spmm(const swconv_plan* pl, const PackedMatrix& pm, const LaunchTarge
 }
 
 // Y[p] = A[p] * X[p]
-int launch_product(const swconv_plan* pl, const PackedMatrix& pm, const LaunchTarget& to, const float* X,
-                   uint32_t x_bytes, float* Y, uint32_t y_bytes) {
-  return launch_spmm<false>(pl, pm, to, SpmmArgs{X, x_bytes, Y, y_bytes, nullptr, nullptr});
+int launch_product(const swconv_plan* pl, const PackedMatrix& pm, const LaunchTarget& to, const float* X, float* Y,
+                   uint32_t y_bytes) {
+  return launch_spmm<false>(pl, pm, to, SpmmArgs{X, Y, y_bytes, nullptr, nullptr});
 }
 
 template <int R, int NW, int B>
@@ -444,7 +443,7 @@ int launch_stage(const swconv_plan* pl, const LaunchTarget& to, int stage, const
   switch (stage) {
     case 0:
       return dispatch_mr(pl, [&](auto M, auto R) { return launch_input_transform<M(), R()>(pl, to, in, ws.V); });
-    case 1: return launch_product(pl, pl->fw, to, ws.V, pl->g.v_bytes, ws.M, pl->g.m_bytes);
+    case 1: return launch_product(pl, pl->fw, to, ws.V, ws.M, pl->g.m_bytes);
     default:
       return dispatch_mr(pl, [&](auto M, auto R) { return launch_output_transform<M(), R()>(pl, to, ws.M, out); });
   }
@@ -1356,14 +1355,14 @@ int launch_backward_stage(swconv_plan* pl, const LaunchTarget& to, int stage, co
     case 1: return launch_stage(pl, to, 0, in_dev, nullptr);
     case 2:
       return launch_spmm<true>(pl, pl->bt, to,
-                               SpmmArgs{pl->dM, pl->g.m_bytes, pl->dD, pl->g.v_bytes, pl->dV, pl->d_partial});
+                               SpmmArgs{pl->dM, pl->dD, pl->g.v_bytes, pl->dV, pl->d_partial});
     case 3: {
       if (together) return SWCONV_OK;
       const PartialSums sums = partial_sums(pl, dvals_dev);
       return launch_kernel(weight_grad_reduce_kernel, dim3((sums.n_entries + kReduceThreads - 1) / kReduceThreads),
                            dim3(kReduceThreads), 0, to, sums);
     }
-    case 4: return launch_product(pl, pl->bt, to, pl->dM, pl->g.m_bytes, pl->dD, pl->g.v_bytes);
+    case 4: return launch_product(pl, pl->bt, to, pl->dM, pl->dD, pl->g.v_bytes);
     default:
       return dispatch_mr(pl, [&](auto M, auto R) {
         return launch_backward_transforms<M(), R()>(pl, to, stage - 4, nullptr, din_dev, together ? dvals_dev : nullptr);
@@ -1737,7 +1736,7 @@ int swconv_profile_backward(swconv_plan* pl, void* hip_stream, const float* in_d
   // behind each, it took the next one's first kernel from 8.5 to 14 us (N = 32, 256 -> 384: dL/dO no longer in the L2).
   for (int it = 0; it < iters && !rc && joint; ++it) {
     hipEvent_t* e = &ev[((size_t)it * kBackwardStages + 4) * 2];
-    rc = launch_product(pl, pl->bt, LaunchTarget{st, e[0], e[1]}, pl->dM, pl->g.m_bytes, pl->dD, pl->g.v_bytes);
+    rc = launch_product(pl, pl->bt, LaunchTarget{st, e[0], e[1]}, pl->dM, pl->dD, pl->g.v_bytes);
   }
   if (hipStreamSynchronize(st) != hipSuccess) rc = rc ? rc : SWCONV_EHIP;
   if (!rc) {
@@ -1907,7 +1906,7 @@ int swconv_debug_copy_M(swconv_plan* pl, float* M_host) {
   if (!pl->ran_forward) return SWCONV_ESTATE;
   if (!pl->m_current) {  // the fused kernel kept the products on chip: run step 2 alone on the V of that pass
     HIP_TRY(hipDeviceSynchronize());
-    int rc = launch_product(pl, pl->fw, LaunchTarget{nullptr, nullptr, nullptr}, pl->dV, pl->g.v_bytes, pl->dM, pl->g.m_bytes);
+    int rc = launch_product(pl, pl->fw, LaunchTarget{nullptr, nullptr, nullptr}, pl->dV, pl->dM, pl->g.m_bytes);
     if (rc) return rc;
     pl->m_current = true;
   }

@@ -540,7 +540,7 @@ template <int NWAVES, int PIECES, bool DOTS, bool LONG>
 __global__ __launch_bounds__(NWAVES * 64, NWAVES == 12 ? 6 : 4) void spmm_kernel(
     const float* __restrict__ V, float* __restrict__ Mbuf, const uint32_t* __restrict__ stream, uint32_t stream_bytes,
     const Slice* __restrict__ slices, int n_slices, const WorkItem* __restrict__ items,
-    const RangeHeader* __restrict__ ranges, int n_wgs, int C, int K, int Tp, uint32_t m_bytes, uint32_t v_bytes,
+    const RangeHeader* __restrict__ ranges, int n_wgs, int C, int K, int Tp, uint32_t m_bytes,
     const float* __restrict__ zrows, float* __restrict__ partial, uint32_t partial_stride) {
   constexpr int NT = NWAVES * 64;
   constexpr int TB = kTileBlock;
