@@ -28,7 +28,7 @@ using namespace swconv;
 namespace {
 
 constexpr int kMaxLdsBytes = 160 * 1024;
-constexpr int kSpmmLdsExtra = 64;    // the sparse product's slice counter sits behind the panel, then the slice descriptors
+constexpr int kSpmmLdsExtra = 64;    // the sparse product's slice counter, in front of the panel; the slice descriptors are behind it
 
 int env_int(const char* name, int dflt) {
   const char* s = std::getenv(name);
@@ -148,8 +148,8 @@ struct PackedMatrix {
   size_t cap_tables = 0;
 };
 
-// W_F packed for the fused product + output transform kernel (m = 2, few input channels): rows in
-// their natural order, 64 per workgroup, one package of 16-step batches per position.
+// W_F packed for the kernels that run steps 2 and 3 together: rows in their natural order, one package of 16-step
+// batches per position and chunk of 64 rows.
 struct FusedProduct {
   int out_tile = 0;       // m of the kernel that would run: 2 (product_output_kernel) or 4 (product_output4_kernel)
   bool eligible = false;  // the layer shape allows the kernel; m = 4: and it was asked for
@@ -854,8 +854,8 @@ void pack_matrix(PackedMatrix* pm, int P, int ntb, const int32_t* rowptr, const 
     pm->padded_nnz += (int64_t)sl.len * kSliceRows;
   }
   // an entry is (byte offset of the panel row of its column, weight); padding = row 0, weight +0.0f.
-  // The kernel addresses the stream with 32-bit byte offsets and fetches up to two batches past a
-  // slice's end: two spare batches keep even those inside the allocation.
+  // The kernel addresses the stream with 32-bit byte offsets and asks for up to four batches ahead of what it uses:
+  // what lies behind the two spare ones reads 0 by the buffer descriptor's bound and touches no memory.
   const uint64_t spare0 = cursor;
   cursor += 2;
   if (cursor * 512 >= ((uint64_t)1 << 32) - 4096) throw std::bad_alloc();
@@ -1201,7 +1201,7 @@ int prepare_backward(swconv_plan* pl, hipStream_t st) {
     PositionStats stats[kMaxPositions];
     HIP_TRY(hipStreamSynchronize(st));
     HIP_TRY(hipMemcpy(stats, bt.tables.stats, (size_t)P * sizeof(PositionStats), hipMemcpyDeviceToHost));
-    uint64_t batches = 2;  // the product fetches up to two batches past a slice's end
+    uint64_t batches = 2;  // spare ones, as behind a stream that the host packs
     longest = 0;
     for (int p = 0; p < P; ++p) {
       batches += (uint64_t)stats[p].batches;
@@ -1828,7 +1828,7 @@ int swconv_set_weights_device(swconv_plan* pl, void* hip_stream, const int32_t* 
   pl->stays = pattern_stays(pl);
   weights_replaced(pl);
   fw.on_device = fw.packed = fw.index_current = fw.host_current = false;
-  uint64_t batches = 2;  // the product fetches up to two batches past a slice's end
+  uint64_t batches = 2;  // spare ones, as behind a stream that the host packs
   int longest = 0;
   fw.padded_nnz = 0;
   for (int p = 0; p < P; ++p) {

@@ -443,8 +443,8 @@ __device__ __forceinline__ void fill_slice(int p, int s, int rows_padded, int ba
   }
 }
 
-// Pairs behind the last slice (the loop of the product fetches up to two batches past a slice's end), one of
-// kPackSpareWgs workgroups' share of them.
+// Pairs behind the last slice, up to the size the buffers were given (the value update and the weight gradient's sums
+// walk them all), one of kPackSpareWgs workgroups' share of them.
 __device__ __forceinline__ void fill_spare(const PackTables& t, int P, const PackedOut& out, int part) {
   const uint32_t used = (uint32_t)(position_batch0(t.stats, P - 1) + t.stats[P - 1].batches) * 64u;
   for (uint32_t pair = used + part * kPackThreads + threadIdx.x; pair < out.n_pairs; pair += kPackSpareWgs * kPackThreads) {
