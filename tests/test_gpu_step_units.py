@@ -1,7 +1,7 @@
 """The inner loops of the sparse product where they can go wrong: slices of every number of steps (units of two batches,
 their exits after each group of four steps, slices of none, one and several units), plans with and without slices of more
 than 32 steps, every size of panel a workgroup stages, items that are ragged (few rows, one tile, several tile blocks),
-and weights the broadcast has to carry unchanged (denormal, huge, negative zero).
+plans whose rows pass 32 entries and come back, and weights the broadcast has to carry (denormal, huge, infinite, NaN).
 
 Integer data: M and the backward pass's D and dvals equal to the oracle bit for bit."""
 import numpy as np
@@ -63,16 +63,14 @@ def test_slices_of_every_length(C, K, longest):
     np.testing.assert_array_equal(dvals.astype(np.float64), dvals64)
 
 
-def test_weights_are_broadcast_unchanged():
-    """One entry a row, so that every product is one multiplication: the single float product, bit for bit."""
+def products_of_single_entries(special, seed):
+    """M and what numpy makes of it, for one entry a row: every product is one multiplication."""
     N, C, H, W, K, m, P = 2, 130, 6, 6, 22, 2, 16
-    rng = np.random.default_rng(3)
+    rng = np.random.default_rng(seed)
     rp, ci, va = rows_of_lengths(P, K, C, lambda p, k: 1, rng)
-    special = np.array([1e-45, -1e-45, 1.17e-38, -3.3e-39, 3.4e38, -3.4e38, -0.0, 1.0, -1.5, 2.0 ** -126], np.float32)
-    va = special[rng.integers(0, len(special), size=len(va))]
+    va = np.array(special, np.float32)[rng.integers(0, len(special), size=len(va))]
     x = np.zeros((N, C, H, W), np.float32)
     x[:, :, ::2, ::2] = rng.integers(0, 2, size=(N, C, 3, 3))  # V holds small integers
-    G = np.zeros((N, K, H, W), np.float32)
     plan = sw.swconv_plan_create(N, C, H, W, K, m, 3, 1)
     try:
         sw.swconv_set_weights(plan, rp, ci, va)
@@ -82,6 +80,45 @@ def test_weights_are_broadcast_unchanged():
     finally:
         sw.swconv_plan_destroy(plan)
     col = ci.reshape(P, K)
-    with np.errstate(over="ignore"):
+    with np.errstate(over="ignore", invalid="ignore"):
         want = va.reshape(P, K, 1) * np.stack([V[p][col[p]] for p in range(P)]) + np.float32(0)
+    assert M.dtype == want.dtype == np.float32
+    return M, want
+
+
+def test_weights_are_broadcast_unchanged():
+    """The single float product, bit for bit.  (A weight of -0 comes out as +0, which no sum that starts at +0 shows.)"""
+    M, want = products_of_single_entries([1e-45, -1e-45, 1.17e-38, -3.3e-39, 3.4e38, -3.4e38, -0.0, 1.0, -1.5, 2.0 ** -126], 3)
+    np.testing.assert_array_equal(M.view(np.uint32), want.view(np.uint32))
+
+
+def test_infinite_and_nan_weights_stay_in_their_rows():
+    """Four rows share a slice, a matrix instruction and their registers."""
+    M, want = products_of_single_entries([np.inf, -np.inf, np.nan, 1.0, -2.0, 0.5], 4)
+    assert np.isnan(want).any() and np.isinf(want).any() and np.isfinite(want).any()
     np.testing.assert_array_equal(M, want)
+
+
+@pytest.mark.parametrize("C,K", [(70, 40), (330, 24)])
+def test_rows_pass_32_entries_and_come_back(C, K):
+    """The product is built for rows of up to 32 entries and for longer ones: new patterns on the device move a plan from
+    one to the other."""
+    N, H, W, m, P = 5, 9, 11, 2, 16
+    rng = np.random.default_rng(C)
+    x = rng.integers(0, 4, size=(N, C, H, W)).astype(np.float32)
+    xd, out = torch.from_numpy(x).cuda(), torch.empty((N, K, H, W), device="cuda")
+    plan = sw.swconv_plan_create(N, C, H, W, K, m, 3, 1)
+    try:
+        for longest in (32, 33, 31, 65, 32, 1):
+            print("case", C, K, longest, flush=True)
+            rp, ci, va = rows_of_lengths(P, K, C, lambda p, k: (p * 7 + k * 5) % longest if (p, k) != (3, 2) else longest, rng)
+            dev = [torch.from_numpy(a).cuda() for a in (rp, ci, va)]
+            sw.swconv_set_weights_device(plan, 0, *(d.data_ptr() for d in dev))
+            sw.swconv_debug_check_schedule(plan)
+            sw.swconv_forward(plan, 0, xd.data_ptr(), out.data_ptr())
+            M = sw.swconv_debug_copy_M(plan, K)
+            ref, _, M64 = oracle.forward_f64(x, rp, ci, va, K, m)
+            np.testing.assert_array_equal(M.astype(np.float64), M64)
+            np.testing.assert_array_equal(out.cpu().numpy().astype(np.float64), ref)
+    finally:
+        sw.swconv_plan_destroy(plan)
