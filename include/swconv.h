@@ -113,8 +113,8 @@ int swconv_set_weights(swconv_plan* plan, const int32_t* rowptr, const int32_t* 
  * after enqueueing, does not synchronise.  For m = 2 layers
  * whose rows have at most 48 stored entries (the 5x5 layer of Section 6) steps 2 and 3 run as
  * ONE kernel that keeps the per-position products on chip (Section 5: a core that owns its
- * tiles through all steps can fuse the second and third), where that is the faster way by the number
- * of tiles and stored entries; the results are the same bits either way.  The environment variable
+ * tiles through all steps can fuse the second and third), where that is the faster way by what
+ * it reads against what V and M cost; the results are the same bits either way.  The environment variable
  * SWCONV_FUSE_OUTPUT=0, read by swconv_plan_create, keeps such a plan on three kernels;
  * SWCONV_FUSE_OUTPUT=2 runs the one kernel whatever the sizes,
  * and also runs F(4x4,3x3) layers with C a multiple of 4, C <= 256 and rows of

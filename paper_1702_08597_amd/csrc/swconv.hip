@@ -392,8 +392,8 @@ int launch_product_output_t(const swconv_plan* pl, const LaunchTarget& to, const
 }
 
 int launch_product_output(const swconv_plan* pl, const LaunchTarget& to, const float* V, float* out) {
-  // F(2x2,3x3), 16 positions: two to a wave, or one where there is at most one workgroup for each CU anyway (one image of
-  // 13 x 13, 256 -> 384: 6.9 against 8.0 us)
+  // F(2x2,3x3), 16 positions: two to a wave, or one, with more rows in flight, where there is at most one workgroup for each
+  // CU anyway (one image of 13 x 13, 256 -> 384: 6.5 against 8.0 us; 1 x 27 x 27, 128 -> 128 at 20 %: 6.6 and 7.7)
   const bool one_each = (int64_t)pl->n_tau_blocks * ((pl->g.K + kSliceRows - 1) / kSliceRows) <= pl->fw.cus;
   auto with = [&](auto b) {
     constexpr int B = decltype(b)::value;
