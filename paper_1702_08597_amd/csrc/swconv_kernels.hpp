@@ -525,9 +525,9 @@ __device__ __forceinline__ float product_dots_batch(const f32x4_t& lane_base4, f
 // against 10.3 us).
 // What it takes (us, before: DPP broadcasts, panel pieces written to LDS by 4-byte words because the array's declared
 // alignment was that of a float, the panel asked for behind an item's last slice, and a draw of a slice 25 instructions
-// longer): 64 x 13 x 13, 384 -> 384 at 10 %: 42.1 -> 37; 384 -> 256 at 30 %: 67 -> 59.5 (37 TFLOP/s); 32 x 13 x 13,
-// 256 -> 384: 18.8 -> 16.8; 32 x 56 x 56, 256 -> 256: 142 -> 132, of which 118 remain without the inner loop (V and M
-// go through memory).  Both gradients in one pass: 69 -> 65, 222 -> 204 (56 x 56), 30.1 -> 26.6.
+// longer): 64 x 13 x 13, 384 -> 384 at 10 %: 42.1 -> 36; 384 -> 256 at 30 %: 67 -> 57 (38 TFLOP/s); 32 x 13 x 13,
+// 256 -> 384: 18.8 -> 16.5; 32 x 56 x 56, 256 -> 256: 142 -> 129, and of 132 there remained 118 without the inner loop (V and M
+// go through memory).  Both gradients in one pass: 69 -> 61.5, 222 -> 204 (56 x 56), 30.1 -> 27.
 // Tried and not kept: a wave of its own that loads panels straight into one of two LDS buffers, one barrier an item
 // (15 waves compute): 16.0 for 16.8 and 9.1 for 9.7 us on the two small layers, 135 for 132 and 220 for 205 on the
 // 56 x 56 one; drawing a slice under the unit in front instead of before it: 17.2 for 16.6.
